@@ -181,13 +181,13 @@ int stats_roundtrip(HostStage &hs, const pm_layout *L, int64_t count, const pm_c
 
 // Validation + statistics round trip and planning for `count` products.
 int stats_and_plan(HostStage &hs, const pm_layout *L, int64_t count, const pm_cpoly *f, const pm_cpoly *g,
-                   void *dev, hipStream_t st, const Tuning &tune, Plan &P) {
+                   void *dev, hipStream_t st, const Tuning &tune, Plan &P, int64_t limit) {
     std::vector<SegInput> in;
     const uint64_t *stats = nullptr;
     const uint32_t *flags = nullptr;
     int rc = stats_roundtrip(hs, L, count, f, g, dev, st, in, &stats, &flags);
     if (rc) return rc;
-    return plan_build((int)L->nvars, (int)L->bits, L->ring, in, stats, flags, tune, P, device_cus());
+    return plan_build((int)L->nvars, (int)L->bits, L->ring, in, stats, flags, tune, P, device_cus(), true, limit);
 }
 
 // Upload the descriptor block of plan P (output pointers filled) and enqueue
@@ -208,6 +208,10 @@ int upload_descriptors(HostStage &hs, Plan &P, void *ws, hipStream_t st, hipStre
     if (!P.iv_seg.empty()) memcpy(pin + (P.o_iv_seg - d0), P.iv_seg.data(), 4 * P.iv_seg.size());
     if (!P.bk_tile_pre.empty()) memcpy(pin + (P.o_bk_tile_pre - d0), P.bk_tile_pre.data(), 8 * P.bk_tile_pre.size());
     if (!P.bk_seg.empty()) memcpy(pin + (P.o_bk_seg - d0), P.bk_seg.data(), 4 * P.bk_seg.size());
+    if (P.ngp) {
+        memcpy(pin + (P.o_gp_seg - d0), P.gp_seg.data(), 4 * P.gp_seg.size());
+        memcpy(pin + (P.o_gp_sb_pre - d0), P.gp_sb_pre.data(), 8 * P.gp_sb_pre.size());
+    }
     if (!P.bk_sb_pre.empty()) memcpy(pin + (P.o_bk_sb_pre - d0), P.bk_sb_pre.data(), 8 * P.bk_sb_pre.size());
     // the copy runs on `ust` (default: the launch stream); the launch stream
     // then waits for it, so the staging is free once `ust` has run the copy
@@ -266,11 +270,11 @@ int bound_impl(HostStage &hs, const pm_layout *L, int64_t count, const pm_cpoly 
     int rc = hs.device_tmp(need, &dev);
     if (rc) return rc;
     Plan P;
-    rc = stats_and_plan(hs, L, count, f, g, dev, st, tune, P);
+    rc = stats_and_plan(hs, L, count, f, g, dev, st, tune, P, 0);
     if (rc) return rc;
     if (max_terms)
         for (int64_t q = 0; q < count; q++) max_terms[q] = P.bound[q];
-    if (ws_bytes) *ws_bytes = (int64_t)P.total;
+    if (ws_bytes) *ws_bytes = (int64_t)P.report;
     return PM_OK;
 }
 
@@ -281,7 +285,7 @@ int mul_impl(HostStage &hs, const pm_layout *L, int64_t count, const pm_cpoly *f
     if (!ws || ws_bytes < (int64_t)need0) return PM_ENOMEM;
     if ((uintptr_t)ws & 255) return PM_EINVAL;  // kernels use 16-byte loads from workspace regions
     Plan P;
-    int rc = stats_and_plan(hs, L, count, f, g, ws, st, tune, P);
+    int rc = stats_and_plan(hs, L, count, f, g, ws, st, tune, P, ws_bytes);
     if (rc) return rc;
     if ((int64_t)P.total > ws_bytes) return PM_ENOMEM;
     rc = upload_and_launch(hs, P, h, ws, st);
@@ -373,7 +377,7 @@ int pm_mul_batch_drain(const pm_layout *layout, int64_t count, const pm_cpoly *f
         std::vector<SegInput> sub(in.begin() + a, in.begin() + e);
         Plan P;
         const int r = plan_build(nv, (int)layout->bits, layout->ring, sub, stats.data() + (size_t)a * sw,
-                                 flags.data() + (size_t)a * 2, g_tune, P, device_cus());
+                                 flags.data() + (size_t)a * 2, g_tune, P, device_cus(), true, 0);
         if (r) return r;
         size_t dev = al(8 * (size_t)(e - a)), host = 0;
         for (int64_t q = a; q < e; q++) {
@@ -555,7 +559,8 @@ extern "C" int pm_mul_noalloc(const pm_layout *layout, const pm_cpoly *f, const 
     const size_t need0 = stats_region_bytes(1, (int)layout->nvars) + sizeof(DevSeg);
     if (need0 > NOALLOC_SCRATCH) return PM_ENOMEM;
     Plan P;
-    rc = stats_and_plan(g_noalloc_stage, layout, 1, f, g, ws, (hipStream_t)stream, g_tune, P);
+    rc = stats_and_plan(g_noalloc_stage, layout, 1, f, g, ws, (hipStream_t)stream, g_tune, P,
+                        (int64_t)NOALLOC_SCRATCH);
     if (rc) return rc;
     if (P.total > NOALLOC_SCRATCH) {
         set_error("workspace beyond the static scratch of pm_mul_noalloc", hipErrorOutOfMemory);
@@ -587,7 +592,7 @@ int pm_batch_prepare(const pm_layout *layout, int64_t count, const pm_cpoly *f, 
     if (!workspace || workspace_bytes < (int64_t)need0) return PM_ENOMEM;
     if ((uintptr_t)workspace & 255) return PM_EINVAL;
     pm_batch *b = new pm_batch();
-    rc = stats_and_plan(g_stage, layout, count, f, g, workspace, st, g_tune, b->plan);
+    rc = stats_and_plan(g_stage, layout, count, f, g, workspace, st, g_tune, b->plan, workspace_bytes);
     if (!rc && (int64_t)b->plan.total > workspace_bytes) rc = PM_ENOMEM;
     if (rc) {
         delete b;
@@ -667,7 +672,7 @@ int pm_autotune(const pm_layout *layout, const pm_cpoly *f, const pm_cpoly *g, c
     rc = mul_impl(g_stage, layout, 1, f, g, h, workspace, workspace_bytes, st, base, &P0);
     if (rc) return rc;
     if (P0.nseg < 1 || P0.segs[0].mode == SEG_EMPTY) return PM_OK;
-    const bool dense = P0.segs[0].mode == SEG_DENSE;
+    const bool dense = P0.segs[0].mode == SEG_DENSE || P0.segs[0].mode == SEG_GRPD;
     struct Cand {
         int tile_cfg, combine, digits;
     };
@@ -749,11 +754,11 @@ int pm_plan_from_stats(const pm_layout *layout, int64_t count, const int64_t *na
     }
     std::vector<uint32_t> flags(2 * count, 0);
     Plan P;
-    rc = plan_build((int)layout->nvars, (int)layout->bits, layout->ring, in, stats, flags.data(), g_tune, P);
+    rc = plan_build((int)layout->nvars, (int)layout->bits, layout->ring, in, stats, flags.data(), g_tune, P, 256, false);
     if (rc) return rc;
     if (max_terms)
         for (int64_t q = 0; q < count; q++) max_terms[q] = P.bound[q];
-    if (workspace_bytes) *workspace_bytes = (int64_t)P.total;
+    if (workspace_bytes) *workspace_bytes = (int64_t)P.report;
     return PM_OK;
 }
 

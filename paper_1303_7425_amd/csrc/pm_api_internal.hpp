@@ -33,7 +33,7 @@ int stats_roundtrip(HostStage &hs, const pm_layout *L, int64_t count, const pm_c
                     void *dev, hipStream_t st, std::vector<SegInput> &in, const uint64_t **stats,
                     const uint32_t **flags, bool sync = true);
 int stats_and_plan(HostStage &hs, const pm_layout *L, int64_t count, const pm_cpoly *f, const pm_cpoly *g,
-                   void *dev, hipStream_t st, const Tuning &tune, Plan &P);
+                   void *dev, hipStream_t st, const Tuning &tune, Plan &P, int64_t limit);
 // ust: stream of the descriptor copy (null: st); st waits for it.
 int upload_descriptors(HostStage &hs, Plan &P, void *ws, hipStream_t st, hipStream_t ust = nullptr);
 // part: PipelinePart of pm_launch.hpp (default: the whole pipeline).

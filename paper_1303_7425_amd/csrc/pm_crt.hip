@@ -330,7 +330,7 @@ int z192_mul(HostStage &hs, const pm_layout *L, const pm_cpoly *f, const pm_cpol
     const size_t need0 = stats_region_bytes(1, (int)L->nvars) + sizeof(DevSeg);
     if (ws_bytes < (int64_t)need0) return PM_ENOMEM;
     Plan P0;
-    int rc = stats_and_plan(hs, &l64, 1, f, g, ws, st, tune, P0);
+    int rc = stats_and_plan(hs, &l64, 1, f, g, ws, st, tune, P0, 0);
     if (rc) return rc;
     const int64_t B = P0.bound[0], wsub = (int64_t)P0.total;
     const ZLayout z = z_layout(f->n, g->n, B, wsub);
@@ -368,7 +368,7 @@ int z192_mul(HostStage &hs, const pm_layout *L, const pm_cpoly *f, const pm_cpol
         const pm_cpoly fx{f->n, f->keys, fr + X * na};
         const pm_cpoly gx{g->n, g->keys, gr + X * nb};
         const pm_poly hx{B, &ctr->nsub[X], subk + X * B, subc + X * B};
-        rc = mul_impl(hs, &lx, 1, &fx, &gx, &hx, base + z.sub, (int64_t)(z.total - z.sub), st, tune, nullptr);
+        rc = mul_impl(hs, &lx, 1, &fx, &gx, &hx, base + z.sub, ws_bytes - (int64_t)z.sub, st, tune, nullptr);
         if (rc) return rc;
     }
     u64 *mkey = (u64 *)(base + z.mkey), *mres = (u64 *)(base + z.mres);

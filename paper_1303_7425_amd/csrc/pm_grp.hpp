@@ -1,0 +1,1059 @@
+// Prefix groups (SEG_GRP, SEG_GRPD): products whose term pairs are generated
+// where they are summed.  Included by pm_kernels.hip.
+//
+// The mixed-radix compressed key adds digit by digit without carries, so the
+// key of a pair (i, j) splits at any variable boundary into a prefix (the
+// leading gp.d variables, value P_i + P_j) and a low part (below S, the number
+// of cells of the remaining variables).  Sorted operands are runs of terms of
+// equal prefix ("groups"), and the pairs of output prefix b are exactly the
+// blocks (group of prefix p) x (group of prefix b - p).  One workgroup owns a
+// range of consecutive output prefixes ("bins") and forms all of its pairs
+// itself, from contiguous pieces of both operands, in LDS cells: no pair is
+// staged in memory, counted or scattered one by one.  This is Algorithm 1's
+// output interval with FindEdge done once per group instead of once per row.
+//   k_gp_prep    compressed terms, group lists, zeroing of the per-call state
+//   k_gp_lut     first inner term of every prefix; SEG_GRP: pairs per bin, one
+//                addition per pair of groups
+//   k_gp_coarse  SEG_GRPD: pairs per run of gp.K bins
+//   k_gp_cut     bins to work items of about gp.T pairs
+//   k_gp_reduce  work items summed in LDS: sparse results to staging
+//                (SEG_GRP), degree-box cells stored directly (SEG_GRPD)
+//   k_gp_copy    result offsets, keys decompressed, terms to h
+#pragma once
+
+namespace pm {
+
+constexpr int GPP_T = 1024;  // threads of k_gp_prep (four terms each per step)
+
+typedef u32 u32x3 __attribute__((ext_vector_type(3)));
+
+struct GpOperand {
+    const GpTerm *t;
+    const u32 *pfx, *start;
+    u32 n, groups;
+};
+
+__device__ inline GpOperand gp_operand(const Ctx &C, const DevSeg &s, int bq, int side) {
+    GpOperand o;
+    const i64 off = uniform64(side ? s.gp.tg : s.gp.tf);
+    o.t = C.gp_term + off;
+    o.pfx = C.gp_pfx + off;
+    o.start = C.gp_start + off + 2 * bq + side;  // one more entry than terms per operand
+    o.n = uniform32((u32)(side ? s.nb : s.na));
+    o.groups = uniform32(C.gp_ng[2 * bq + side]);
+    return o;
+}
+
+// Workgroups [0, nop): one operand each.  The others clear [zp, zp + zn).
+__global__ __launch_bounds__(GPP_T) void k_gp_prep(Ctx C, int nop, u64 *zp, i64 zn) {
+    if ((int)blockIdx.x >= nop) {
+        for (i64 i = (i64)(blockIdx.x - nop) * GPP_T + threadIdx.x; i < zn; i += (i64)(gridDim.x - nop) * GPP_T)
+            zp[i] = 0;
+        return;
+    }
+    __shared__ u32 s_hi[MAX_VARS], s_lo[MAX_VARS], s_sh[MAX_VARS];
+    __shared__ u64 s_mn[MAX_VARS];
+    __shared__ u32 s_scan[GPP_T / 64];
+    const int bq = blockIdx.x >> 1, side = blockIdx.x & 1;
+    const DevSeg &s = C.segs[C.gp_seg[bq]];
+    const int nv = C.nvars, d = (int)s.gp.d;
+    const VarParam *vp = C.vars + s.var_off;
+    for (int v = threadIdx.x; v < nv; v += GPP_T) {
+        s_hi[v] = v < d ? (u32)(vp[v].stride / s.gp.S) : 0;
+        s_lo[v] = v < d ? 0 : (u32)vp[v].stride;
+        s_sh[v] = vp[v].shift;
+        s_mn[v] = side ? vp[v].ming : vp[v].minf;
+    }
+    __syncthreads();
+    const u64 mask = vp[0].mask;
+    const u64 *key = side ? s.gk : s.fk, *coef = side ? s.gc : s.fc;
+    const i64 n = side ? s.nb : s.na;
+    const i64 off = side ? s.gp.tg : s.gp.tf;
+    GpTerm *out = C.gp_term + off;
+    u32 *pfx = C.gp_pfx + off, *start = C.gp_start + off + 2 * bq + side;
+    const u32 S = s.gp.S, psh = s_sh[d - 1];
+    // coefficient words: 31 and 30 bits mod p, else 32 and 32
+    const u32 csh = C.ring == RING_MODP ? 31 : 32, cmask = C.ring == RING_MODP ? 0x7FFFFFFFu : ~0u;
+    u32 ng = 0;
+    for (i64 b = 0; b < n; b += GPP_T * 4) {
+        const i64 i0 = b + (i64)threadIdx.x * 4;
+        u64 k[4], c[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const i64 i = i0 + e;
+            k[e] = i < n ? key[i] : 0;
+            c[e] = i < n ? coef[i] : 0;
+        }
+        u64 prev = i0 > 0 && i0 < n ? key[i0 - 1] : 0;
+        u32 p[4], lo[4], hd = 0;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            p[e] = lo[e] = 0;
+            for (int v = 0; v < nv; v++) {
+                const u32 x = (u32)(((k[e] >> s_sh[v]) & mask) - s_mn[v]);
+                p[e] += x * s_hi[v];
+                lo[e] += x * s_lo[v];
+            }
+            const i64 i = i0 + e;
+            if (i < n && (i == 0 || ((k[e] ^ prev) >> psh) != 0)) hd |= 1u << e;
+            prev = k[e];
+        }
+        u32 tot;
+        u32 at = ng + block_excl_scan<u32, GPP_T>((u32)__popc(hd), s_scan, tot);
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            const i64 i = i0 + e;
+            if (i < n) out[i] = GpTerm{(u32)c[e] & cmask, (u32)(c[e] >> csh), p[e] * S + lo[e], p[e]};
+            if ((hd >> e) & 1u) {
+                pfx[at] = p[e];
+                start[at] = (u32)i;
+                at++;
+            }
+        }
+        ng += tot;
+    }
+    if (threadIdx.x == 0) {
+        start[ng] = (u32)n;
+        C.gp_ng[2 * bq + side] = ng;
+    }
+}
+
+// lut[b]: first inner term of prefix b or more (b up to and including nbins).
+// SEG_GRP: pairs of every bin, each pair of groups adding its block's size.
+__global__ __launch_bounds__(256) void k_gp_lut(Ctx C) {
+    for (int bq = blockIdx.y; bq < C.ngp; bq += gridDim.y) {
+        const DevSeg &s = C.segs[C.gp_seg[bq]];
+        const int so = (int)uniform32(s.gp.swap);
+        const GpOperand I = gp_operand(C, s, bq, 1 - so), O = gp_operand(C, s, bq, so);
+        const u32 nbins = uniform32(s.gp.nbins);
+        u32 *lut = C.gp_lut + uniform64(s.gp.lut);
+        for (u32 b = blockIdx.x * 256 + threadIdx.x; b <= nbins; b += gridDim.x * 256) {
+            u32 lo = 0, hi = I.groups;
+            while (lo < hi) {
+                const u32 mid = (lo + hi) >> 1;
+                if (I.pfx[mid] < b) lo = mid + 1;
+                else hi = mid;
+            }
+            lut[b] = I.start[lo];
+        }
+        if (s.mode != SEG_GRP) continue;
+        u32 *hist = C.gp_hist + uniform64(s.gp.hist);
+        const u32 nw = gridDim.x * 4;
+        for (u32 o = uniform32(blockIdx.x * 4 + (threadIdx.x >> 6)); o < O.groups; o += nw) {
+            const u32 p = O.pfx[o], r = O.start[o + 1] - O.start[o];
+            for (u32 i = threadIdx.x & 63; i < I.groups; i += 64)
+                atomicAdd(&hist[p + I.pfx[i]], r * (I.start[i + 1] - I.start[i]));
+        }
+    }
+}
+
+// SEG_GRPD: pairs of every run of K bins (the bins of one value of the
+// variables before the last prefix variable), enough to cut the work evenly.
+// A wave takes 16 outer groups and 64 runs of the inner operand, adds up the
+// rows of the groups in one run and meets its runs with them.
+__global__ __launch_bounds__(256) void k_gp_coarse(Ctx C) {
+    const u32 lane = threadIdx.x & 63, nw = gridDim.x * 4;
+    for (int bq = blockIdx.y; bq < C.ngp; bq += gridDim.y) {
+        const DevSeg &s = C.segs[C.gp_seg[bq]];
+        if (s.mode != SEG_GRPD) continue;
+        const GpOperand O = gp_operand(C, s, bq, (int)uniform32(s.gp.swap));
+        const u32 K = uniform32(s.gp.K), nc = uniform32(s.gp.nbins) / K;
+        const u32 *lut = C.gp_lut + uniform64(s.gp.lut);
+        u32 *hist = C.gp_hist + uniform64(s.gp.hist);
+        // pairs in units of 2^gp.csh, so that a count stays below 2^32
+        const u32 csh = uniform32(s.gp.csh);
+        const u32 nq = (nc + 63) / 64;
+        for (u32 x = uniform32(blockIdx.x * 4 + (threadIdx.x >> 6)); x < (O.groups + 15) / 16 * nq; x += nw) {
+            const u32 o = x / nq * 16 + lane, i = x % nq * 64 + lane;
+            const bool in = lane < 16 && o < O.groups;
+            u32 c = ~0u, r = 0, n = 0;
+            if (in) {
+                c = O.pfx[o] / K;
+                r = O.start[o + 1] - O.start[o];
+            }
+            if (i < nc) n = lut[(i + 1) * K] - lut[i * K];
+            u64 todo = __ballot(in);
+            while (todo) {
+                const u32 l = (u32)__ffsll((unsigned long long)todo) - 1;
+                const u32 cc = (u32)__builtin_amdgcn_readlane((int)c, (int)l);
+                const u64 same = __ballot(c == cc);
+                todo &= ~same;
+                u64 rows = 0;
+                for (u64 m = same; m; m &= m - 1)
+                    rows += (u32)__builtin_amdgcn_readlane((int)r, (int)__ffsll((unsigned long long)m) - 1);
+                if (n && cc + i < nc) atomicAdd(&hist[cc + i], (u32)((rows * n + (1u << csh) - 1) >> csh));
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// k_gp_cut: one workgroup per super-bin of GP_SB bins, four bins per thread.
+// A non-empty bin starts a work item when it is the super-bin's first, when
+// the pairs before it cross a multiple of gp.T, when it enters another span of
+// gp.span_bins bins (what the presence bitmap covers), or when it or the bin
+// before it is dense enough to fill direct cells by itself.  Work items keep
+// key order: their places and their staging offsets (at most min(pairs, S)
+// results per bin) are prefix sums over the super-bins, by a look-back.
+// SEG_GRPD: the counted bins are runs of K bins; a run is cut into work items
+// of equal width, as many as its pairs ask for and its cells need.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(BC_T) void k_gp_cut(Ctx C) {
+    __shared__ u32 s_pre[GP_SB + 1];
+    __shared__ u32 s_scan[BC_T / 64];
+    __shared__ u32 s_max[BC_T / 64];
+    __shared__ u32 s_sb;
+    __shared__ u64 s_ibase, s_mbase;
+    if (threadIdx.x == 0) s_sb = atomicAdd(&C.counters[CNT_GP_CUT], 1u);
+    __syncthreads();
+    const i64 sb = (i64)uniform32(s_sb);
+    const int bq = seg_search(C.gp_sb_pre, C.ngp, sb);
+    const int q = C.gp_seg[bq];
+    const DevSeg &s = C.segs[q];
+    const u32 lsb = (u32)(sb - C.gp_sb_pre[bq]);
+    const u32 t = threadIdx.x, lane = t & 63, w = t >> 6;
+    const uint4 hv = *(const uint4 *)(C.gp_hist + s.gp.hist + (i64)lsb * GP_SB + 4 * t);
+    const u32 h[4] = {hv.x, hv.y, hv.z, hv.w};
+    const u32 S = s.gp.S, T = s.gp.T, span = s.gp.span_bins, heavy = s.gp.heavy;
+    u32 tot, mtot;
+    u32 run = block_excl_scan<u32, BC_T>(h[0] + h[1] + h[2] + h[3], s_scan, tot);
+    u32 m[4], ms = 0;
+    for (int k = 0; k < 4; k++) {
+        s_pre[4 * t + k] = run;
+        run += h[k];
+        m[k] = s.gp.K ? 0u : min(h[k], S);
+        ms += m[k];
+    }
+    if (t == BC_T - 1) s_pre[GP_SB] = tot;
+    const u32 mpre = block_excl_scan<u32, BC_T>(ms, s_scan, mtot);
+    if (w == 1) {  // staging offset of the super-bin
+        const u64 pre = lookback_wave(C.gp_look + C.gp_nsb, 0, sb, 203u, mtot, &C.counters[CNT_ERR_SPIN]);
+        if (lane == 0) s_mbase = pre;
+    }
+    // last non-empty bin (plus one) before this thread's
+    u32 mine = 0;
+    for (int k = 0; k < 4; k++)
+        if (h[k]) mine = 4 * t + k + 1;
+    u32 x = mine;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const u32 y = __shfl_up(x, d, 64);
+        if (lane >= (u32)d) x = max(x, y);
+    }
+    if (lane == 63) s_max[w] = x;
+    __syncthreads();
+    u32 pv = __shfl_up(x, 1, 64), all = 0;
+    if (lane == 0) pv = 0;
+    for (u32 i = 0; i < BC_T / 64; i++) {
+        if (i < w) pv = max(pv, s_max[i]);
+        all = max(all, s_max[i]);
+    }
+    const u32 pv0 = pv;
+    u32 st = 0, np[4], nsum = 0;
+    const u32 K = s.gp.K;
+    for (int k = 0; k < 4; k++) {
+        np[k] = 0;
+        const u32 b = 4 * t + k;
+        if (K && (u64)(lsb * GP_SB + b) * K < s.gp.nbins)
+            np[k] = max((u32)(((u64)K * S + GP_CELLS - 1) / GP_CELLS), min(K, h[k] / T + 1));
+        if (K) nsum += np[k];
+        if (K || !h[k]) continue;
+        bool start = pv == 0;
+        if (!start) {
+            const u32 a = pv - 1, ha = s_pre[pv] - s_pre[a];
+            start = s_pre[b] / T != s_pre[a] / T || b / span != a / span || h[k] >= heavy || ha >= heavy;
+        }
+        if (start) st |= 1u << k;
+        pv = b + 1;
+    }
+    u32 ni;
+    u32 it = block_excl_scan<u32, BC_T>((u32)__popc(st) + nsum, s_scan, ni);
+    if (w == 0) {
+        const u64 pre = lookback_wave(C.gp_look, 0, sb, 204u, ni, &C.counters[CNT_ERR_SPIN]);
+        if (lane == 0) s_ibase = pre;
+    }
+    __syncthreads();
+    u64 end = s_ibase + ni;
+    if ((i64)end > C.gp_ibound) {  // never planned: keep every item inside the arrays
+        if (t == 0) atomicOr(&C.counters[CNT_ERR_SPIN], 32u);
+        end = (u64)C.gp_ibound;
+    }
+    if (t == 0) {
+        C.gp_sbit[sb] = (u32)min(s_ibase, (u64)C.gp_ibound);
+        if (sb == C.gp_nsb - 1) C.gp_sbit[C.gp_nsb] = (u32)end;
+    }
+    for (int k = 0; k < 4 && K; k++) {
+        const u32 b0 = (lsb * GP_SB + 4 * t + k) * K;
+        for (u32 e = 0; e < np[k]; e++) {
+            const i64 at = (i64)(s_ibase + it++);
+            if (at >= C.gp_ibound) break;
+            GpItem &I = C.gp_item[at];
+            I.bin_lo = b0 + (u32)((u64)K * e / np[k]);
+            I.bin_hi = b0 + (u32)((u64)K * (e + 1) / np[k]);
+            I.q = q;
+            I.off = 0;
+        }
+    }
+    if (K) return;
+    u64 off = s_mbase + mpre;
+    pv = pv0;
+    for (int k = 0; k < 4; k++) {
+        const u32 b = 4 * t + k;
+        if ((st >> k) & 1u) {
+            const i64 at = (i64)(s_ibase + it);
+            if (it > 0 && at - 1 < C.gp_ibound) C.gp_item[at - 1].bin_hi = lsb * GP_SB + pv;
+            if (at < C.gp_ibound) {
+                GpItem &I = C.gp_item[at];
+                I.bin_lo = lsb * GP_SB + b;
+                I.q = q;
+                I.off = off;
+                if (it + 1 == ni) I.bin_hi = lsb * GP_SB + all;
+            }
+            it++;
+        }
+        if (h[k]) pv = b + 1;
+        off += m[k];
+    }
+}
+
+// ---------------------------------------------------------------------------
+// k_gp_reduce.  Cells: direct (cell = key inside the work item, at most
+// GP_CELLS), else ranked: a presence bitmap over the work item's key span
+// gives every present key its rank, the pairs are formed a second time and
+// accumulate in the cell of their rank, GP_CELLS ranks per round.
+// ---------------------------------------------------------------------------
+constexpr int GR_T = 512;
+constexpr int GR_NW = GR_T / 64;
+constexpr int GR_CPT = GP_CELLS / GR_T;  // cells per thread
+constexpr int GR_WIDE = 448, GR_NARROW = 512;  // pieces listed at a time
+constexpr u32 GP_SPAN = 1u << GP_SPAN_LOG;
+static_assert(GP_SPAN / 64 == GR_T * 4, "each thread scans four bitmap words");
+
+// Cells of the modular rings hold the sum A of the products modulo 2^64 and the
+// sum H of their top 16 bits (GP_HI) apart.  At most 2^16 products meet in a
+// cell (the planner's condition), so the full sum lies in
+// [2^48 H, 2^48 H + 2^64), which tells how often A wrapped: an accumulation
+// needs no look at the old value (no returned atomic, no wrap to repair).
+template <int RING>
+constexpr bool gp_split() {
+    return RING == RING_MODP || RING == RING_MODQ;
+}
+constexpr int GP_HI = 48;
+
+// a * b in a form that is congruent.  Mod p the coefficients come split at bit
+// 31 (k_gp_prep): with T = a0 b1 + a1 b0 < 2^62 the product is
+// a0 b0 + 2^31 T + 2^62 a1 b1, and 2^61 = 1, so it is congruent to
+// a0 b0 + 2 a1 b1 + (T >> 30) + 2^31 (T mod 2^30) < 2^63: four multiply-adds
+// and five more instructions.
+template <int RING>
+__device__ inline u64 gp_mul(u32 a0, u32 a1, u32 b0, u32 b1) {
+    if constexpr (RING == RING_MODP) {
+        const u64 T = (u64)a1 * b0 + (u64)a0 * b1;
+        const u64 r = (u64)a1 * (b1 << 1) + (u64)a0 * b0;
+        const u32 tl = (u32)T;
+        return r + (T >> 30) + (((u64)((tl >> 1) & 0x1FFFFFFFu) << 32) | (tl << 31));
+    } else {
+        return ring_mul<RING>(((u64)a1 << 32) | a0, ((u64)b1 << 32) | b0);
+    }
+}
+
+// The sum of a cell.
+template <int RING>
+__device__ inline u64 gp_join(u64 A, u32 H) {
+    const u32 k = (H + 0xFFFFu - (u32)(A >> GP_HI)) >> (64 - GP_HI);  // A + 2^64 k
+    if constexpr (RING == RING_MODP) {
+        const u64 r = (A & P61) + (A >> 61) + 8 * k;  // 2^64 = 8
+        return r >= P61 ? r - P61 : r;
+    } else {
+        return addmodq(A >= Q64 ? A - Q64 : A, Q64_C * k);  // 2^64 = 59
+    }
+}
+
+// LDS of a work item.  Direct: acc u64[GP_CELLS], then (modular rings)
+// hi u32[GP_CELLS].  Ranked, over the same memory: acc u64[GP_CELLS],
+// rkey u16[GP_CELLS] (key modulo 2^16), bm u64[GP_SPAN / 64] and
+// pre u16[GP_SPAN / 64].  Everything but rkey and pre is zero between uses.
+struct GrLds {
+    static constexpr int HI = GP_CELLS * 8;
+    static constexpr int RKEY = GP_CELLS * 8;
+    static constexpr int BM = RKEY + GP_CELLS * 2;
+    static constexpr int PRE = BM + (int)GP_SPAN / 8;
+    static constexpr int RANKED = PRE + (int)GP_SPAN / 64 * 2;
+};
+static_assert(GP_SPAN_LOG <= 17, "a ranked key is its lower 16 bits and which half of the span it is in");
+
+enum { GP_DIRECT = 0, GP_MARK = 1, GP_RANK = 2 };
+
+// What one pair does: its cell's accumulation, or its key's mark.
+template <int RING, int MODE>
+__device__ inline void gp_pair(unsigned char *mem, const u32x3 a, const u32x3 b, u32 key, u32 wbase, bool ok) {
+    if constexpr (MODE == GP_MARK) {
+        if (ok) atomicOr((u32 *)(mem + GrLds::BM) + (key >> 5), 1u << (key & 31));
+    } else {
+        const u64 v = gp_mul<RING>(a.x, a.y, b.x, b.y);
+        if (ok) {
+            u32 c = key;
+            if constexpr (MODE == GP_RANK) {
+                const u32 w = key >> 6;
+                const u64 bits = ((const u64 *)(mem + GrLds::BM))[w];
+                c = ((const unsigned short *)(mem + GrLds::PRE))[w] +
+                    (u32)__popcll(bits & ((1ull << (key & 63)) - 1)) - wbase;
+                if (c < (u32)GP_CELLS) ring_atomic_acc<RING>((u64 *)mem + c, v);
+            } else {
+                atomicAdd((unsigned long long *)mem + c, (unsigned long long)v);
+                if constexpr (gp_split<RING>()) atomicAdd((u32 *)(mem + GrLds::HI) + c, (u32)(v >> GP_HI));
+            }
+        }
+    }
+}
+
+// A term at a byte offset from a uniform base: coefficient and key.  (Three
+// words: a loaded word that nothing reads would be taken for a free register
+// while the load is still under way, and its next use would wait for it.)
+__device__ inline u32x3 gp_term(const GpTerm *base, u32 off) {
+    return *(const __attribute__((address_space(1))) u32x3 *)((const char *)base + off);
+}
+
+// Pieces of a block, GP_U steps of a wave each.  A wide piece is 33 to 64
+// columns (inner terms, one per lane) by GP_U rows (outer terms, the same for
+// every lane: one scalar load of all of them, so that the vector memory path,
+// which takes 12 cycles for a load whatever its lanes ask for, only carries
+// the columns).  A narrow piece has 2^lg >= columns lanes across and 2^(6-lg)
+// stretches of GP_U rows side by side.
+constexpr u32 GP_U = 4;
+typedef u32 u32x16a __attribute__((ext_vector_type(16), aligned(16)));
+
+struct GpWide {
+    u32x3 b;
+    u32x16a a;
+    u32 cols, rows;
+};
+
+// Loads past the piece's rows and columns stay inside the term array and its
+// padding (GP_PAD terms) and are not used.
+__device__ inline void gp_load_wide(GpWide &p, const uint4 *list, u32 k, const GpTerm *to, const GpTerm *ti) {
+    const uint4 e = list[k];
+    const u32 row = uniform32(e.x), col = uniform32(e.y), rc = uniform32(e.z);
+    p.rows = rc & 0xFFFFu;
+    p.cols = rc >> 16;
+    p.b = gp_term((const GpTerm *)((const char *)ti + col), (threadIdx.x & 63) * (u32)sizeof(GpTerm));
+    p.a = *(const __attribute__((address_space(4))) u32x16a *)((const char *)to + row);
+}
+
+template <int RING, int MODE>
+__device__ inline void gp_run_wide(const GpWide &p, unsigned char *mem, u32 base, u32 wbase) {
+    const bool in = (threadIdx.x & 63) < p.cols;
+    const u32 kb = p.b.z - base;
+#pragma unroll
+    for (u32 u = 0; u < GP_U; u++) {
+        const u32x3 a = {p.a[4 * u], p.a[4 * u + 1], p.a[4 * u + 2]};
+        if (u < p.rows) gp_pair<RING, MODE>(mem, a, p.b, a.z + kb, wbase, in);
+    }
+}
+
+struct GpNarrow {
+    u32x3 b, a[GP_U];
+    u32 r, R;     // this lane's first row; rows (0 for a lane without a column)
+    u32 steps;    // (uniform)
+};
+
+__device__ inline void gp_load_narrow(GpNarrow &p, const uint4 *list, u32 k, const GpTerm *to, const GpTerm *ti) {
+    const uint4 e = list[k];
+    const u32 row = uniform32(e.x), col = uniform32(e.y), rc = uniform32(e.z), lg = uniform32(e.w);
+    const u32 lane = threadIdx.x & 63, c = lane & ((1u << lg) - 1), rows = rc & 0xFFFFu;
+    p.steps = (rows + (64u >> lg) - 1) >> (6 - lg);
+    p.r = (lane >> lg) * p.steps;  // stretches apart: neighbouring rows often have neighbouring keys
+    p.R = c < (rc >> 16) ? rows : 0u;
+    p.b = gp_term((const GpTerm *)((const char *)ti + col), c * (u32)sizeof(GpTerm));
+#pragma unroll
+    for (u32 u = 0; u < GP_U; u++)
+        p.a[u] = gp_term((const GpTerm *)((const char *)to + row), (p.r + u) * (u32)sizeof(GpTerm));
+}
+
+template <int RING, int MODE>
+__device__ inline void gp_run_narrow(const GpNarrow &p, unsigned char *mem, u32 base, u32 wbase) {
+    const u32 kb = p.b.z - base;
+#pragma unroll
+    for (u32 u = 0; u < GP_U; u++)
+        if (u < p.steps) gp_pair<RING, MODE>(mem, p.a[u], p.b, p.a[u].z + kb, wbase, p.r + u < p.R);
+}
+
+// The listed pieces, a wave per piece, each piece's terms loaded while the
+// one before is worked on (the last one's once more instead of a branch).
+template <int RING, int MODE>
+__device__ inline void gp_pieces(unsigned char *mem, const uint4 *wide, u32 nw, const uint4 *narrow, u32 nn,
+                                 const GpTerm *to, const GpTerm *ti, u32 base, u32 wbase) {
+    const u32 w = uniform32(threadIdx.x >> 6);
+    if (w < nw) {
+        u32 k = w;
+        GpWide p, q;
+        gp_load_wide(p, wide, k, to, ti);
+        while (true) {
+            k += GR_NW;
+            gp_load_wide(q, wide, min(k, nw - 1), to, ti);
+            gp_run_wide<RING, MODE>(p, mem, base, wbase);
+            if (k >= nw) break;
+            k += GR_NW;
+            gp_load_wide(p, wide, min(k, nw - 1), to, ti);
+            gp_run_wide<RING, MODE>(q, mem, base, wbase);
+            if (k >= nw) break;
+        }
+    }
+    // (the narrow ones from the other end of the waves)
+    u32 k = GR_NW - 1 - w;
+    if (k < nn) {
+        GpNarrow p, q;
+        gp_load_narrow(p, narrow, k, to, ti);
+        while (true) {
+            k += GR_NW;
+            gp_load_narrow(q, narrow, min(k, nn - 1), to, ti);
+            gp_run_narrow<RING, MODE>(p, mem, base, wbase);
+            if (k >= nn) break;
+            k += GR_NW;
+            gp_load_narrow(p, narrow, min(k, nn - 1), to, ti);
+            gp_run_narrow<RING, MODE>(q, mem, base, wbase);
+            if (k >= nn) break;
+        }
+    }
+}
+
+// What a thread keeps of its first outer group from one work item to the next.
+struct GpOuter {
+    u32 p, i0, rows;  // prefix, first row, rows (0: no such group)
+    u32 j0, nc;       // columns in the work item at hand
+};
+
+__device__ inline void gp_cols(const u32 *lut, u32 p, u32 B0, u32 B1, u32 &j0, u32 &nc) {
+    j0 = nc = 0;
+    if (p < B1) {
+        j0 = gload(lut + (B0 > p ? B0 - p : 0u));
+        nc = gload(lut + (B1 - p)) - j0;
+    }
+}
+
+// Inclusive sum over the wave: shifts by 1, 2, 4 and 8 within each row of 16
+// lanes, then the sums of row 0 (and 2) to row 1 (and 3), of rows 0-1 to 2-3.
+// (A wave's additions to one LDS counter are served lane by lane, about 550
+// cycles for 64 lanes; the scan takes a few dozen and leaves one addition.)
+__device__ inline u32 wave_scan_dpp(u32 x) {
+    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);
+    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);
+    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);
+    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);
+    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);
+    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);
+    return x;
+}
+
+// List counters, by parity of the listing: wide and narrow pieces, and what is
+// left (1: pieces that did not fit, 2: outer groups).
+struct GpCtl {
+    u32 nw[2], nn[2], more[2];
+};
+
+// Forms every pair of output prefixes [B0, B1): lists the blocks' pieces, a
+// thread per outer group, and runs them whenever the list fills up.
+// `before` runs between the first listing and its pieces.
+template <int RING, int MODE, typename Before>
+__device__ inline void gp_sweep(const GpOperand &O, const GpOperand &I, const u32 *lut, u32 B0, u32 B1, u32 base,
+                                unsigned char *mem, uint4 *list, GpCtl *ctl, u32 &par, const GpOuter &F, u32 wbase,
+                                Before &&before) {
+    uint4 *wide = list, *narrow = list + GR_WIDE;
+    u32 og = threadIdx.x;
+    u32 i0 = 0, rows = 0, j0 = 0, nc = 0;
+    u32 nwide = 0, nnarrow = 0;  // pieces still to be listed
+    u32 wc = 0, wr = 0, nr = 0;  // next wide piece: column, row; next narrow piece: row
+    const u32 lane = threadIdx.x & 63;
+    bool first = true;
+    while (true) {
+        u32 flags, nw, nn;
+        while (true) {
+            if (!(nwide | nnarrow) && og < O.groups) {
+                if (og == threadIdx.x) {
+                    i0 = F.i0;
+                    j0 = F.j0;
+                    nc = F.nc;
+                    rows = F.rows;
+                } else {
+                    gp_cols(lut, gload(O.pfx + og), B0, B1, j0, nc);
+                    if (nc) {
+                        i0 = gload(O.start + og);
+                        rows = gload(O.start + og + 1) - i0;
+                    }
+                }
+                og += GR_T;
+                wc = wr = nr = 0;
+                if (nc && rows) {
+                    const u32 rest = nc & 63;
+                    nwide = ((nc + 31) >> 6) * ((rows + GP_U - 1) / GP_U);
+                    if (rest && rest <= 32) {
+                        const u32 lg = rest > 1 ? 32u - (u32)__clz((int)(rest - 1)) : 0u;
+                        nnarrow = (rows + (GP_U << (6 - lg)) - 1) >> (8 - lg);
+                    }
+                }
+            }
+            const u32 iw = wave_scan_dpp(nwide), in = wave_scan_dpp(nnarrow);
+            const u32 tw = (u32)__builtin_amdgcn_readlane((int)iw, 63), tn = (u32)__builtin_amdgcn_readlane((int)in, 63);
+            u32 aw = 0, an = 0;
+            if (lane == 0) {
+                if (tw) aw = atomicAdd(&ctl->nw[par], tw);
+                if (tn) an = atomicAdd(&ctl->nn[par], tn);
+            }
+            aw = uniform32(aw) + iw - nwide;
+            an = uniform32(an) + in - nnarrow;
+            for (u32 e = aw; e < (u32)GR_WIDE && nwide; e++, nwide--) {
+                wide[e] = make_uint4((i0 + wr) * (u32)sizeof(GpTerm), (j0 + wc) * (u32)sizeof(GpTerm),
+                                     min(rows - wr, GP_U) | (min(nc - wc, 64u) << 16), 6u);
+                wr += GP_U;
+                if (wr >= rows) {
+                    wr = 0;
+                    wc += 64;
+                }
+            }
+            for (u32 e = an; e < (u32)GR_NARROW && nnarrow; e++, nnarrow--) {
+                const u32 cols = nc & 63, lg = cols > 1 ? 32u - (u32)__clz((int)(cols - 1)) : 0u;
+                const u32 ch = min(rows - nr, GP_U << (6 - lg));
+                narrow[e] = make_uint4((i0 + nr) * (u32)sizeof(GpTerm), (j0 + nc - cols) * (u32)sizeof(GpTerm),
+                                       ch | (cols << 16), lg);
+                nr += ch;
+            }
+            const u32 mine = (__ballot((nwide | nnarrow) != 0) ? 1u : 0u) | (__ballot(og < O.groups) ? 2u : 0u);
+            if (lane == 0 && mine) atomicOr(&ctl->more[par], mine);
+            __syncthreads();
+            flags = uniform32(ctl->more[par]);
+            nw = uniform32(ctl->nw[par]);
+            nn = uniform32(ctl->nn[par]);
+            if (flags != 2 || nw >= (u32)GR_WIDE / 2 || nn >= (u32)GR_NARROW / 2) break;
+            __syncthreads();  // every thread has read the counters
+            if (threadIdx.x == 0) ctl->more[par] = 0;
+            __syncthreads();
+        }
+        par ^= 1u;
+        if (threadIdx.x == 0) {  // the next listing's counters: read by everyone before the last pieces
+            ctl->nw[par] = 0;
+            ctl->nn[par] = 0;
+            ctl->more[par] = 0;
+        }
+        if (first) before();
+        first = false;
+        gp_pieces<RING, MODE>(mem, wide, min(nw, (u32)GR_WIDE), narrow, min(nn, (u32)GR_NARROW), O.t, I.t, base, wbase);
+        __syncthreads();
+        if (!flags) break;
+    }
+}
+
+// The same with a thread per outer term, each walking its own columns: for
+// operands whose groups hold a term or two.
+template <int RING, int MODE>
+__device__ inline void gp_rows(const GpOperand &O, const GpOperand &I, const u32 *lut, u32 B0, u32 B1, u32 base,
+                               unsigned char *mem, u32 wbase) {
+    for (u32 i = threadIdx.x; i < O.n; i += GR_T) {
+        const u32x3 a = gp_term(O.t, i * (u32)sizeof(GpTerm));
+        u32 j0, nc;
+        gp_cols(lut, gload(&O.t[i].pfx), B0, B1, j0, nc);
+        const u32 ka = a.z - base;
+        for (u32 c = 0; c < nc; c += 4) {
+            u32x3 b[4];
+#pragma unroll
+            for (u32 u = 0; u < 4; u++) b[u] = gp_term(I.t, (j0 + c + u) * (u32)sizeof(GpTerm));
+#pragma unroll
+            for (u32 u = 0; u < 4; u++)
+                if (c + u < nc) gp_pair<RING, MODE>(mem, a, b[u], b[u].z + ka, wbase, true);
+        }
+    }
+    __syncthreads();
+}
+
+// The work items of SEG_GRPD products (BOX: every cell is stored; part k of n
+// of the list) or of SEG_GRP products.  The first work items of a workgroup
+// are its own, the later ones come from a counter (an addition to one address
+// by many workgroups takes about 10 ns each).  The next work item's
+// descriptor and its columns (first outer group of every thread) are loaded
+// while the current one runs.
+template <int RING, bool BOX>
+__global__ __launch_bounds__(GR_T) __attribute__((amdgpu_waves_per_eu(4))) void k_gp_reduce(Ctx C, i64 part, i64 nparts) {
+    constexpr bool SPLIT = gp_split<RING>();
+    constexpr int DIRECT = GP_CELLS * (SPLIT ? 12 : 8);
+    constexpr int MEM = BOX ? DIRECT : (DIRECT > GrLds::RANKED ? DIRECT : GrLds::RANKED);
+    __shared__ __align__(16) unsigned char s_mem[MEM];
+    __shared__ uint4 s_list[GR_WIDE + GR_NARROW];
+    __shared__ GpCtl s_ctl;
+    __shared__ u32 s_w[GR_NW];
+    __shared__ u32 s_tn[2];  // by parity: read after the barrier that ends a work item, while the other is written
+    u64 *acc = (u64 *)s_mem;
+    u32 *counter = &C.counters[BOX ? CNT_GP_BOX : CNT_GP_REDUCE];
+    // every array starts at zero and is left so
+    for (u32 e = threadIdx.x; e < (u32)MEM / 16; e += GR_T) ((uint4 *)s_mem)[e] = make_uint4(0, 0, 0, 0);
+    if (threadIdx.x == 0) s_ctl = GpCtl{{0, 0}, {0, 0}, {0, 0}};
+    __syncthreads();
+    const i64 nall = (i64)uniform32(C.gp_sbit[C.gp_nsb]);
+    const i64 tb = nall * part / nparts, ntk = nall * (part + 1) / nparts, G = gridDim.x;
+    const i64 own = max((i64)2, BOX ? 0 : (ntk - tb) / G * 3 / 8);  // work items of its own per workgroup
+    i64 t = tb + blockIdx.x, t1 = t + G;
+    i64 round = 2;
+    u32 par = 0, lpar = 0;
+    const u32 lane = threadIdx.x & 63, w = uniform32(threadIdx.x >> 6);
+    auto item = [&](i64 t) -> GpItem {
+        GpItem it{};
+        if (t < ntk) it = C.gp_item[t];
+        return it;
+    };
+    GpItem d0 = item(t), d1 = item(t1);
+    int qc = -1;  // product whose fields are held
+    u32 S = 1, rowmode = 0;
+    GpOperand O, I;
+    const u32 *lut = nullptr;
+    u64 *box = nullptr;
+    GpOuter F{};
+    bool have = false;  // F's columns are the coming work item's
+    bool mine = false;  // the product is of this kernel's kind
+    while (t < ntk) {
+        const int q = (int)uniform32((u32)d0.q);
+        const u32 B0 = uniform32(d0.bin_lo), B1 = uniform32(d0.bin_hi);
+        const u64 off = (u64)uniform64((i64)d0.off);
+        if (q != qc) {
+            const DevSeg &s = C.segs[q];
+            const int bq = (int)uniform32(s.gp.bq), so = (int)uniform32(s.gp.swap);
+            S = uniform32(s.gp.S);
+            rowmode = uniform32(s.gp.rows);
+            O = gp_operand(C, s, bq, so);
+            I = gp_operand(C, s, bq, 1 - so);
+            lut = C.gp_lut + uniform64(s.gp.lut);
+            if constexpr (BOX) box = C.box + uniform64(s.stage_base);
+            mine = (uniform32(s.gp.K) != 0) == BOX;
+            qc = q;
+            F.rows = 0;
+            if (threadIdx.x < O.groups) {
+                F.p = gload(O.pfx + threadIdx.x);
+                F.i0 = gload(O.start + threadIdx.x);
+                F.rows = gload(O.start + threadIdx.x + 1) - F.i0;
+            }
+            have = false;
+        }
+        if (!have && F.rows) gp_cols(lut, F.p, B0, B1, F.j0, F.nc);
+        const GpOuter F0 = F;
+        u32 tk = 0;
+        auto ahead = [&]() {  // the next work item's columns, the ticket of the one after it
+            have = t1 < ntk && (int)uniform32((u32)d1.q) == qc && !rowmode;
+            if (have && F.rows) gp_cols(lut, F.p, d1.bin_lo, d1.bin_hi, F.j0, F.nc);
+            if (round >= own && threadIdx.x == 0) tk = atomicAdd(counter, 1u);
+        };
+        if (!mine || rowmode) ahead();
+        const u32 base = B0 * S;  // keys are compared modulo 2^32: a work item spans fewer
+        const u32 span = (B1 - B0) * S;
+        u32 done = 0;  // result terms so far
+        if (!mine) {
+            // another kernel's product
+        } else if (BOX || span <= (u32)GP_CELLS) {
+            if (rowmode) gp_rows<RING, GP_DIRECT>(O, I, lut, B0, B1, base, s_mem, 0u);
+            else gp_sweep<RING, GP_DIRECT>(O, I, lut, B0, B1, base, s_mem, s_list, &s_ctl, lpar, F0, 0u, ahead);
+            // a wave's cells are consecutive, a lane takes two at a time
+            const u32 cw = (span + GR_NW * 128 - 1) / (GR_NW * 128) * 128;
+            const u32 c0 = w * cw + lane * 2;
+            u64 val[GR_CPT];
+            u32 em = 0;
+#pragma unroll
+            for (int k = 0; k < GR_CPT / 2; k++) {
+                const u32 c = c0 + k * 128;
+                val[2 * k] = val[2 * k + 1] = 0;
+                if ((u32)k * 128 < cw) {
+                    ulonglong2 x = *(ulonglong2 *)&acc[c];
+                    *(ulonglong2 *)&acc[c] = make_ulonglong2(0, 0);
+                    if constexpr (SPLIT) {
+                        uint2 *hi = (uint2 *)(s_mem + GrLds::HI + c * 4);
+                        const uint2 y = *hi;
+                        *hi = make_uint2(0, 0);
+                        x.x = gp_join<RING>(x.x, y.x);
+                        x.y = gp_join<RING>(x.y, y.y);
+                    }
+                    val[2 * k] = x.x;
+                    val[2 * k + 1] = x.y;
+                    if constexpr (BOX) {
+                        // (cells beyond the work item are zero: nothing was added)
+                        u64 *o = box + ((i64)B0 * S + c);
+                        if (c < span) o[0] = x.x;
+                        if (c + 1 < span) o[1] = x.y;
+                    }
+                    if (!ring_is_zero<RING>(x.x)) em |= 1u << (2 * k);
+                    if (!ring_is_zero<RING>(x.y)) em |= 2u << (2 * k);
+                }
+            }
+            {
+                u32 rk[GR_CPT / 2], before = 0;
+#pragma unroll
+                for (int k = 0; k < GR_CPT / 2; k++) {
+                    const u64 b0 = __ballot((em >> (2 * k)) & 1u), b1 = __ballot((em >> (2 * k + 1)) & 1u);
+                    rk[k] = before + mbcnt(b0) + mbcnt(b1);
+                    before += (u32)__popcll(b0) + (u32)__popcll(b1);
+                }
+                if (lane == 0) s_w[w] = before;
+                __syncthreads();
+                u32 wpre = 0;
+#pragma unroll
+                for (u32 i = 0; i < (u32)GR_NW; i++) {
+                    const u32 v = s_w[i];
+                    if (i < w) wpre += v;
+                    done += v;
+                }
+                // the next work item's columns and the ticket are taken here:
+                // later their wait would be one for the stores, too
+                asm volatile("" : "+v"(F.j0), "+v"(F.nc), "+v"(tk));
+#pragma unroll
+                for (int k = 0; k < GR_CPT / 2 && !BOX; k++) {
+                    u64 at = off + wpre + rk[k];
+                    if ((em >> (2 * k)) & 1u) {
+                        C.gp_rkey[at] = c0 + k * 128;
+                        C.gp_rcoef[at] = val[2 * k];
+                        at++;
+                    }
+                    if ((em >> (2 * k + 1)) & 1u) {
+                        C.gp_rkey[at] = c0 + k * 128 + 1;
+                        C.gp_rcoef[at] = val[2 * k + 1];
+                    }
+                }
+            }
+        } else if constexpr (!BOX) {
+            unsigned short *rkey = (unsigned short *)(s_mem + GrLds::RKEY);
+            u64 *bm = (u64 *)(s_mem + GrLds::BM);
+            unsigned short *pre = (unsigned short *)(s_mem + GrLds::PRE);
+            auto none = [] {};
+            if (rowmode) gp_rows<RING, GP_MARK>(O, I, lut, B0, B1, base, s_mem, 0u);
+            else gp_sweep<RING, GP_MARK>(O, I, lut, B0, B1, base, s_mem, s_list, &s_ctl, lpar, F0, 0u, ahead);
+            // rank of a word's first key (thread t: words 4t .. 4t + 3)
+            u64 wd[4];
+            u32 sum = 0, distinct;
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                wd[e] = bm[threadIdx.x * 4 + e];
+                sum += (u32)__popcll(wd[e]);
+            }
+            const u32 ex = block_excl_scan<u32, GR_T>(sum, s_w, distinct);
+            {
+                u32 r = ex;
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    pre[threadIdx.x * 4 + e] = (unsigned short)r;
+                    r += (u32)__popcll(wd[e]);
+                }
+            }
+            __syncthreads();
+            const u32 lower = pre[GP_SPAN / 128];  // ranks in the lower half of the span
+            const u32 half = (u32)GP_SPAN > 65536u ? 65536u : 0u;
+            for (u32 wb = 0; wb < distinct; wb += GP_CELLS) {
+                // keys of the round's ranks
+                u32 r = ex - wb;
+#pragma unroll
+                for (int e = 0; e < 4; e++) {
+                    u64 x = wd[e];
+                    while (x) {
+                        if (r < (u32)GP_CELLS)
+                            rkey[r] = (unsigned short)((threadIdx.x * 4 + e) * 64 + (u32)__ffsll((unsigned long long)x) - 1);
+                        r++;
+                        x &= x - 1;
+                    }
+                }
+                __syncthreads();
+                if (rowmode) gp_rows<RING, GP_RANK>(O, I, lut, B0, B1, base, s_mem, wb);
+                else gp_sweep<RING, GP_RANK>(O, I, lut, B0, B1, base, s_mem, s_list, &s_ctl, lpar, F0, wb, none);
+                const u32 ncell = min(distinct - wb, (u32)GP_CELLS);
+                const u32 cw = (ncell + GR_T - 1) / GR_T * 64;  // cells of a wave
+                constexpr int CPT = GP_CELLS / GR_T;
+                u64 val[CPT];
+                u32 kk[CPT], rk[CPT], em = 0, before = 0;
+#pragma unroll
+                for (int k = 0; k < CPT; k++) {
+                    const u32 c = w * cw + k * 64 + lane;
+                    val[k] = 0;
+                    kk[k] = 0;
+                    if ((u32)k * 64 < cw && c < ncell) {
+                        kk[k] = rkey[c] + (wb + c >= lower ? half : 0u);
+                        val[k] = ring_cell_final<RING>(acc[c]);
+                        acc[c] = 0;
+                        if (!ring_is_zero<RING>(val[k])) em |= 1u << k;
+                    }
+                    const u64 bal = __ballot((em >> k) & 1u);
+                    rk[k] = before + mbcnt(bal);
+                    before += (u32)__popcll(bal);
+                }
+                if (lane == 0) s_w[w] = before;
+                __syncthreads();
+                u32 wpre = 0, tot = 0;
+#pragma unroll
+                for (u32 i = 0; i < (u32)GR_NW; i++) {
+                    const u32 v = s_w[i];
+                    if (i < w) wpre += v;
+                    tot += v;
+                }
+#pragma unroll
+                for (int k = 0; k < CPT; k++) {
+                    if ((em >> k) & 1u) {
+                        const u64 at = off + done + wpre + rk[k];
+                        C.gp_rkey[at] = kk[k];
+                        C.gp_rcoef[at] = val[k];
+                    }
+                }
+                done += tot;
+                __syncthreads();
+            }
+            // the direct cells overlay the keys, the bitmap and its prefix
+            for (u32 e = threadIdx.x; e < (u32)(GrLds::RANKED - GrLds::RKEY) / 16; e += GR_T)
+                ((uint4 *)(s_mem + GrLds::RKEY))[e] = make_uint4(0, 0, 0, 0);
+        }
+        if (mine && threadIdx.x == 0) {
+            C.gp_u[t] = done;
+            atomicAdd(&C.gp_usum[t >> GP_USUM_LOG], done);
+        }
+        if (round >= own && threadIdx.x == 0) s_tn[par] = tk;
+        __syncthreads();
+        d0 = d1;
+        t = t1;
+        t1 = round < own ? tb + blockIdx.x + round * G : tb + own * G + (i64)uniform32(s_tn[par]);
+        d1 = item(t1);
+        round++;
+        par ^= 1u;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// k_gp_copy: a workgroup takes a run of consecutive work items; the result
+// offset of its first one is the sum of the term counts of the product's
+// earlier ones (gp_usum holds them per 2^GP_USUM_LOG items).
+// ---------------------------------------------------------------------------
+constexpr int GC_T = 256;
+constexpr int GC_B = 4;  // terms per thread per batch
+
+__device__ inline u64 gp_range_sum(const u32 *v, i64 a, i64 b) {
+    u64 x = 0;
+    for (i64 i = a + threadIdx.x; i < b; i += GC_T) x += v[i];
+    return x;
+}
+
+__global__ __launch_bounds__(GC_T) void k_gp_copy(Ctx C) {
+    __shared__ u32 s_vl[5 * MAX_VARS];
+    __shared__ u64 s_sum[GC_T / 64];
+    const i64 nt = (i64)C.gp_sbit[C.gp_nsb];
+    const i64 t0 = nt * blockIdx.x / gridDim.x, t1 = nt * (blockIdx.x + 1) / gridDim.x;
+    if (t0 >= t1) return;
+    const int nvars = C.nvars;
+    const u32 lane = threadIdx.x & 63, w = uniform32(threadIdx.x >> 6);
+    int q = C.gp_item[t0].q;
+    u64 at0;
+    {
+        const i64 f = (i64)C.gp_sbit[C.segs[q].gp.sb_first];
+        const i64 m = (i64)1 << GP_USUM_LOG;
+        const i64 f1 = min((f + m - 1) & ~(m - 1), t0), g1 = max(t0 & ~(m - 1), f1);
+        u64 x = gp_range_sum(C.gp_u, f, f1) + gp_range_sum(C.gp_u, g1, t0);
+        if (g1 > f1) x += gp_range_sum(C.gp_usum, f1 >> GP_USUM_LOG, g1 >> GP_USUM_LOG);
+        x = wave_sum_u64(x);
+        if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = x;
+        __syncthreads();
+        at0 = 0;
+        for (int i = 0; i < GC_T / 64; i++) at0 += s_sum[i];
+    }
+    int qc = -1;
+    u64 *hk = nullptr, *hc = nullptr;
+    const u64 *box = nullptr;
+    i64 cap = 0, last = 0;
+    u64 lo_key = 0;
+    Div32 sd{0, 0, 0, 1};
+    int d = 1;
+    // term at of h: cell x of the work item that starts at bin b
+    auto put = [&](i64 at, u32 b, u32 x, u64 coef) {
+        if (at >= cap) return;
+        u32 hi = div32(x, sd);
+        u32 low = x - hi * sd.d;
+        hi += b;
+        u64 key = lo_key;
+        for (int v = nvars - 1; v >= 0; v--) {
+            const Div32 dv{s_vl[5 * v + 1], s_vl[5 * v + 2], s_vl[5 * v + 3], s_vl[5 * v + 4]};
+            const u32 y = v >= d ? low : hi;
+            const u32 z = div32(y, dv);
+            key += (u64)(y - z * dv.d) << s_vl[5 * v];
+            if (v >= d) low = z;
+            else hi = z;
+        }
+        hk[at] = key;
+        hc[at] = coef;
+    };
+    for (i64 t = t0; t < t1; t++) {
+        const GpItem it = C.gp_item[t];
+        q = it.q;
+        const u32 u = C.gp_u[t];
+        if (q != qc) {
+            const DevSeg &s = C.segs[q];
+            if (qc >= 0) at0 = 0;
+            __syncthreads();
+            const VarParam *vp = C.vars + s.var_off;
+            for (int v = threadIdx.x; v < nvars; v += GC_T) {
+                s_vl[5 * v] = vp[v].shift;
+                s_vl[5 * v + 1] = vp[v].rdiv.m;
+                s_vl[5 * v + 2] = vp[v].rdiv.s1;
+                s_vl[5 * v + 3] = vp[v].rdiv.s2;
+                s_vl[5 * v + 4] = vp[v].rdiv.d;
+            }
+            hk = s.hk;
+            hc = s.hc;
+            cap = s.cap;
+            lo_key = s.lo_key;
+            sd = s.nb_div;
+            d = (int)s.gp.d;
+            box = s.gp.K ? C.box + s.stage_base : nullptr;
+            last = (i64)C.gp_sbit[s.gp.sb_first + s.gp.nsb] - 1;
+            __syncthreads();
+            qc = q;
+        }
+        if (box) {
+            // the non-zero cells of the degree box
+            const u64 *cell = box + (i64)it.bin_lo * sd.d;
+            const u32 n = (it.bin_hi - it.bin_lo) * sd.d;
+            u64 at = at0;
+            for (u32 c0 = 0; c0 < n && u; c0 += GC_T * GC_B) {
+                u64 v[GC_B];
+                u32 rk[GC_B], before = 0;
+#pragma unroll
+                for (int e = 0; e < GC_B; e++) v[e] = cell[min(c0 + w * (64 * GC_B) + e * 64 + lane, n - 1)];
+#pragma unroll
+                for (int e = 0; e < GC_B; e++) {
+                    if (c0 + w * (64 * GC_B) + e * 64 + lane >= n) v[e] = 0;
+                    const u64 bal = __ballot(v[e] != 0);
+                    rk[e] = before + mbcnt(bal);
+                    before += (u32)__popcll(bal);
+                }
+                __syncthreads();
+                if (lane == 0) s_sum[w] = before;
+                __syncthreads();
+                u64 tot = 0;
+                for (u32 i = 0; i < GC_T / 64; i++) {
+                    if (i == w) before = (u32)tot;
+                    tot += s_sum[i];
+                }
+#pragma unroll
+                for (int e = 0; e < GC_B; e++)
+                    if (v[e]) put((i64)(at + before + rk[e]), it.bin_lo, c0 + w * (64 * GC_B) + e * 64 + lane, v[e]);
+                at += tot;
+            }
+        } else {
+            const u32 *rk = C.gp_rkey + it.off;
+            const u64 *rc = C.gp_rcoef + it.off;
+            for (u32 r0 = 0; r0 < u; r0 += GC_T * GC_B) {
+                u32 ck[GC_B];
+                u64 cv[GC_B];
+#pragma unroll
+                for (int e = 0; e < GC_B; e++) {
+                    const u32 r = min(r0 + e * GC_T + threadIdx.x, u - 1);
+                    ck[e] = rk[r];
+                    cv[e] = rc[r];
+                }
+#pragma unroll
+                for (int e = 0; e < GC_B; e++) {
+                    const u32 r = r0 + e * GC_T + threadIdx.x;
+                    if (r < u) put((i64)(at0 + r), it.bin_lo, ck[e], cv[e]);
+                }
+            }
+        }
+        at0 += u;
+        if (t == last && threadIdx.x == 0) *C.segs[q].n_out = (i64)at0;
+    }
+}
+
+}  // namespace pm

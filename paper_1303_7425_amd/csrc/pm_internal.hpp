@@ -24,6 +24,51 @@ enum SegMode : int {
     SEG_DENSE = 3,    // accumulated directly into the degree box, then compaction
     SEG_IVAL = 4,     // output-key intervals owned by workgroups, merged in LDS (no global sort)
     SEG_BKT = 5,      // pairs scattered once into output-key work items, each sorted and summed in LDS
+    SEG_GRP = 6,      // pairs formed from prefix groups inside their output-key work items
+    SEG_GRPD = 7,     // the same, every degree-box cell stored, then compaction
+};
+
+// Prefix groups (SEG_GRP, SEG_GRPD).  One output prefix (the value of the
+// leading variables of a compressed key) is a bin.
+constexpr int GP_SB_LOG = 12;
+constexpr int GP_SB = 1 << GP_SB_LOG;  // bins per super-bin (one workgroup of the cut)
+constexpr int GP_CELLS = 4096;         // LDS cells of a work item
+constexpr int GP_SPAN_LOG = 17;        // key span (log2) of the presence bitmap
+constexpr int GP_MAX_S = 61440;        // cells of a bin, at most: a work item then has at most 2^16 keys (gp.T <= 4096 pairs before its last bin)
+constexpr int GP_PAD = 1024;           // term slots after the last operand (loads past a block's rows)
+constexpr int GP_USUM_LOG = 7;         // work items per partial sum of result counts
+
+// An operand term: coefficient, compressed key modulo 2^32, prefix.
+struct GpTerm {
+    u32 c0, c1, ck, pfx;
+};
+
+// Work item: bins [bin_lo, bin_hi) of product q, results staged from off.
+struct GpItem {
+    u32 bin_lo, bin_hi;
+    i32 q;
+    u32 pad;
+    u64 off;
+};
+
+// Plan of one such product.
+struct GrpSeg {
+    u32 S;          // cells of a bin (product of the ranges of variables d and up)
+    u32 d;          // variables of the prefix
+    u32 nbins;
+    u32 T;          // pairs per work item, about (SEG_GRPD: in units of 2^csh)
+    u32 span_bins;  // SEG_GRP: bins of one bitmap span
+    u32 heavy;      // SEG_GRP: a bin of this many pairs or more is a work item of its own
+    u32 swap;       // 1: g's groups are the outer ones (rows)
+    u32 K;          // SEG_GRPD: bins of a run (one value of the variables before the last prefix variable)
+    u32 csh;        // SEG_GRPD: a run's pairs are counted in units of 2^csh
+    u32 bq;         // index among the launch's group products
+    u32 rows;       // 1: a thread per outer term instead of a wave per block
+    u32 pad;
+    i64 tf, tg;     // offsets of the operands' terms
+    i64 lut;        // offset of the prefix table (nbins + 1 entries)
+    i64 hist;       // SEG_GRP: offset of the bin counts (multiple of GP_SB)
+    i64 sb_first, nsb;
 };
 
 // Output-key work items (SEG_BKT).  The compressed key range of a product is
@@ -114,19 +159,24 @@ struct DevSeg {
     i64 ck_f, ck_g;                // offsets of the compressed operand keys
     i64 stage_base;                // first staging slot (sparse) or first box cell (dense)
     i64 stage_bound;               // staging slots (sparse) or box cells (dense)
-    i64 tile_first;                // first tile of this product in the tile queue
-    i64 tiles_n;                   // tiles along g
-    Div32 nb_div;                  // division by nb: pair index -> (row, column) (SEG_RAW)
-    i64 dpart_first;               // first compaction partition (SEG_DENSE)
+    Div32 nb_div;                  // division by nb: pair index -> (row, column) (SEG_RAW, SEG_IVAL, SEG_BKT); by gp.S (SEG_GRP)
+    i64 dpart_first;               // first compaction partition (SEG_DENSE, SEG_GRPD)
     i64 var_off;                   // offset of this product's VarParam entries
-    i64 iv_l;                      // grid parameter l (SEG_IVAL): (l+1)^2 samples
-    i64 iv_samp_off, iv_spl_off;   // offsets of its samples and splitters
-    i64 bk_bin_off;                // SEG_BKT: first fine bin in the launch's bin arrays (multiple of BK_SB)
-    i64 bk_sb_first, bk_nsb;       // first super-bin (launch-wide index) and super-bins
-    i64 bk_tile_first;             // first generation tile
-    i64 bk_tiles_n;                // generation tiles along g
-    i32 bk_fs;                     // fine shift: bin = compressed key >> bk_fs
-    i32 bk_tnl;                    // log2 of the generation tile's columns (rows: BK_TILE >> bk_tnl)
+    union {
+        struct {
+            i64 tile_first;                // first tile of this product in the tile queue
+            i64 tiles_n;                   // tiles along g
+            i64 iv_l;                      // grid parameter l (SEG_IVAL): (l+1)^2 samples
+            i64 iv_samp_off, iv_spl_off;   // offsets of its samples and splitters
+            i64 bk_bin_off;                // SEG_BKT: first fine bin in the launch's bin arrays (multiple of BK_SB)
+            i64 bk_sb_first, bk_nsb;       // first super-bin (launch-wide index) and super-bins
+            i64 bk_tile_first;             // first generation tile
+            i64 bk_tiles_n;                // generation tiles along g
+            i32 bk_fs;                     // fine shift: bin = compressed key >> bk_fs
+            i32 bk_tnl;                    // log2 of the generation tile's columns (rows: BK_TILE >> bk_tnl)
+        };
+        GrpSeg gp;                         // SEG_GRP, SEG_GRPD
+    };
     u64 lo_key;                    // packed key of the smallest output exponent vector
     u64 *hk, *hc;                  // result arrays
     i64 *n_out;
@@ -226,6 +276,21 @@ struct Ctx {
     i64 bk_ntiles, bk_nsb;
     i64 bk_wi_bound;            // work-item slots (tickets beyond are an internal error)
     i64 bk_nstage;              // staging slots
+    // SEG_GRP, SEG_GRPD (prefix groups)
+    const i32 *gp_seg;          // [ngp] their segment indices
+    const i64 *gp_sb_pre;       // [ngp+1] super-bin prefix
+    i32 ngp;
+    i64 gp_nsb, gp_ibound;      // super-bins; work-item slots of SEG_GRP
+    GpTerm *gp_term;            // operand terms
+    u32 *gp_pfx, *gp_start;     // groups of every operand: prefix, first term (closed by the term count)
+    u32 *gp_ng;                 // [2 ngp] groups of f and g
+    u32 *gp_lut, *gp_hist;      // first inner term per prefix; pairs per bin (zeroed per call)
+    u64 *gp_look;               // [2][nsb] look-back words (zeroed per call)
+    u32 *gp_sbit;               // [nsb+1] first work item of every super-bin
+    GpItem *gp_item;            // [ibound]
+    u32 *gp_u, *gp_usum;        // result terms per work item and per 2^GP_USUM_LOG of them (zeroed per call)
+    u32 *gp_rkey;               // staged result terms: key inside the work item,
+    u64 *gp_rcoef;              // coefficient
     i32 tb_tile, tb_sort, tb_cmp;  // consecutive work items handed out per work-queue ticket
 };
 
@@ -241,6 +306,9 @@ enum Counter : int {
     CNT_ZEROS,                      // some product of the launch has cancelled terms
     CNT_ZCOMPACT,
     CNT_BK_REDUCE,                  // work items of the in-LDS sort and sum
+    CNT_GP_CUT,
+    CNT_GP_REDUCE,
+    CNT_GP_BOX,
     CNT_COUNT
 };
 

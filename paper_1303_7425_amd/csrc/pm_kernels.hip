@@ -31,7 +31,9 @@ namespace pm {
 // ---------------------------------------------------------------------------
 // k_stats: one workgroup per (segment, operand side).  Per-variable min/max of
 // the exponents, strict ascending order, key bits outside the fields, and
-// coefficient range.  out[(q*2+side)*2*nvars + v] = min, [... + nvars + v] = max.
+// coefficient range.  out[(q*2+side)*2*nvars + v] = min, [... + nvars + v] = max;
+// with fields of at most 32 bits the upper half of the minimum holds the
+// number of distinct prefixes of variables 0..v (the planner's group counts).
 // One sweep over the terms per group of eight variables, four independent
 // loads in flight per thread (1024 threads: an operand of a few thousand
 // terms takes one or two steps); the checks ride along with the first group.
@@ -72,6 +74,7 @@ __global__ __launch_bounds__(ST_T) void k_stats(const DevSeg *segs, int nvars, i
     const u64 mask = bits == 64 ? ~0ull : ((1ull << bits) - 1);
     const int used = nvars * bits;
     __shared__ u64 s_mn[G][NW], s_mx[G][NW];
+    __shared__ u32 s_hd[G][NW];
     __shared__ u32 s_flag;
     if (threadIdx.x == 0) s_flag = 0;
     __syncthreads();
@@ -79,9 +82,10 @@ __global__ __launch_bounds__(ST_T) void k_stats(const DevSeg *segs, int nvars, i
     u64 *o = out + (i64)(q * 2 + side) * 2 * nvars;
     for (int v0 = 0; v0 < nvars; v0 += G) {
         u64 mn[G], mx[G];
-        u32 sh[G];
+        u32 sh[G], hd[G];
 #pragma unroll
         for (int u = 0; u < G; u++) {
+            hd[u] = 0;
             mn[u] = ~0ull;
             mx[u] = 0;
             sh[u] = v0 + u < nvars ? (u32)((nvars - 1 - (v0 + u)) * bits) : 0u;
@@ -92,7 +96,7 @@ __global__ __launch_bounds__(ST_T) void k_stats(const DevSeg *segs, int nvars, i
             for (int r = 0; r < U; r++) {
                 const i64 i = i0 + (i64)r * ST_T;
                 kk[r] = i < n ? k[i] : 0;
-                kp[r] = (v0 == 0 && i > 0 && i < n) ? k[i - 1] : 0;
+                kp[r] = (i > 0 && i < n) ? k[i - 1] : 0;
                 cc[r] = (v0 == 0 && i < n) ? c[i] : 0;
             }
 #pragma unroll
@@ -111,6 +115,7 @@ __global__ __launch_bounds__(ST_T) void k_stats(const DevSeg *segs, int nvars, i
                     const u64 e = (kk[r] >> sh[u]) & mask;
                     mn[u] = e < mn[u] ? e : mn[u];
                     mx[u] = e > mx[u] ? e : mx[u];
+                    hd[u] += i == 0 || ((kk[r] ^ kp[r]) >> sh[u]) != 0 ? 1u : 0u;
                 }
             }
         }
@@ -118,6 +123,10 @@ __global__ __launch_bounds__(ST_T) void k_stats(const DevSeg *segs, int nvars, i
         for (int u = 0; u < G; u++) {
             mn[u] = wave_minmax_u64<false>(mn[u]);
             mx[u] = wave_minmax_u64<true>(mx[u]);
+            if (bits <= 32) {
+                for (int d = 32; d >= 1; d >>= 1) hd[u] += (u32)__shfl_xor((int)hd[u], d, 64);
+                if (lane_id() == 0) s_hd[u][threadIdx.x >> 6] = hd[u];
+            }
             if (lane_id() == 63) {
                 s_mn[u][threadIdx.x >> 6] = mn[u];
                 s_mx[u][threadIdx.x >> 6] = mx[u];
@@ -130,6 +139,11 @@ __global__ __launch_bounds__(ST_T) void k_stats(const DevSeg *segs, int nvars, i
             for (int w = 1; w < NW; w++) {
                 a = s_mn[u][w] < a ? s_mn[u][w] : a;
                 b = s_mx[u][w] > b ? s_mx[u][w] : b;
+            }
+            if (bits <= 32) {
+                u64 h = 0;
+                for (int w = 0; w < NW; w++) h += s_hd[u][w];
+                a = (a & 0xFFFFFFFFull) | (min(h, (u64)0xFFFFFFFFull) << 32);
             }
             o[v0 + u] = a;
             o[nvars + v0 + u] = b;
@@ -1550,6 +1564,7 @@ __global__ __launch_bounds__(NTHREADS) void k_compact(Ctx C) {
 
 #include "pm_ival.hpp"
 #include "pm_bkt.hpp"
+#include "pm_grp.hpp"
 static_assert(pm::BK_TL == 512, "workspace layout sizes the tile lists for 512 bins");
 
 // ===========================================================================
@@ -1763,12 +1778,15 @@ static void launch_tile(const Plan &P, const Ctx &C, hipStream_t st, int grid, i
     }
 }
 
-int64_t tile_launches(const Plan &P) {
+static int64_t tile_combine_launches(const Plan &P) {
     if (P.ntiles <= 0) return 0;
     const i64 tile_pairs = (i64)TILE_CFGS[P.tile_cfg].tm * TILE_CFGS[P.tile_cfg].tn;
     const i64 per = std::max<i64>(1, TILE_LAUNCH_PAIRS / tile_pairs);
     return (P.ntiles + per - 1) / per;
 }
+
+static i64 gp_chunks(const Plan &P);
+int64_t tile_launches(const Plan &P) { return tile_combine_launches(P) + gp_chunks(P); }
 
 template <typename K, typename V, int RING>
 static void launch_sort_reduce(const Plan &P, const Ctx &C, hipStream_t st, int cus) {
@@ -1869,10 +1887,58 @@ static void launch_bkt(const Plan &P, const Ctx &C, hipStream_t st, int cus) {
     hipLaunchKernelGGL(k_bk_copy, dim3(grid_for(P.bk_wi_bound, cus * 8)), dim3(BK_T), 0, st, C);
 }
 
+// Tile launches of the degree-box work items: about GP_LAUNCH_PAIRS pairs each
+// (about a millisecond), as launch_tile's.
+constexpr double GP_LAUNCH_PAIRS = 1 << 29;
+static i64 gp_chunks(const Plan &P) {
+    return P.ngp_box ? std::max<i64>(1, (i64)(P.gp_dpairs / GP_LAUNCH_PAIRS)) : 0;
+}
+
+// Work items [chunk] of the degree-box products by prefix groups (-1: all).
+template <int RING>
+static void launch_gp_box(const Plan &P, const Ctx &C, hipStream_t st, int cus, i64 chunk) {
+    ProfScope ps("gp_box", st);
+    const i64 n = chunk >= 0 ? gp_chunks(P) : 1;
+    for (i64 k = chunk >= 0 ? chunk : 0; k < n; k++) {
+        if (k > 0) hipLaunchKernelGGL(k_set32, dim3(1), dim3(1), 0, st, C.counters + CNT_GP_BOX, 0u);
+        hipLaunchKernelGGL((k_gp_reduce<RING, true>), dim3(grid_for(P.gp_ibound, cus * 2)), dim3(GR_T), 0, st, C, k, n);
+        if (chunk >= 0) break;
+    }
+}
+
+static void launch_gp_head(const Plan &P, const Ctx &C, hipStream_t st, int cus, u64 *zp, i64 zn) {
+    {
+        ProfScope ps("gp_prep", st);
+        const int nz = grid_for((zn + GPP_T - 1) / GPP_T, cus * 2);
+        hipLaunchKernelGGL(k_gp_prep, dim3(2 * P.ngp + nz), dim3(GPP_T), 0, st, C, 2 * P.ngp, zp, zn);
+    }
+    ProfScope ps("gp_lut", st);
+    const int gy = std::min(P.ngp, 1024);
+    const int gx = std::max(1, std::min((int)std::max<i64>((P.gp_maxbins + 255) / 256, (P.gp_maxgrp + 3) / 4), cus * 8 / gy));
+    hipLaunchKernelGGL(k_gp_lut, dim3(gx, gy), dim3(256), 0, st, C);
+    if (P.ngp_box)
+        hipLaunchKernelGGL(k_gp_coarse, dim3(std::max(1, cus * 8 / gy), gy),
+                           dim3(256), 0, st, C);
+    hipLaunchKernelGGL(k_gp_cut, dim3((unsigned)P.gp_nsb), dim3(BC_T), 0, st, C);
+}
+
+template <int RING>
+static void launch_gp_sparse(const Plan &P, const Ctx &C, hipStream_t st, int cus) {
+    {
+        ProfScope ps("gp_reduce", st);
+        hipLaunchKernelGGL((k_gp_reduce<RING, false>), dim3(grid_for(P.gp_ibound, cus * 2)), dim3(GR_T), 0, st, C, (i64)0,
+                           (i64)1);
+    }
+}
+
 template <typename K, int RING>
 static void launch_typed(const Plan &P, const Ctx &C, hipStream_t st, int cus, int part, i64 chunk) {
     if (part == PART_CHUNK) {
-        if constexpr (RING != RING_F64) launch_tile<K, RING>(P, C, st, grid_for(P.ntiles, cus * 8), chunk);
+        if constexpr (RING != RING_F64) {
+            const i64 nt = tile_combine_launches(P);
+            if (chunk < nt) launch_tile<K, RING>(P, C, st, grid_for(P.ntiles, cus * 8), chunk);
+            else launch_gp_box<RING>(P, C, st, cus, chunk - nt);
+        }
         return;
     }
     if (part != PART_TAIL && P.nck > 0) {
@@ -1884,7 +1950,18 @@ static void launch_typed(const Plan &P, const Ctx &C, hipStream_t st, int cus, i
         if constexpr (RING != RING_F64)
             launch_tile<K, RING>(P, C, st, grid_for(P.ntiles, cus * 8), part == PART_HEAD ? 0 : -1);
     }
+    if constexpr (RING != RING_F64) {
+        if (P.ngp_box > 0 && part != PART_TAIL && (part != PART_HEAD || P.ntiles == 0))
+            launch_gp_box<RING>(P, C, st, cus, part == PART_HEAD ? 0 : -1);
+    }
     if (part == PART_HEAD) return;
+    if constexpr (RING != RING_F64) {
+        if (P.ngp_sparse > 0) launch_gp_sparse<RING>(P, C, st, cus);
+    }
+    if (P.ngp > 0) {
+        ProfScope ps("gp_copy", st);
+        hipLaunchKernelGGL(k_gp_copy, dim3(grid_for(P.gp_ibound, cus * 8)), dim3(GC_T), 0, st, C);
+    }
     if (P.nival > 0) {
         if constexpr (sizeof(K) == 4) {
             {
@@ -1910,7 +1987,7 @@ static void launch_typed(const Plan &P, const Ctx &C, hipStream_t st, int cus, i
         } else {
             if constexpr (RING != RING_F64) launch_sort_reduce<K, u64, RING>(P, C, st, cus);
         }
-    } else if (P.nseg > 0) {
+    } else if (P.nempty > 0) {
         // products without a sort still need n_out = 0 when an operand is empty
         hipLaunchKernelGGL(k_seg_prepare, dim3(1), dim3(NTHREADS), 0, st, C);
     }
@@ -1925,7 +2002,9 @@ hipError_t launch_pipeline(const Plan &P, const Ctx &C, hipStream_t st, int cus,
     // per-call zeroed state
     const size_t zbytes = P.r_zero.bytes;
     u64 *zp = (u64 *)((char *)C.segs - P.o_segs + P.r_zero.off);
-    if (part == PART_ALL || part == PART_HEAD) {
+    if (P.ngp > 0 && (part == PART_ALL || part == PART_HEAD)) {
+        launch_gp_head(P, C, st, cus, zp, (i64)(zbytes / 8));
+    } else if (part == PART_ALL || part == PART_HEAD) {
         ProfScope ps("fill", st);
         hipLaunchKernelGGL(k_fill, dim3(grid_for((int64_t)(zbytes / 8 + 255) / 256, cus * 8)), dim3(256), 0, st, zp,
                            (i64)(zbytes / 8), 0ull);
@@ -2032,6 +2111,24 @@ Ctx make_ctx(const Plan &P, void *ws) {
     C.bk_seg = (const i32 *)(b + P.o_bk_seg);
     C.bk_sb_pre = (const i64 *)(b + P.o_bk_sb_pre);
     C.nbk = P.nbk;
+    C.ngp = P.ngp;
+    C.gp_nsb = P.gp_nsb;
+    C.gp_ibound = P.gp_ibound;
+    C.gp_seg = (const i32 *)(b + P.o_gp_seg);
+    C.gp_sb_pre = (const i64 *)(b + P.o_gp_sb_pre);
+    C.gp_term = (GpTerm *)(b + P.o_gp_term);
+    C.gp_pfx = (u32 *)(b + P.o_gp_pfx);
+    C.gp_start = (u32 *)(b + P.o_gp_start);
+    C.gp_ng = (u32 *)(b + P.o_gp_ng);
+    C.gp_lut = (u32 *)(b + P.o_gp_lut);
+    C.gp_hist = (u32 *)(b + P.o_gp_hist);
+    C.gp_look = (u64 *)(b + P.o_gp_look);
+    C.gp_sbit = (u32 *)(b + P.o_gp_sbit);
+    C.gp_item = (GpItem *)(b + P.o_gp_item);
+    C.gp_u = (u32 *)(b + P.o_gp_u);
+    C.gp_usum = (u32 *)(b + P.o_gp_usum);
+    C.gp_rkey = (u32 *)(b + P.o_gp_rkey);
+    C.gp_rcoef = (u64 *)(b + P.o_gp_rcoef);
     C.bk_ntiles = P.bk_ntiles;
     C.bk_nsb = P.bk_nsb;
     C.bk_wi_bound = P.bk_wi_bound;

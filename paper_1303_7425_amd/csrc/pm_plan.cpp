@@ -119,8 +119,110 @@ static int bitlen128(unsigned __int128 x) {
     return b;
 }
 
-int plan_build(int nvars, int bits, int ring, const std::vector<SegInput> &in, const uint64_t *stats,
-               const uint32_t *flags, const Tuning &tune_in, Plan &P, int cus) {
+// One way to run a product by prefix groups (SEG_GRP, SEG_GRPD).
+struct GpTry {
+    bool ok = false;
+    GrpSeg g{};
+    int64_t ibound = 0, items = 0, nres = 0;
+    int64_t bytes = 0;  // of workspace
+};
+
+// Groups of both operands at every depth (prefixes of 1, 2, ... variables).
+struct GpCounts {
+    std::vector<int64_t> f, g;
+};
+
+// The split of a product's keys into prefix and bin, from sizes and ranges
+// alone.  way 1: bins that fit direct cells, with a few to a work item for
+// the degree box (so that items can be cut to an even size: box cells over 16
+// rounds of the device, 512 to GP_CELLS); way 2 (sparse): bins that only fit
+// the presence bitmap.  The fewest prefix variables that do: fewer groups,
+// larger blocks.
+static GpTry gp_try(int nvars, const VarParam *vp, int64_t na, int64_t nb, unsigned __int128 box, bool dense, int cus,
+                    int way) {
+    GpTry o;
+    const double pairs = (double)na * (double)nb;
+    if (na >= (int64_t)1 << 27 || nb >= (int64_t)1 << 27) return o;  // byte offsets of terms: 32 bits
+    if (std::min(na, nb) > 65536) return o;  // pairs of one monomial: see gp_split
+    if (!dense && (unsigned __int128)na * nb > 0xFFFFFFFFull) return o;
+    const int64_t target =
+        (int64_t)std::min<unsigned __int128>(GP_CELLS, std::max<unsigned __int128>(512, box / ((unsigned)cus * 16)));
+    const uint64_t fit = dense ? (way == 1 ? (uint64_t)target / 4 : (uint64_t)GP_CELLS)
+                               : (way == 1 ? (uint64_t)GP_CELLS : (uint64_t)GP_MAX_S);
+    const double most_bins = dense ? 2147483648.0 : std::max(16384.0, pairs / 4);
+    GrpSeg &g = o.g;
+    for (int d = 1; d <= nvars && !o.ok; d++) {
+        const VarParam &v = vp[d - 1];
+        if (v.range == 0 || v.range > 0xFFFFFFFFull) return o;
+        if (v.stride > fit) continue;
+        const unsigned __int128 bins = box / v.stride;
+        if ((double)bins > most_bins) return o;
+        if (!dense && way == 2 && v.stride <= (uint64_t)GP_CELLS) return o;
+        g.S = (uint32_t)v.stride;
+        g.d = (uint32_t)d;
+        g.nbins = (uint32_t)bins;
+        o.ok = true;
+    }
+    if (!o.ok) return o;
+    const int64_t nt = na + nb;
+    o.bytes = (int64_t)(sizeof(GpTerm) + 8) * nt + 4 * ((int64_t)g.nbins + 1) + 16 * 256 +
+              GP_PAD * (int64_t)sizeof(GpTerm);
+    if (dense) {
+        // runs of K bins, cut into work items of about 1/12 of a workgroup's
+        // share (512 workgroups), at least 2048 pairs
+        g.K = (uint32_t)vp[g.d - 1].range;
+        const int64_t runs = g.nbins / g.K, least = ((int64_t)g.K * g.S + GP_CELLS - 1) / GP_CELLS;
+        const double t = std::max(2048.0, pairs / (24.0 * cus));
+        while (pairs / (double)(1ull << g.csh) + 1e6 > 4e9) g.csh++;
+        g.T = (uint32_t)std::max(1.0, t / (double)(1ull << g.csh));
+        g.nsb = (runs + GP_SB - 1) / GP_SB;
+        o.ibound = runs * (least + 2) + (int64_t)(pairs / t * 1.1 * (double)(1u << g.csh)) + 64;
+        o.items = runs * least + (int64_t)(pairs / t);
+        o.bytes += g.nsb * (4 * GP_SB + 20) + o.ibound * ((int64_t)sizeof(GpItem) + 5);
+        return o;
+    }
+    // work items of about 4096 pairs, fewer while that leaves compute units idle
+    g.T = (uint32_t)std::min(4096.0, std::max(512.0, pairs / (4.0 * cus)));
+    g.span_bins = std::max<uint32_t>(1, (1u << GP_SPAN_LOG) / g.S);
+    // a bin that alone fills the direct cells to a quarter and more (with
+    // S <= GP_CELLS / 2 several fit and stay together up to gp.T pairs)
+    g.heavy = g.S <= (uint32_t)GP_CELLS && 2 * g.S > (uint32_t)GP_CELLS ? g.S / 4 : 0xFFFFFFFFu;
+    g.nsb = ((int64_t)g.nbins + GP_SB - 1) / GP_SB;
+    o.nres = (int64_t)std::min((unsigned __int128)na * nb, box);
+    // starts of work items: the first bin of a super-bin, a crossing of a
+    // multiple of T (or of a span), a heavy bin and the one after it
+    const int64_t span_cross = ((int64_t)g.nbins + g.span_bins - 1) / g.span_bins + g.nsb;
+    o.ibound = (int64_t)(pairs / g.T) + span_cross + 2 * g.nsb;
+    if (g.heavy != 0xFFFFFFFFu) o.ibound += 2 * (int64_t)(pairs / g.heavy);
+    o.ibound = std::min<int64_t>(o.ibound, g.nbins) + 1;
+    o.items = std::max<int64_t>((int64_t)(pairs / g.T), (g.nbins + g.span_bins - 1) / g.span_bins);
+    o.bytes += g.nsb * (4 * GP_SB + 20) + o.ibound * ((int64_t)sizeof(GpItem) + 5) + 12 * o.nres;
+    return o;
+}
+
+// Whether the operands' groups make that split pay.  Every work item looks
+// every outer group up (at most two lookups per pair, where the staged path
+// spends hundreds of instructions); a block below four pairs leaves most of
+// its lanes idle.  The bitmap needs some pairs per span to pay for its scan.
+static bool gp_pays(const GpTry &t, const GpCounts &c, int64_t na, int64_t nb, unsigned __int128 box, bool dense,
+                    int way) {
+    const double pairs = (double)na * (double)nb;
+    const double gf = (double)c.f[t.g.d - 1], gg = (double)c.g[t.g.d - 1];
+    if (pairs < 4096 || gf < 1 || gg < 1) return false;
+    if ((double)t.items * std::min(gf, gg) > 2 * pairs) return false;
+    const double block = pairs / (gf * gg);
+    if (dense) return block * t.g.nbins / t.items >= 4;
+    if (pairs / (double)box * (double)(1 << GP_SPAN_LOG) < 256) return false;
+    return block >= (way == 1 ? 4 : 1.5);
+}
+
+// counts: null, or the group counts of every product; products that pay then
+// run by prefix groups.  old_bytes: workspace that each product's own arrays
+// take in the general plan (counts null).
+static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> &in, const uint64_t *stats,
+                     const uint32_t *flags, const Tuning &tune_in, Plan &P, int cus, uint64_t smask,
+                     const std::vector<GpCounts> *counts, std::vector<int64_t> *old_bytes,
+                     std::vector<int64_t> *gp_bytes) {
     const int S = (int)in.size();
     P = Plan();
     P.nseg = S;
@@ -157,7 +259,12 @@ int plan_build(int nvars, int bits, int ring, const std::vector<SegInput> &in, c
             continue;
         }
         const uint64_t *st = stats + (size_t)q * 4 * nvars;  // f: min[nv] max[nv], g: min[nv] max[nv]
-        const uint64_t *fmin = st, *fmax = st + nvars, *gmin = st + 2 * nvars, *gmax = st + 3 * nvars;
+        uint64_t fmin[MAX_VARS], gmin[MAX_VARS];
+        const uint64_t *fmax = st + nvars, *gmax = st + 3 * nvars;
+        for (int v = 0; v < nvars; v++) {
+            fmin[v] = st[v] & smask;
+            gmin[v] = st[2 * nvars + v] & smask;
+        }
         unsigned __int128 b = 1;
         bool big = false;
         uint64_t lo_key = 0;
@@ -202,14 +309,8 @@ int plan_build(int nvars, int bits, int ring, const std::vector<SegInput> &in, c
             d.mode = SEG_DENSE;
         } else {
             d.mode = SEG_RAW;  // decided for the whole launch below
-            int kb = bitlen128(box[q] - 1);
-            max_bits = std::max(max_bits, kb);
         }
-        if (box[q] > (unsigned __int128)0xFFFFFFFFull) need_u64 = true;
     }
-    P.ksize = need_u64 ? 8 : 4;
-    P.passes = (max_bits + RADIX_BITS - 1) / RADIX_BITS;
-    P.max_bits = max_bits;
 
     // automatic settings: the autotuner's choice for the largest product's class
     Tuning tune = tune_in;
@@ -233,6 +334,38 @@ int plan_build(int nvars, int bits, int ring, const std::vector<SegInput> &in, c
             }
         }
     }
+
+    // prefix groups, where an explicit setting does not ask for another path
+    std::vector<GpTry> gt(S);
+    for (int q = 0; q < S; q++) {
+        DevSeg &d = P.segs[q];
+        const bool dense = d.mode == SEG_DENSE;
+        if (d.mode == SEG_EMPTY || ring == RING_F64) continue;
+        if (dense ? tune_in.tile_cfg >= 0 : tune.combine != -1 && tune.combine != 3) continue;
+        for (int way = 1; way <= 2 && !gt[q].ok; way++) {
+            GpTry t = gp_try(nvars, &P.vars[(size_t)q * nvars], d.na, d.nb, box[q], dense, cus, way);
+            if (!t.ok) continue;
+            if (gp_bytes) (*gp_bytes)[q] = std::max((*gp_bytes)[q], t.bytes);
+            if (counts && gp_pays(t, (*counts)[q], d.na, d.nb, box[q], dense, way)) {
+                gt[q] = t;
+                const double gf = (double)(*counts)[q].f[t.g.d - 1], gg = (double)(*counts)[q].g[t.g.d - 1];
+                // pairs that an outer group has with the bins of a work item
+                const double bins = dense ? (double)t.g.nbins / (double)t.items : std::max(1.0, std::min<double>(t.g.span_bins, (double)t.g.nbins * t.g.T / ((double)d.na * d.nb)));
+                gt[q].g.rows = (double)d.na * (double)d.nb / (gf * gg) * bins < 32 ? 1 : 0;
+                gt[q].g.swap = (*counts)[q].g[t.g.d - 1] < (*counts)[q].f[t.g.d - 1] ? 1 : 0;
+                d.mode = dense ? SEG_GRPD : SEG_GRP;
+            }
+        }
+    }
+    for (int q = 0; q < S; q++) {
+        const int m = P.segs[q].mode;
+        if (m == SEG_EMPTY || m == SEG_GRP || m == SEG_GRPD) continue;
+        if (m == SEG_RAW) max_bits = std::max(max_bits, bitlen128(box[q] - 1));
+        if (box[q] > (unsigned __int128)0xFFFFFFFFull) need_u64 = true;
+    }
+    P.ksize = need_u64 ? 8 : 4;
+    P.passes = (max_bits + RADIX_BITS - 1) / RADIX_BITS;
+    P.max_bits = max_bits;
 
     // one sort mode per launch: pair indices (products regenerated in the
     // reduction, FP64 summed in row-major order) or LDS-combined coefficients
@@ -333,12 +466,41 @@ int plan_build(int nvars, int bits, int ring, const std::vector<SegInput> &in, c
     int64_t nstage = 0, nbox = 0, nck = 0;
     for (int q = 0; q < S; q++) {
         DevSeg &d = P.segs[q];
+        if (d.mode == SEG_EMPTY) P.nempty++;
+        const bool grp = d.mode == SEG_GRP || d.mode == SEG_GRPD;
         d.ck_f = nck;
-        nck += d.na;
+        nck += grp ? 0 : d.na;
         d.ck_g = nck;
-        nck += d.nb;
-        P.cpre.push_back(P.cpre.back() + d.na);
-        P.cpre.push_back(P.cpre.back() + d.nb);
+        nck += grp ? 0 : d.nb;
+        P.cpre.push_back(P.cpre.back() + (grp ? 0 : d.na));
+        P.cpre.push_back(P.cpre.back() + (grp ? 0 : d.nb));
+        if (grp) {
+            const GpTry &t = gt[q];
+            d.gp = t.g;
+            d.gp.bq = (uint32_t)P.ngp++;
+            if (P.gp_sb_pre.empty()) P.gp_sb_pre.push_back(0);
+            d.gp.tf = P.gp_nterm;
+            d.gp.tg = P.gp_nterm + d.na;
+            P.gp_nterm += d.na + d.nb;
+            d.gp.lut = P.gp_nlut;
+            P.gp_nlut += (int64_t)t.g.nbins + 1;
+            d.gp.hist = P.gp_nsb * GP_SB;
+            d.gp.sb_first = P.gp_nsb;
+            P.gp_nsb += t.g.nsb;
+            P.gp_ibound += t.ibound;
+            P.gp_nres += t.nres;
+            P.gp_maxbins = std::max<int64_t>(P.gp_maxbins, t.g.nbins);
+            P.gp_maxgrp = std::max<int64_t>(P.gp_maxgrp, std::min(d.na, d.nb));
+            d.nb_div = make_div32(t.g.S);
+            P.gp_seg.push_back(q);
+            P.gp_sb_pre.push_back(P.gp_nsb);
+            if (d.mode == SEG_GRPD) {
+                P.ngp_box++;
+                P.gp_dpairs += (double)d.na * (double)d.nb;
+            } else {
+                P.ngp_sparse++;
+            }
+        }
         if (d.mode == SEG_COMBINE || d.mode == SEG_DENSE) {
             const int64_t tmn = (d.na + tc.tm - 1) / tc.tm, tnn = (d.nb + tc.tn - 1) / tc.tn;
             d.tile_first = P.tile_pre.back();
@@ -411,10 +573,17 @@ int plan_build(int nvars, int bits, int ring, const std::vector<SegInput> &in, c
             d.nb_div = make_div32((uint32_t)d.nb);
             P.nbk++;
         }
-        if (d.mode == SEG_DENSE) {
+        if (old_bytes) {
+            const int64_t pairs = d.na * d.nb;
+            int64_t &b = (*old_bytes)[q];
+            if (d.mode == SEG_BKT) b = 4 * (d.na + d.nb) + 12 * pairs + 6 * d.bk_nsb * BK_SB;
+            if (d.mode == SEG_RAW || d.mode == SEG_COMBINE) b = 2 * (int64_t)(P.ksize + P.vsize) * pairs;
+        }
+        if (d.mode == SEG_DENSE || d.mode == SEG_GRPD) {
             d.stage_base = nbox;
             d.stage_bound = (int64_t)box[q];
             nbox += d.stage_bound;
+            if (d.mode == SEG_GRPD) continue;
             d.dpart_first = P.dpart_pre.back();
             P.dseg.push_back(q);
             P.dpart_pre.push_back(P.dpart_pre.back() + (d.stage_bound + PART - 1) / PART);
@@ -473,6 +642,10 @@ int plan_build(int nvars, int bits, int ring, const std::vector<SegInput> &in, c
     P.o_bk_tile_pre = take(8 * std::max<size_t>(1, P.bk_tile_pre.size()));
     P.o_bk_seg = take(4 * std::max<size_t>(1, P.bk_seg.size()));
     P.o_bk_sb_pre = take(8 * std::max<size_t>(1, P.bk_sb_pre.size()));
+    if (P.ngp) {
+        P.o_gp_seg = take(4 * P.gp_seg.size());
+        P.o_gp_sb_pre = take(8 * P.gp_sb_pre.size());
+    }
     P.r_desc.off = desc0;
     P.r_desc.bytes = off - desc0;
     const size_t zero0 = off;
@@ -481,7 +654,14 @@ int plan_build(int nvars, int bits, int ring, const std::vector<SegInput> &in, c
     P.o_look_red = take((size_t)8 * std::max<int64_t>(1, P.nparts_bound));
     P.o_look_cmp = take((size_t)8 * std::max<int64_t>(1, P.ndparts));
     P.o_look_tile = take((size_t)8 * std::max<int64_t>(1, P.ntiles));
-    P.o_box = take((size_t)8 * std::max<int64_t>(1, nbox));
+    // (boxes of prefix-group products are stored whole and need no zeroing)
+    const bool zero_box = P.ntiles > 0;
+    if (zero_box) P.o_box = take((size_t)8 * std::max<int64_t>(1, nbox));
+    if (P.ngp) {
+        P.o_gp_hist = take((size_t)4 * GP_SB * std::max<int64_t>(1, P.gp_nsb));
+        P.o_gp_look = take((size_t)16 * std::max<int64_t>(1, P.gp_nsb));
+        P.o_gp_usum = take((size_t)4 * ((P.gp_ibound >> GP_USUM_LOG) + 1));
+    }
     P.o_bk_hist = take((size_t)4 * std::max<int64_t>(1, P.bk_nbins));
     P.o_bk_fill = take((size_t)4 * std::max<int64_t>(1, P.bk_wi_bound));
     P.o_bk_fatfill = take(8);
@@ -516,6 +696,19 @@ int plan_build(int nvars, int bits, int ring, const std::vector<SegInput> &in, c
     P.o_rtot = take((size_t)8 * RADIX * 2 * P.nrng);
     P.r_zero.off = zero0;
     P.r_zero.bytes = off - zero0;
+    if (!zero_box) P.o_box = take((size_t)8 * std::max<int64_t>(1, nbox));
+    if (P.ngp) {
+        P.o_gp_term = take(sizeof(GpTerm) * (size_t)(P.gp_nterm + GP_PAD));
+        P.o_gp_pfx = take((size_t)4 * P.gp_nterm);
+        P.o_gp_start = take((size_t)4 * (P.gp_nterm + 2 * P.ngp));
+        P.o_gp_ng = take((size_t)8 * P.ngp);
+        P.o_gp_lut = take((size_t)4 * P.gp_nlut);
+        P.o_gp_sbit = take((size_t)4 * (P.gp_nsb + 1));
+        P.o_gp_item = take(sizeof(GpItem) * (size_t)std::max<int64_t>(1, P.gp_ibound));
+        P.o_gp_u = take((size_t)4 * std::max<int64_t>(1, P.gp_ibound));
+        P.o_gp_rkey = take((size_t)4 * std::max<int64_t>(1, P.gp_nres));
+        P.o_gp_rcoef = take((size_t)8 * std::max<int64_t>(1, P.gp_nres));
+    }
     P.o_ppre = take((size_t)8 * (S + 1));
     P.o_chpre = take((size_t)8 * (S + 1));
     P.o_rpre = take((size_t)8 * (S + 1));
@@ -548,6 +741,40 @@ int plan_build(int nvars, int bits, int ring, const std::vector<SegInput> &in, c
     P.o_stBk = take((size_t)P.ksize * std::max<int64_t>(1, nstage));
     P.o_stBv = take((size_t)(P.nival ? 8 : P.vsize) * std::max<int64_t>(1, nstage));
     P.total = off;
+    return PM_OK;
+}
+
+int plan_build(int nvars, int bits, int ring, const std::vector<SegInput> &in, const uint64_t *stats,
+               const uint32_t *flags, const Tuning &tune, Plan &P, int cus, bool counted, int64_t limit) {
+    const size_t S = in.size();
+    // with wider fields (one variable) a minimum takes the whole word
+    counted = counted && bits <= 32;
+    const uint64_t smask = counted ? 0xFFFFFFFFull : ~0ull;
+    std::vector<int64_t> old_bytes(S, 0), gp_bytes(S, 0);
+    int rc = plan_core(nvars, bits, ring, in, stats, flags, tune, P, cus, smask, nullptr, &old_bytes, &gp_bytes);
+    if (rc) return rc;
+    int64_t more = 0, any = 0;
+    for (size_t q = 0; q < S; q++) {
+        any += gp_bytes[q];
+        more += std::max<int64_t>(0, gp_bytes[q] - old_bytes[q]);
+    }
+    P.report = P.total + (any ? align256((size_t)more + 4096) : 0);
+    const size_t report = P.report, general = P.total;
+    if (!any || !counted || limit < (int64_t)general) return PM_OK;
+    std::vector<GpCounts> counts(S);
+    for (size_t q = 0; q < S; q++) {
+        const uint64_t *st = stats + q * 4 * nvars;
+        for (int v = 0; v < nvars; v++) {
+            counts[q].f.push_back((int64_t)(st[v] >> 32));
+            counts[q].g.push_back((int64_t)(st[2 * nvars + v] >> 32));
+        }
+    }
+    Plan G;
+    rc = plan_core(nvars, bits, ring, in, stats, flags, tune, G, cus, smask, &counts, nullptr, nullptr);
+    if (rc || !G.ngp || (int64_t)G.total > limit) return PM_OK;
+    P = std::move(G);
+    P.total = std::max(P.total, general);
+    P.report = report;
     return PM_OK;
 }
 

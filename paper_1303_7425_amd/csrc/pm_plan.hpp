@@ -86,8 +86,18 @@ struct Plan {
     int64_t bk_ntiles = 0, bk_nsb = 0, bk_nbins = 0, bk_wi_bound = 0, bk_nstage = 0, bk_fat_cap = 0;
     size_t o_bk_hist = 0, o_bk_wbin = 0, o_bk_sbtot = 0, o_bk_sbwi = 0, o_bk_sbtb = 0, o_bk_sbpre = 0;
     size_t o_bk_tlist = 0, o_bk_tcnt = 0, o_bk_rkey = 0, o_bk_u = 0, o_bk_opre = 0, o_bk_wi = 0, o_bk_fill = 0, o_bk_fatc = 0, o_bk_fbase = 0, o_bk_fatfill = 0, o_bk_stage = 0, o_bk_tile_pre = 0, o_bk_seg = 0, o_bk_sb_pre = 0;
+    // prefix groups (SEG_GRP, SEG_GRPD)
+    int ngp = 0, ngp_sparse = 0;
+    std::vector<int32_t> gp_seg;
+    std::vector<int64_t> gp_sb_pre;
+    int64_t gp_nterm = 0, gp_nlut = 0, gp_nsb = 0, gp_ibound = 0, gp_nres = 0, gp_maxgrp = 0, gp_maxbins = 0;
+    int ngp_box = 0;            // SEG_GRPD products
+    double gp_dpairs = 0;       // their term pairs
+    size_t o_gp_seg = 0, o_gp_sb_pre = 0, o_gp_term = 0, o_gp_pfx = 0, o_gp_start = 0, o_gp_ng = 0;
+    size_t o_gp_lut = 0, o_gp_hist = 0, o_gp_look = 0, o_gp_sbit = 0, o_gp_item = 0, o_gp_u = 0, o_gp_usum = 0;
+    size_t o_gp_rkey = 0, o_gp_rcoef = 0;
     int64_t nstage = 0, nbox = 0, nck = 0;
-    int nsparse = 0, ndense = 0;
+    int nsparse = 0, ndense = 0, nempty = 0;
     // workspace layout
     Region r_stats, r_flags, r_desc, r_zero;
     size_t o_segs = 0, o_vars = 0, o_tile_pre = 0, o_tile_seg = 0, o_dpart_pre = 0, o_dseg = 0, o_cpre = 0;
@@ -101,7 +111,8 @@ struct Plan {
     int kl = 0;               // pair-index radix passes copy the operand keys to LDS (two workgroups per CU)
     int64_t nrng = 1;         // range rows of the radix-pass counters
     int rscan = 0;            // some product may have more than RSUM_MAX ranges
-    size_t total = 0;
+    size_t total = 0;         // workspace that this plan has to be given
+    size_t report = 0;        // workspace for every plan that these sizes and ranges may get
 };
 
 // Byte size of the statistics block written by the validation kernel.
@@ -113,9 +124,14 @@ struct SegInput {
 };
 
 // Returns PM_OK or an error code.  `stats` holds [nseg][2 sides][min|max][nvars]
-// and `flags` [nseg][2].  Output pointers of the segments are filled later.
+// and `flags` [nseg][2].  `counted`: as k_stats writes them, with the group
+// count of every variable in the upper half of the minima (bits <= 32).
+// `limit`: workspace at hand; a plan that needs more of it than the general
+// one is taken only where it fits, so no limit refuses what it held before.
+// Output pointers of the segments are filled later.
 int plan_build(int nvars, int bits, int ring, const std::vector<SegInput> &in, const uint64_t *stats,
-               const uint32_t *flags, const Tuning &tune, Plan &plan, int cus = 256);
+               const uint32_t *flags, const Tuning &tune, Plan &plan, int cus = 256, bool counted = true,
+               int64_t limit = INT64_MAX);
 
 // Byte size of the region holding the statistics, for a call with nseg products.
 size_t stats_region_bytes(int nseg, int nvars);

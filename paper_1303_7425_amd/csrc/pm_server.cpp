@@ -187,7 +187,7 @@ static void plan_and_launch(pm_server *s, std::vector<hipEvent_t> &free_events) 
     const Tuning &tune = default_tuning();
     auto plan_prefix = [&](int n, Plan &P) {
         std::vector<SegInput> sub(in.begin(), in.begin() + n);
-        return plan_build(nv, (int)L.bits, L.ring, sub, stats.data(), flags.data(), tune, P, cus);
+        return plan_build(nv, (int)L.bits, L.ring, sub, stats.data(), flags.data(), tune, P, cus, true, s->arena.size);
     };
     // requests that fail validation or have too small result arrays fail alone
     {
@@ -199,7 +199,7 @@ static void plan_and_launch(pm_server *s, std::vector<hipEvent_t> &free_events) 
             Plan P1;
             std::vector<SegInput> one{in[i]};
             int rc = plan_build(nv, (int)L.bits, L.ring, one, stats.data() + i * sw, flags.data() + 2 * i, tune, P1,
-                                cus);
+                                cus, true, 0);
             if (rc == PM_OK && group[i]->h.capacity < P1.bound[0]) rc = PM_ECAPACITY;
             if (rc == PM_OK && (int64_t)P1.total > s->arena.size) rc = PM_ENOMEM;
             if (rc != PM_OK) {

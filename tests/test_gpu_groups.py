@@ -1,0 +1,193 @@
+"""The prefix-group path (the automatic choice where the operands' sorted keys
+form runs of equal leading exponents) against the oracle at the sizes where
+its pieces change: blocks of 31 to 129 columns, more outer groups than
+threads, blocks that overflow the piece lists, work items of direct cells and
+of ranks, several rounds of ranks, one term per group, result arrays that are
+too small, terms that cancel, and launches that mix it with the other paths."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from paper_1303_7425_amd import workloads as W
+from test_gpu_parity import check
+
+
+def _pm():
+    from paper_1303_7425_amd import polymul
+    return polymul
+
+
+def grid(rng, ring, shape, bits, keep=1.0, step=None):
+    """All exponent vectors below `shape` (a share `keep` of them), scaled by
+    `step` per variable, with random coefficients."""
+    e = np.indices(shape).reshape(len(shape), -1).T * np.array(step or [1] * len(shape))
+    if keep < 1:
+        e = e[rng.uniform(size=len(e)) < keep]
+    lay = W.Layout(len(shape), bits, ring)
+    p = W.Poly(lay, np.sort(W.pack(e, len(shape), bits)), np.zeros(len(e), np.uint64))
+    return W.with_random_coefs(p, rng, ring)
+
+
+def takes_groups(f, g, name, scope="gp_"):
+    """check() against the oracle; the prefix-group kernels must have run."""
+    pm = _pm()
+    pm.profile_enable(True)
+    check(f, g, name)
+    names = list(pm.profile_read())
+    pm.profile_enable(False)
+    assert any(n.startswith(scope) for n in names), names
+
+
+@pytest.mark.parametrize("ring", ["modp", "i64", "modq"])
+@pytest.mark.parametrize("cols", [1, 3, 31, 32, 33, 63, 64, 65, 96, 97, 129])
+def test_columns_of_a_block(ring, cols):
+    rng = W.rng_for(cols)
+    f = grid(rng, ring, (20, 37), 16, step=(1, 3))
+    g = grid(rng, ring, (60, cols), 16, step=(2, 5))
+    takes_groups(f, g, f"{cols} columns") if len(f) * len(g) >= 100000 else check(f, g, f"{cols} columns")
+
+
+@pytest.mark.parametrize("ring", ["modp", "f64"])
+@pytest.mark.parametrize("n", [5, 7, 9])
+def test_sparse_family(ring, n):
+    check(*W.config3(ring, n=n), f"sparse family n={n}")
+
+
+@pytest.mark.parametrize("ring", ["modp", "i64", "modq"])
+def test_degree_box(ring):
+    rng = W.rng_for(3)
+    for shape_f, shape_g in (((9, 10, 11), (12, 8, 5)), ((40, 45), (50, 33)), ((2, 2, 2, 2, 2, 2, 2), (3, 3, 3, 3, 3, 3, 3))):
+        takes_groups(grid(rng, ring, shape_f, 8), grid(rng, ring, shape_g, 8), f"box {shape_f} x {shape_g}", "gp_box")
+
+
+@pytest.mark.parametrize("ring", ["modp", "i64"])
+def test_more_groups_than_threads(ring):
+    # 900 outer groups: a second round of listing, and single columns of 700
+    # rows that overflow the piece lists
+    rng = W.rng_for(5)
+    takes_groups(grid(rng, ring, (30, 30, 4), 10, step=(1, 1, 7)), grid(rng, ring, (25, 28, 3), 10, step=(1, 1, 11)), "many groups")
+    takes_groups(grid(rng, ring, (3, 700), 12), grid(rng, ring, (4, 700), 12, step=(1, 2)), "long groups")
+
+
+@pytest.mark.parametrize("ring", ["modp", "i64", "modq"])
+def test_rounds_of_ranks(ring):
+    # bins of 50001 cells with about 20000 distinct keys each: a presence
+    # bitmap and several rounds of ranks, in both halves of the bitmap
+    rng = W.rng_for(9)
+
+    def poly():
+        lay = W.Layout(2, 16, ring)
+        x = np.repeat(np.arange(16), 75)
+        y = np.concatenate([rng.choice(25001, 75, replace=False) for _ in range(16)])
+        p = W.Poly(lay, np.sort(W.pack(np.stack([x, y], 1), 2, 16)), np.zeros(len(x), np.uint64))
+        return W.with_random_coefs(p, rng, ring)
+
+    takes_groups(poly(), poly(), "rounds of ranks", "gp_reduce")
+
+
+@pytest.mark.parametrize("ring", ["modp", "modq"])
+def test_one_term_per_group(ring):
+    # a thread per outer term (few terms share a prefix)
+    rng = W.rng_for(10)
+    f, g = W.random_sparse(rng, 777, 6, 10, 15, ring), W.random_sparse(rng, 9000, 6, 10, 15, ring)
+    takes_groups(f, g, "random", "gp_reduce")
+    takes_groups(g, f, "random, swapped", "gp_reduce")
+
+
+def test_many_additions_wrap():
+    # p - 1 everywhere: every cell's sum wraps past 2^64 many times
+    lay = W.Layout(2, 12, "modp")
+    e = np.indices((30, 60)).reshape(2, -1).T
+    k = np.sort(W.pack(e, 2, 12))
+    for ring, top in (("modp", W.P61 - 1), ("modq", W.Q64 - 1)):
+        p = W.Poly(W.Layout(2, 12, ring), k, np.full(len(k), top, np.uint64))
+        takes_groups(p, p, f"wraps {ring}")
+
+
+def test_truncated_and_cancelled():
+    import torch
+    pm = _pm()
+    rng = W.rng_for(12)
+    lay = W.Layout(3, 10, "i64")
+    e = np.indices((9, 9, 30)).reshape(3, -1).T
+    keys = np.sort(W.pack(e * np.array([1, 1, 9]), 3, 10))
+    # coefficients +1 / -1: many terms cancel
+    f, g = (W.Poly(lay, keys, rng.choice([-1, 1], len(keys)).astype(np.int64)) for _ in range(2))
+    takes_groups(f, g, "cancelling")
+    df, dg = pm.to_device(f), pm.to_device(g)
+    full = pm.MulCall((3, 10, "i64"), df, dg)
+    full.run()
+    n = full.n()
+    short = pm.MulCall((3, 10, "i64"), df, dg, capacity=n // 3)
+    short.run()
+    assert short.n() == n
+    for a, b in zip(short.out[:2], full.out[:2]):
+        assert torch.equal(a[:n // 3], b[:n // 3])
+
+
+@pytest.mark.parametrize("ring", ["modp", "i64"])
+def test_batch_of_every_kind(ring):
+    # prefix groups (sparse and degree box), staged work items, empty and
+    # single-term operands in one launch, validated and as a replayed graph
+    pm = _pm()
+    import oracle
+    import torch
+    rng = W.rng_for(13)
+
+    def rnd(n):
+        return W.random_sparse(rng, n, 4, 16, 31, ring)
+
+    box = grid(rng, ring, (6, 6, 6, 6), 16), grid(rng, ring, (5, 7, 4, 6), 16)
+    slab = grid(rng, ring, (6, 6, 1, 20), 16, step=(1, 1, 1, 31)), grid(rng, ring, (5, 5, 9, 8), 16, step=(1, 1, 19, 7))
+    empty = W.Poly(W.Layout(4, 16, ring), np.zeros(0, np.uint64), np.zeros(0, np.int64 if ring == "i64" else np.uint64))
+    pairs = [box, (rnd(40), rnd(60)), slab, (empty, rnd(5)), (rnd(1), rnd(900)), (slab[1], slab[0]), box]
+    call = pm.BatchCall((4, 16, ring), [pm.to_device(f) for f, _ in pairs], [pm.to_device(g) for _, g in pairs])
+
+    def compare():
+        torch.cuda.synchronize()
+        assert pm.last_call_status() == 0
+        for (k, c), (f, g) in zip(call.results(), pairs):
+            wk, wc, _ = oracle.mul(f, g)
+            assert np.array_equal(k, wk) and np.array_equal(c.view(np.uint64), np.asarray(wc).view(np.uint64))
+
+    call.run()
+    compare()
+    call.prepare_graph()
+    for _ in range(3):
+        call.out_n.fill_(-1)
+        call.launch_graph()
+        compare()
+
+
+def test_graph_replay_with_other_groups():
+    # a prepared batch's operands may change within their ranges: other groups
+    pm = _pm()
+    import oracle
+    import torch
+    rng = W.rng_for(14)
+    n, lay = 1500, W.Layout(3, 10, "modp")
+
+    def poly(shape):
+        e = np.indices(shape).reshape(3, -1).T
+        corner = np.array([[0, 0, 0], [39, 39, 39]])
+        pick = e[rng.choice(len(e), n, replace=False)]
+        k = np.unique(np.concatenate([W.pack(corner, 3, 10), W.pack(pick, 3, 10)]))
+        return k[np.sort(np.concatenate([[0, len(k) - 1], 1 + rng.choice(len(k) - 2, n - 2, replace=False)]))]
+
+    dev, call = None, None
+    for shape in ((10, 10, 40), (40, 40, 2), (40, 2, 40)):
+        f, g = (W.Poly(lay, k, W.residues(rng, n)) for k in (poly(shape), poly(shape)))
+        if call is None:
+            dev = pm.to_device(f), pm.to_device(g)
+            call = pm.BatchCall((3, 10, "modp"), [dev[0]], [dev[1]])
+            call.prepare_graph()
+        for p, d in zip((f, g), dev):
+            d.keys.copy_(torch.from_numpy(p.keys.view(np.int64)))
+            d.coefs.copy_(torch.from_numpy(p.coefs.view(np.int64)))
+        call.launch_graph()
+        torch.cuda.synchronize()
+        assert pm.last_call_status() == 0
+        (k, c), = call.results()
+        wk, wc, _ = oracle.mul(f, g)
+        assert np.array_equal(k, wk) and np.array_equal(c, wc)
