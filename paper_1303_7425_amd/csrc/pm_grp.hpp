@@ -915,144 +915,317 @@ __global__ __launch_bounds__(GR_T) __attribute__((amdgpu_waves_per_eu(4))) void 
 }
 
 // ---------------------------------------------------------------------------
-// k_gp_copy: a workgroup takes a run of consecutive work items; the result
-// offset of its first one is the sum of the term counts of the product's
-// earlier ones (gp_usum holds them per 2^GP_USUM_LOG items).
+// k_gp_f64: FP64 work items.  Every monomial's products are added left to
+// right in row-major order, so one wave takes a whole work item and adds one
+// row at a time: the LDS additions of a wave are carried out in the order it
+// issues them, none waits for another, and a row meets a monomial at most once.
+// Rows ascend (f's groups are the outer ones); of a block with more than 64
+// columns the last ones come first, since a monomial's later rows meet it in
+// earlier columns.  FC: LDS cells of a wave (a work item's key span).
+// ---------------------------------------------------------------------------
+// A piece: up to 64 rows, a lane each, read across lanes one after another
+// (scalar loads would share their wait counter with the LDS additions), and
+// up to 64 columns, a lane each.
+struct GpRows {
+    u32x3 a, b;
+    u32 cols, rows;  // 0 rows: no more pieces
+};
+
+template <int FC>
+__global__ __launch_bounds__(64) void k_gp_f64(Ctx C) {
+    __shared__ __align__(16) double acc[FC];
+    const u32 lane = threadIdx.x;
+    for (u32 c = lane; c < (u32)FC; c += 64) acc[c] = 0.0;
+    const i64 nt = (i64)uniform32(C.gp_sbit[C.gp_nsb]), G = gridDim.x;
+    const i64 own = max((i64)1, nt / G / 2);
+    i64 t = blockIdx.x, round = 1;
+    int qc = -1;
+    u32 S = 1;
+    GpOperand O, I;
+    const u32 *lut = nullptr;
+    GpItem it{};
+    if (t < nt) it = C.gp_item[t];
+    while (t < nt) {
+        const int q = (int)uniform32((u32)it.q);
+        const u32 B0 = uniform32(it.bin_lo), B1 = uniform32(it.bin_hi);
+        const u64 off = (u64)uniform64((i64)it.off);
+        if (q != qc) {
+            const DevSeg &s = C.segs[q];
+            const int bq = (int)uniform32(s.gp.bq);
+            S = uniform32(s.gp.S);
+            O = gp_operand(C, s, bq, 0);
+            I = gp_operand(C, s, bq, 1);
+            lut = C.gp_lut + uniform64(s.gp.lut);
+            qc = q;
+        }
+        u32 tk = 0;
+        if (round >= own && lane == 0) tk = atomicAdd(&C.counters[CNT_GP_REDUCE], 1u);
+        const u32 base = B0 * S, span = (B1 - B0) * S;
+        // outer groups, 64 at a time, a lane each: prefix and rows are loaded
+        // two steps ahead, the columns one step ahead
+        GpOuter c1{}, c2{};
+        auto fetch = [&](u32 g) {
+            GpOuter o{};
+            const u32 at = min(g + lane, O.groups);
+            o.p = g + lane < O.groups ? gload(O.pfx + at) : ~0u;
+            o.i0 = gload(O.start + at);
+            o.rows = gload(O.start + min(at + 1, O.groups));
+            return o;
+        };
+        u32 g = 0;
+        c1 = fetch(0);
+        gp_cols(lut, c1.p, B0, B1, c1.j0, c1.nc);
+        c2 = fetch(64);
+        u64 todo = 0;
+        bool more = true;
+        GpOuter cur{};
+        u32 i0 = 0, R = 0, j0 = 0, N = 0, r = 0;
+        i32 cc = -1;
+        auto next = [&](GpRows &p) {
+            p.rows = 0;
+            if (r >= R) {
+                r = 0;
+                cc -= 64;
+                if (cc < 0) {
+                    while (!todo && more) {
+                        cur = c1;
+                        todo = __ballot(cur.nc != 0);
+                        g += 64;
+                        more = g < O.groups;
+                        if (more) {
+                            c1 = c2;
+                            gp_cols(lut, c1.p, B0, B1, c1.j0, c1.nc);
+                            c2 = fetch(g + 64);
+                        }
+                    }
+                    if (!todo) {  // no more pieces, now and in every later call
+                        R = 0;
+                        cc = -1;
+                        return;
+                    }
+                    const int l = (int)__ffsll((unsigned long long)todo) - 1;
+                    todo &= todo - 1;
+                    i0 = (u32)__builtin_amdgcn_readlane((int)cur.i0, l);
+                    R = (u32)__builtin_amdgcn_readlane((int)cur.rows, l) - i0;
+                    j0 = (u32)__builtin_amdgcn_readlane((int)cur.j0, l);
+                    N = (u32)__builtin_amdgcn_readlane((int)cur.nc, l);
+                    cc = (i32)((N - 1) & ~63u);
+                }
+            }
+            p.rows = min(R - r, 64u);
+            p.cols = min(N - (u32)cc, 64u);
+            p.b = gp_term((const GpTerm *)((const char *)I.t + (j0 + (u32)cc) * (u32)sizeof(GpTerm)),
+                          lane * (u32)sizeof(GpTerm));
+            p.a = gp_term((const GpTerm *)((const char *)O.t + (i0 + r) * (u32)sizeof(GpTerm)), lane * (u32)sizeof(GpTerm));
+            r += 64;
+        };
+        auto run = [&](const GpRows &p) {
+            const bool in = lane < p.cols;
+            const double b = __longlong_as_double((long long)(((u64)p.b.y << 32) | p.b.x));
+            const u32 kb = p.b.z - base;
+            auto row = [&](u32 u) {
+                const u64 a = ((u64)(u32)__builtin_amdgcn_readlane((int)p.a.y, (int)u) << 32) |
+                              (u32)__builtin_amdgcn_readlane((int)p.a.x, (int)u);
+                const double v = __longlong_as_double((long long)a) * b;
+                unsafeAtomicAdd(&acc[(u32)__builtin_amdgcn_readlane((int)p.a.z, (int)u) + kb], v);
+            };
+            if (in) {
+                u32 u = 0;
+                for (; u + 4 <= p.rows; u += 4) {
+                    row(u);
+                    row(u + 1);
+                    row(u + 2);
+                    row(u + 3);
+                }
+                for (; u < p.rows; u++) row(u);
+            }
+        };
+        GpRows p0, p1, p2;
+        next(p0);
+        next(p1);
+        while (p0.rows) {
+            next(p2);
+            run(p0);
+            if (!p1.rows) break;
+            next(p0);
+            run(p1);
+            if (!p2.rows) break;
+            next(p1);
+            run(p2);
+        }
+        // the next work item's descriptor
+        const i64 tn = round < own ? (i64)blockIdx.x + round * G : own * G + (i64)uniform32(tk);
+        GpItem nx{};
+        if (tn < nt) nx = C.gp_item[tn];
+        u32 done = 0;
+        // four cells of a lane at a time (a sum is never -0: it started at +0)
+        for (u32 c0 = 0; c0 < span; c0 += 256) {
+            ulonglong2 x[2];
+#pragma unroll
+            for (int e = 0; e < 2; e++) x[e] = *(ulonglong2 *)&acc[c0 + e * 128 + lane * 2];
+            if (!__ballot((x[0].x | x[0].y | x[1].x | x[1].y) != 0)) continue;
+#pragma unroll
+            for (int e = 0; e < 2; e++) {
+                const u32 c = c0 + e * 128 + lane * 2;
+                *(ulonglong2 *)&acc[c] = make_ulonglong2(0, 0);
+                const u64 b0 = __ballot(x[e].x != 0), b1 = __ballot(x[e].y != 0);
+                u64 at = off + done + mbcnt(b0) + mbcnt(b1);
+                if (x[e].x) {
+                    C.gp_rkey[at] = c;
+                    C.gp_rcoef[at] = x[e].x;
+                    at++;
+                }
+                if (x[e].y) {
+                    C.gp_rkey[at] = c + 1;
+                    C.gp_rcoef[at] = x[e].y;
+                }
+                done += (u32)__popcll(b0) + (u32)__popcll(b1);
+            }
+        }
+        if (lane == 0) {
+            C.gp_u[t] = done;
+            atomicAdd(&C.gp_usum[t >> GP_USUM_LOG], done);
+        }
+        t = tn;
+        it = nx;
+        round++;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// k_gp_copy: a workgroup takes a run of consecutive work items; its waves share
+// the terms of a large one and take the small ones in turn.  The result offset of the first one is the sum of the term counts of
+// the product's earlier ones (gp_usum holds them per 2^GP_USUM_LOG items; every
+// wave adds them up for itself).
 // ---------------------------------------------------------------------------
 constexpr int GC_T = 256;
-constexpr int GC_B = 4;  // terms per thread per batch
+constexpr int GC_B = 4;  // terms per lane per batch
 
 __device__ inline u64 gp_range_sum(const u32 *v, i64 a, i64 b) {
     u64 x = 0;
-    for (i64 i = a + threadIdx.x; i < b; i += GC_T) x += v[i];
+    for (i64 i = a + (threadIdx.x & 63); i < b; i += 64) x += v[i];
     return x;
 }
 
+// The fields of one product that placing its terms takes.
+struct GpOut {
+    u64 *hk, *hc;
+    const u64 *box;
+    i64 cap, last;
+    u64 lo_key;
+    const VarParam *vp;
+    Div32 sd;
+    int d, nvars;
+};
+
+// Term at of h: cell x of the work item that starts at bin b.
+__device__ inline void gp_put(const GpOut &o, i64 at, u32 b, u32 x, u64 coef) {
+    if (at >= o.cap) return;
+    u32 hi = div32(x, o.sd);
+    u32 low = x - hi * o.sd.d;
+    hi += b;
+    u64 key = o.lo_key;
+    for (int v = o.nvars - 1; v >= 0; v--) {
+        const Div32 dv{uniform32(o.vp[v].rdiv.m), uniform32(o.vp[v].rdiv.s1), uniform32(o.vp[v].rdiv.s2),
+                       uniform32(o.vp[v].rdiv.d)};
+        const u32 y = v >= o.d ? low : hi;
+        const u32 z = div32(y, dv);
+        key += (u64)(y - z * dv.d) << uniform32(o.vp[v].shift);
+        if (v >= o.d) low = z;
+        else hi = z;
+    }
+    o.hk[at] = key;
+    o.hc[at] = coef;
+}
+
 __global__ __launch_bounds__(GC_T) void k_gp_copy(Ctx C) {
-    __shared__ u32 s_vl[5 * MAX_VARS];
-    __shared__ u64 s_sum[GC_T / 64];
-    const i64 nt = (i64)C.gp_sbit[C.gp_nsb];
+    const i64 nt = (i64)uniform32(C.gp_sbit[C.gp_nsb]);
+    const u32 lane = threadIdx.x & 63, w = uniform32(threadIdx.x >> 6);
+    constexpr u32 NW = GC_T / 64;
     const i64 t0 = nt * blockIdx.x / gridDim.x, t1 = nt * (blockIdx.x + 1) / gridDim.x;
     if (t0 >= t1) return;
-    const int nvars = C.nvars;
-    const u32 lane = threadIdx.x & 63, w = uniform32(threadIdx.x >> 6);
-    int q = C.gp_item[t0].q;
+    int q = (int)uniform32((u32)C.gp_item[t0].q), qc = -1;
     u64 at0;
     {
-        const i64 f = (i64)C.gp_sbit[C.segs[q].gp.sb_first];
+        const i64 f = (i64)uniform32(C.gp_sbit[C.segs[q].gp.sb_first]);
         const i64 m = (i64)1 << GP_USUM_LOG;
         const i64 f1 = min((f + m - 1) & ~(m - 1), t0), g1 = max(t0 & ~(m - 1), f1);
         u64 x = gp_range_sum(C.gp_u, f, f1) + gp_range_sum(C.gp_u, g1, t0);
         if (g1 > f1) x += gp_range_sum(C.gp_usum, f1 >> GP_USUM_LOG, g1 >> GP_USUM_LOG);
-        x = wave_sum_u64(x);
-        if ((threadIdx.x & 63) == 0) s_sum[threadIdx.x >> 6] = x;
-        __syncthreads();
-        at0 = 0;
-        for (int i = 0; i < GC_T / 64; i++) at0 += s_sum[i];
+        at0 = (u64)uniform64((i64)wave_sum_u64(x));
     }
-    int qc = -1;
-    u64 *hk = nullptr, *hc = nullptr;
-    const u64 *box = nullptr;
-    i64 cap = 0, last = 0;
-    u64 lo_key = 0;
-    Div32 sd{0, 0, 0, 1};
-    int d = 1;
-    // term at of h: cell x of the work item that starts at bin b
-    auto put = [&](i64 at, u32 b, u32 x, u64 coef) {
-        if (at >= cap) return;
-        u32 hi = div32(x, sd);
-        u32 low = x - hi * sd.d;
-        hi += b;
-        u64 key = lo_key;
-        for (int v = nvars - 1; v >= 0; v--) {
-            const Div32 dv{s_vl[5 * v + 1], s_vl[5 * v + 2], s_vl[5 * v + 3], s_vl[5 * v + 4]};
-            const u32 y = v >= d ? low : hi;
-            const u32 z = div32(y, dv);
-            key += (u64)(y - z * dv.d) << s_vl[5 * v];
-            if (v >= d) low = z;
-            else hi = z;
-        }
-        hk[at] = key;
-        hc[at] = coef;
-    };
+    GpOut o{};
+    GpItem ci{};
+    u32 cu = 0;
     for (i64 t = t0; t < t1; t++) {
-        const GpItem it = C.gp_item[t];
-        q = it.q;
-        const u32 u = C.gp_u[t];
+        const u32 l = (u32)(t - t0) & 63;
+        if (l == 0) {  // descriptors and counts of the next 64 work items, a lane each
+            const i64 i = min(t + lane, t1 - 1);
+            ci = C.gp_item[i];
+            cu = C.gp_u[i];
+        }
+        const u32 bin_lo = (u32)__builtin_amdgcn_readlane((int)ci.bin_lo, (int)l);
+        const u32 bin_hi = (u32)__builtin_amdgcn_readlane((int)ci.bin_hi, (int)l);
+        q = __builtin_amdgcn_readlane(ci.q, (int)l);
+        const u64 off = ((u64)(u32)__builtin_amdgcn_readlane((int)(ci.off >> 32), (int)l) << 32) |
+                        (u32)__builtin_amdgcn_readlane((int)(u32)ci.off, (int)l);
+        const u32 u = (u32)__builtin_amdgcn_readlane((int)cu, (int)l);
         if (q != qc) {
             const DevSeg &s = C.segs[q];
             if (qc >= 0) at0 = 0;
-            __syncthreads();
-            const VarParam *vp = C.vars + s.var_off;
-            for (int v = threadIdx.x; v < nvars; v += GC_T) {
-                s_vl[5 * v] = vp[v].shift;
-                s_vl[5 * v + 1] = vp[v].rdiv.m;
-                s_vl[5 * v + 2] = vp[v].rdiv.s1;
-                s_vl[5 * v + 3] = vp[v].rdiv.s2;
-                s_vl[5 * v + 4] = vp[v].rdiv.d;
-            }
-            hk = s.hk;
-            hc = s.hc;
-            cap = s.cap;
-            lo_key = s.lo_key;
-            sd = s.nb_div;
-            d = (int)s.gp.d;
-            box = s.gp.K ? C.box + s.stage_base : nullptr;
-            last = (i64)C.gp_sbit[s.gp.sb_first + s.gp.nsb] - 1;
-            __syncthreads();
+            o.hk = (u64 *)uniform64((i64)s.hk);
+            o.hc = (u64 *)uniform64((i64)s.hc);
+            o.cap = uniform64(s.cap);
+            o.lo_key = (u64)uniform64((i64)s.lo_key);
+            o.vp = C.vars + uniform64(s.var_off);
+            o.sd = Div32{uniform32(s.nb_div.m), uniform32(s.nb_div.s1), uniform32(s.nb_div.s2), uniform32(s.nb_div.d)};
+            o.d = (int)uniform32(s.gp.d);
+            o.nvars = C.nvars;
+            o.box = uniform32(s.gp.K) ? C.box + uniform64(s.stage_base) : nullptr;
+            o.last = (i64)uniform32(C.gp_sbit[uniform64(s.gp.sb_first) + uniform64(s.gp.nsb)]) - 1;
             qc = q;
         }
-        if (box) {
+        const bool share = !o.box && u > 64 * GC_B;
+        if (!share && (l & (NW - 1)) != w) {
+            // another wave's
+        } else if (o.box) {
             // the non-zero cells of the degree box
-            const u64 *cell = box + (i64)it.bin_lo * sd.d;
-            const u32 n = (it.bin_hi - it.bin_lo) * sd.d;
+            const u64 *cell = o.box + (i64)bin_lo * o.sd.d;
+            const u32 n = (bin_hi - bin_lo) * o.sd.d;
             u64 at = at0;
-            for (u32 c0 = 0; c0 < n && u; c0 += GC_T * GC_B) {
+            for (u32 c0 = 0; c0 < n && u; c0 += 64 * GC_B) {
                 u64 v[GC_B];
-                u32 rk[GC_B], before = 0;
 #pragma unroll
-                for (int e = 0; e < GC_B; e++) v[e] = cell[min(c0 + w * (64 * GC_B) + e * 64 + lane, n - 1)];
+                for (int e = 0; e < GC_B; e++) v[e] = cell[min(c0 + e * 64 + lane, n - 1)];
 #pragma unroll
                 for (int e = 0; e < GC_B; e++) {
-                    if (c0 + w * (64 * GC_B) + e * 64 + lane >= n) v[e] = 0;
-                    const u64 bal = __ballot(v[e] != 0);
-                    rk[e] = before + mbcnt(bal);
-                    before += (u32)__popcll(bal);
+                    const bool in = v[e] && c0 + e * 64 + lane < n;
+                    const u64 bal = __ballot(in);
+                    if (in) gp_put(o, (i64)(at + mbcnt(bal)), bin_lo, c0 + e * 64 + lane, v[e]);
+                    at += (u64)__popcll(bal);
                 }
-                __syncthreads();
-                if (lane == 0) s_sum[w] = before;
-                __syncthreads();
-                u64 tot = 0;
-                for (u32 i = 0; i < GC_T / 64; i++) {
-                    if (i == w) before = (u32)tot;
-                    tot += s_sum[i];
-                }
-#pragma unroll
-                for (int e = 0; e < GC_B; e++)
-                    if (v[e]) put((i64)(at + before + rk[e]), it.bin_lo, c0 + w * (64 * GC_B) + e * 64 + lane, v[e]);
-                at += tot;
             }
         } else {
-            const u32 *rk = C.gp_rkey + it.off;
-            const u64 *rc = C.gp_rcoef + it.off;
-            for (u32 r0 = 0; r0 < u; r0 += GC_T * GC_B) {
+            const u32 *rk = C.gp_rkey + off;
+            const u64 *rc = C.gp_rcoef + off;
+            for (u32 r0 = share ? w * (64 * GC_B) : 0u; r0 < u; r0 += share ? NW * 64 * GC_B : 64 * GC_B) {
                 u32 ck[GC_B];
                 u64 cv[GC_B];
 #pragma unroll
                 for (int e = 0; e < GC_B; e++) {
-                    const u32 r = min(r0 + e * GC_T + threadIdx.x, u - 1);
+                    const u32 r = min(r0 + e * 64 + lane, u - 1);
                     ck[e] = rk[r];
                     cv[e] = rc[r];
                 }
 #pragma unroll
                 for (int e = 0; e < GC_B; e++) {
-                    const u32 r = r0 + e * GC_T + threadIdx.x;
-                    if (r < u) put((i64)(at0 + r), it.bin_lo, ck[e], cv[e]);
+                    const u32 r = r0 + e * 64 + lane;
+                    if (r < u) gp_put(o, (i64)(at0 + r), bin_lo, ck[e], cv[e]);
                 }
             }
         }
         at0 += u;
-        if (t == last && threadIdx.x == 0) *C.segs[q].n_out = (i64)at0;
+        if (t == o.last && threadIdx.x == 0) *C.segs[q].n_out = (i64)at0;
     }
 }
 

@@ -1926,6 +1926,16 @@ template <int RING>
 static void launch_gp_sparse(const Plan &P, const Ctx &C, hipStream_t st, int cus) {
     {
         ProfScope ps("gp_reduce", st);
+        if constexpr (RING == RING_F64) {
+            // the waves whose cells fit the compute units' LDS
+            auto go = [&](auto k, int fc) {
+                hipLaunchKernelGGL(k, dim3(grid_for(P.gp_ibound, cus * ((160 << 10) / (fc * 8 + 256)))), dim3(64), 0, st, C);
+            };
+            if (P.gp_fc <= 1024) go(k_gp_f64<1024>, 1024);
+            else if (P.gp_fc <= 2048) go(k_gp_f64<2048>, 2048);
+            else go(k_gp_f64<GP_F64_CELLS>, GP_F64_CELLS);
+            return;
+        } else
         hipLaunchKernelGGL((k_gp_reduce<RING, false>), dim3(grid_for(P.gp_ibound, cus * 2)), dim3(GR_T), 0, st, C, (i64)0,
                            (i64)1);
     }
@@ -1955,9 +1965,7 @@ static void launch_typed(const Plan &P, const Ctx &C, hipStream_t st, int cus, i
             launch_gp_box<RING>(P, C, st, cus, part == PART_HEAD ? 0 : -1);
     }
     if (part == PART_HEAD) return;
-    if constexpr (RING != RING_F64) {
-        if (P.ngp_sparse > 0) launch_gp_sparse<RING>(P, C, st, cus);
-    }
+    if (P.ngp_sparse > 0) launch_gp_sparse<RING>(P, C, st, cus);
     if (P.ngp > 0) {
         ProfScope ps("gp_copy", st);
         hipLaunchKernelGGL(k_gp_copy, dim3(grid_for(P.gp_ibound, cus * 8)), dim3(GC_T), 0, st, C);

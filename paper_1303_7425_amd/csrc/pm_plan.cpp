@@ -139,7 +139,7 @@ struct GpCounts {
 // the presence bitmap.  The fewest prefix variables that do: fewer groups,
 // larger blocks.
 static GpTry gp_try(int nvars, const VarParam *vp, int64_t na, int64_t nb, unsigned __int128 box, bool dense, int cus,
-                    int way) {
+                    int way, bool f64) {
     GpTry o;
     const double pairs = (double)na * (double)nb;
     if (na >= (int64_t)1 << 27 || nb >= (int64_t)1 << 27) return o;  // byte offsets of terms: 32 bits
@@ -147,7 +147,8 @@ static GpTry gp_try(int nvars, const VarParam *vp, int64_t na, int64_t nb, unsig
     if (!dense && (unsigned __int128)na * nb > 0xFFFFFFFFull) return o;
     const int64_t target =
         (int64_t)std::min<unsigned __int128>(GP_CELLS, std::max<unsigned __int128>(512, box / ((unsigned)cus * 16)));
-    const uint64_t fit = dense ? (way == 1 ? (uint64_t)target / 4 : (uint64_t)GP_CELLS)
+    if (f64 && way != 1) return o;
+    const uint64_t fit = f64 ? (uint64_t)GP_F64_CELLS : dense ? (way == 1 ? (uint64_t)target / 4 : (uint64_t)GP_CELLS)
                                : (way == 1 ? (uint64_t)GP_CELLS : (uint64_t)GP_MAX_S);
     const double most_bins = dense ? 2147483648.0 : std::max(16384.0, pairs / 4);
     GrpSeg &g = o.g;
@@ -181,6 +182,20 @@ static GpTry gp_try(int nvars, const VarParam *vp, int64_t na, int64_t nb, unsig
         o.bytes += g.nsb * (4 * GP_SB + 20) + o.ibound * ((int64_t)sizeof(GpItem) + 5);
         return o;
     }
+    if (f64) {
+        // one wave per work item: its bins fit the wave's cells
+        const int fc = g.S <= 1024 ? 1024 : g.S <= 2048 ? 2048 : GP_F64_CELLS;
+        g.T = (uint32_t)std::min(2048.0, std::max(256.0, pairs / (16.0 * cus)));
+        g.span_bins = std::max<uint32_t>(1, (uint32_t)fc / g.S);
+        g.heavy = 0xFFFFFFFFu;
+        g.nsb = ((int64_t)g.nbins + GP_SB - 1) / GP_SB;
+        o.nres = (int64_t)std::min((unsigned __int128)na * nb, box);
+        const int64_t cross = ((int64_t)g.nbins + g.span_bins - 1) / g.span_bins + g.nsb;
+        o.ibound = std::min<int64_t>((int64_t)(pairs / g.T) + cross + 2 * g.nsb, g.nbins) + 1;
+        o.items = std::max<int64_t>((int64_t)(pairs / g.T), cross);
+        o.bytes += g.nsb * (4 * GP_SB + 20) + o.ibound * ((int64_t)sizeof(GpItem) + 5) + 12 * o.nres;
+        return o;
+    }
     // work items of about 4096 pairs, fewer while that leaves compute units idle
     g.T = (uint32_t)std::min(4096.0, std::max(512.0, pairs / (4.0 * cus)));
     g.span_bins = std::max<uint32_t>(1, (1u << GP_SPAN_LOG) / g.S);
@@ -205,10 +220,18 @@ static GpTry gp_try(int nvars, const VarParam *vp, int64_t na, int64_t nb, unsig
 // spends hundreds of instructions); a block below four pairs leaves most of
 // its lanes idle.  The bitmap needs some pairs per span to pay for its scan.
 static bool gp_pays(const GpTry &t, const GpCounts &c, int64_t na, int64_t nb, unsigned __int128 box, bool dense,
-                    int way) {
+                    int way, bool f64) {
     const double pairs = (double)na * (double)nb;
     const double gf = (double)c.f[t.g.d - 1], gg = (double)c.g[t.g.d - 1];
     if (pairs < 4096 || gf < 1 || gg < 1) return false;
+    if (f64) {
+        // a wave adds one row of one inner group at a time: a step per outer
+        // term and inner group, which the radix sort's cost per pair buys
+        // from about two columns on; lookups: f's groups for every work item
+        // (non-empty bins: a few dozen per group where the groups form a regular set)
+        const double items = std::min<double>(t.items, 32 * (gf + gg) + pairs / t.g.T);
+        return (double)nb / gg >= 4 && items * gf <= pairs;
+    }
     if ((double)t.items * std::min(gf, gg) > 2 * pairs) return false;
     const double block = pairs / (gf * gg);
     if (dense) return block * t.g.nbins / t.items >= 4;
@@ -340,19 +363,23 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
     for (int q = 0; q < S; q++) {
         DevSeg &d = P.segs[q];
         const bool dense = d.mode == SEG_DENSE;
-        if (d.mode == SEG_EMPTY || ring == RING_F64) continue;
+        if (d.mode == SEG_EMPTY) continue;
         if (dense ? tune_in.tile_cfg >= 0 : tune.combine != -1 && tune.combine != 3) continue;
         for (int way = 1; way <= 2 && !gt[q].ok; way++) {
-            GpTry t = gp_try(nvars, &P.vars[(size_t)q * nvars], d.na, d.nb, box[q], dense, cus, way);
+            GpTry t = gp_try(nvars, &P.vars[(size_t)q * nvars], d.na, d.nb, box[q], dense, cus, way, ring == RING_F64);
             if (!t.ok) continue;
             if (gp_bytes) (*gp_bytes)[q] = std::max((*gp_bytes)[q], t.bytes);
-            if (counts && gp_pays(t, (*counts)[q], d.na, d.nb, box[q], dense, way)) {
+            if (counts && gp_pays(t, (*counts)[q], d.na, d.nb, box[q], dense, way, ring == RING_F64)) {
                 gt[q] = t;
                 const double gf = (double)(*counts)[q].f[t.g.d - 1], gg = (double)(*counts)[q].g[t.g.d - 1];
                 // pairs that an outer group has with the bins of a work item
                 const double bins = dense ? (double)t.g.nbins / (double)t.items : std::max(1.0, std::min<double>(t.g.span_bins, (double)t.g.nbins * t.g.T / ((double)d.na * d.nb)));
                 gt[q].g.rows = (double)d.na * (double)d.nb / (gf * gg) * bins < 32 ? 1 : 0;
                 gt[q].g.swap = (*counts)[q].g[t.g.d - 1] < (*counts)[q].f[t.g.d - 1] ? 1 : 0;
+                if (ring == RING_F64) {
+                    gt[q].g.swap = gt[q].g.rows = 0;  // row-major sums: f's groups are the rows
+                    P.gp_fc = std::max(P.gp_fc, t.g.S <= 1024 ? 1024 : t.g.S <= 2048 ? 2048 : GP_F64_CELLS);
+                }
                 d.mode = dense ? SEG_GRPD : SEG_GRP;
             }
         }

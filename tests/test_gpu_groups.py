@@ -191,3 +191,22 @@ def test_graph_replay_with_other_groups():
         (k, c), = call.results()
         wk, wc, _ = oracle.mul(f, g)
         assert np.array_equal(k, wk) and np.array_equal(c, wc)
+
+
+@pytest.mark.parametrize("cols,rows,groups", [(4, 5, 70), (63, 64, 3), (64, 65, 20), (65, 63, 20), (129, 3, 66), (200, 130, 5),
+                                              (900, 40, 9)])
+def test_f64_rows(cols, rows, groups):
+    # one wave per work item: 63 to 130 rows and columns of a block, more than
+    # 64 outer groups, a key span in each class of cells; row-major sums, bit for bit
+    rng = W.rng_for(cols)
+    f, g = grid(rng, "f64", (groups, rows), 16, step=(1, 2)), grid(rng, "f64", (40, cols), 16, step=(3, 3))
+    takes_groups(f, g, f"FP64 {rows} rows, {cols} columns")
+
+
+def test_f64_denormal_and_cancelled():
+    rng = W.rng_for(21)
+    f, g = grid(rng, "f64", (25, 20), 12), grid(rng, "f64", (25, 30), 12, step=(1, 2))
+    for a, b in ((1e-160, 1e-160), (1e-300, 1e-10), (1e150, 1e150)):
+        takes_groups(W.Poly(f.layout, f.keys, f.coefs * a), W.Poly(g.layout, g.keys, g.coefs * b), f"scaled {a} {b}")
+    ff, gg = (W.Poly(p.layout, p.keys, np.round(2 * p.coefs)) for p in (f, g))
+    takes_groups(ff, gg, "cancelling")
