@@ -5,6 +5,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <chrono>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -136,58 +137,120 @@ int check_args(const pm_layout *L, int64_t count, const pm_cpoly *f, const pm_cp
     return PM_OK;
 }
 
-// Validation + statistics round trip for `count` products: fills `in` and
-// returns the statistics and flags (inside the pinned staging, valid until the
-// next use of `hs`).  `dev` is device memory of at least stats_region_bytes +
-// sizeof(DevSeg)*count.
+// Validation + statistics round trip for `count` products: fills `in`; the
+// rows are in the pinned staging once `st` has run (until the next use of
+// `hs`), for stats_collect.  `dev` is device memory of at least
+// stats_region_bytes + sizeof(DevSeg)*count.
 int stats_roundtrip(HostStage &hs, const pm_layout *L, int64_t count, const pm_cpoly *f, const pm_cpoly *g,
-                    void *dev, hipStream_t st, std::vector<SegInput> &in, const uint64_t **stats,
-                    const uint32_t **flags, bool sync) {
-    const int S = (int)count, nv = (int)L->nvars;
-    const size_t sreg = stats_region_bytes(S, nv);
-    const size_t segb = sizeof(DevSeg) * S;
-    const size_t sb = stats_bytes(S, nv);
-    const size_t up_off = 0, dn_off = (segb + 255) & ~(size_t)255;
-    int rc = hs.reserve(dn_off + sreg);
-    if (rc) return rc;
-    DevSeg *hseg = (DevSeg *)((char *)hs.pin + up_off);
+                    void *dev, hipStream_t st, std::vector<SegInput> &in, bool sync) {
+    const int S = (int)count, nv = (int)L->nvars, nops = 2 * S;
+    int64_t most = 1;
     in.resize(S);
     for (int q = 0; q < S; q++) {
-        DevSeg d = DevSeg();
-        d.fk = f[q].keys;
-        d.fc = (const u64 *)f[q].coefs;
-        d.gk = g[q].keys;
-        d.gc = (const u64 *)g[q].coefs;
-        d.na = f[q].n;
-        d.nb = g[q].n;
-        hseg[q] = d;
-        in[q] = SegInput{d.fk, d.fc, d.gk, d.gc, d.na, d.nb};
+        in[q] = SegInput{f[q].keys, (const u64 *)f[q].coefs, g[q].keys, (const u64 *)g[q].coefs, f[q].n, g[q].n};
+        most = std::max(most, std::max(f[q].n, g[q].n));
     }
-    char *dbase = (char *)dev;
-    hipError_t e = hipMemcpyAsync(dbase + sreg, hseg, segb, hipMemcpyHostToDevice, st);
-    if (e == hipSuccess) e = launch_stats((const DevSeg *)(dbase + sreg), S, nv, (int)L->bits, L->ring, (u64 *)dbase,
-                                          (u32 *)(dbase + ((sb + 255) & ~(size_t)255)), st);
-    char *hstats = (char *)hs.pin + dn_off;
-    if (e == hipSuccess) e = hipMemcpyAsync(hstats, dbase, sreg, hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess && sync) e = hipStreamSynchronize(st);
+    // a few workgroups per large operand, while the operands alone do not fill the device
+    const int parts = hs.fixed ? 1 : (int)std::max<int64_t>(1, std::min<int64_t>((most + ST_TERMS - 1) / ST_TERMS,
+                                                                           ST_MAX_ROWS / nops));
+    const bool by_value = nops <= ST_ARGS;
+    const size_t sreg = stats_region_bytes(S, nv), segb = sizeof(DevSeg) * S;
+    const size_t rowb = (size_t)(2 * nv + 2) * 8 * nops * parts, up = by_value ? 0 : (segb + 255) & ~(size_t)255;
+    int rc = hs.reserve(up + rowb);
+    if (rc) return rc;
+    hipError_t e = hipSuccess;
+    StatOps ops{};
+    const DevSeg *dsegs = nullptr;
+    if (by_value) {
+        for (int o = 0; o < nops; o++) {
+            const pm_cpoly &p = (o & 1) ? g[o >> 1] : f[o >> 1];
+            ops.k[o] = p.keys;
+            ops.c[o] = (const u64 *)p.coefs;
+            ops.n[o] = p.n;
+        }
+    } else {
+        DevSeg *hseg = (DevSeg *)hs.pin;
+        for (int q = 0; q < S; q++) {
+            DevSeg d = DevSeg();
+            d.fk = in[q].fk;
+            d.fc = in[q].fc;
+            d.gk = in[q].gk;
+            d.gc = in[q].gc;
+            d.na = in[q].na;
+            d.nb = in[q].nb;
+            hseg[q] = d;
+        }
+        dsegs = (const DevSeg *)((char *)dev + sreg);
+        e = hipMemcpyAsync((char *)dev + sreg, hseg, segb, hipMemcpyHostToDevice, st);
+    }
+    u64 *rows = (u64 *)((char *)hs.pin + up);
+    // pageable staging: one row per operand fits the statistics region of `dev`
+    u64 *out = hs.fixed ? (u64 *)dev : rows;
+    const int w = 2 * nv + 2, nrows = nops * parts;
+    for (int r = 0; r < nrows; r++) rows[(size_t)r * w + w - 1] = 0;
+    if (e == hipSuccess) e = launch_stats(ops, dsegs, nops, parts, nv, (int)L->bits, L->ring, out, 1, st);
+    if (e == hipSuccess && hs.fixed) e = hipMemcpyAsync(rows, dev, rowb, hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess && sync) {
+        // the rows' last words are polled for a while (a stream
+        // synchronisation takes some 10 us longer to return), then waited for
+        bool all = false;
+        if (!hs.fixed) {
+            const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(200);
+            int r = 0;
+            do {
+                while (r < nrows && __atomic_load_n(&rows[(size_t)r * w + w - 1], __ATOMIC_ACQUIRE) == 1) r++;
+                all = r == nrows;
+            } while (!all && std::chrono::steady_clock::now() < until);
+        }
+        if (!all) e = hipStreamSynchronize(st);
+    }
     if (e != hipSuccess) {
         set_error("validation", e);
         return PM_EDEVICE;
     }
-    *stats = (const uint64_t *)hstats;
-    *flags = (const uint32_t *)(hstats + ((sb + 255) & ~(size_t)255));
+    hs.rows = rows;
+    hs.nops = nops;
+    hs.parts = parts;
+    hs.nvars = nv;
+    hs.bits = (int)L->bits;
     return PM_OK;
+}
+
+void stats_collect(HostStage &hs) {
+    const int nv = hs.nvars, w = 2 * nv + 2;
+    // with fields of at most 32 bits a minimum's upper half is a count
+    const bool counted = hs.bits <= 32;
+    const uint64_t low = counted ? 0xFFFFFFFFull : ~0ull;
+    hs.stats.resize((size_t)hs.nops * 2 * nv);
+    hs.flags.resize(hs.nops);
+    for (int o = 0; o < hs.nops; o++) {
+        uint64_t *mn = hs.stats.data() + (size_t)o * 2 * nv, *mx = mn + nv;
+        uint32_t fl = 0;
+        for (int v = 0; v < nv; v++) {
+            uint64_t a = low, b = 0, n = 0;
+            for (int p = 0; p < hs.parts; p++) {
+                const uint64_t *r = hs.rows + ((size_t)o * hs.parts + p) * w;
+                a = std::min(a, r[v] & low);
+                b = std::max(b, r[nv + v]);
+                n += counted ? r[v] >> 32 : 0;
+            }
+            mn[v] = a | (std::min<uint64_t>(n, 0xFFFFFFFFull) << 32 & ~low);
+            mx[v] = b;
+        }
+        for (int p = 0; p < hs.parts; p++) fl |= (uint32_t)hs.rows[((size_t)o * hs.parts + p) * w + 2 * nv];
+        hs.flags[o] = fl;
+    }
 }
 
 // Validation + statistics round trip and planning for `count` products.
 int stats_and_plan(HostStage &hs, const pm_layout *L, int64_t count, const pm_cpoly *f, const pm_cpoly *g,
                    void *dev, hipStream_t st, const Tuning &tune, Plan &P, int64_t limit) {
     std::vector<SegInput> in;
-    const uint64_t *stats = nullptr;
-    const uint32_t *flags = nullptr;
-    int rc = stats_roundtrip(hs, L, count, f, g, dev, st, in, &stats, &flags);
+    int rc = stats_roundtrip(hs, L, count, f, g, dev, st, in);
     if (rc) return rc;
-    return plan_build((int)L->nvars, (int)L->bits, L->ring, in, stats, flags, tune, P, device_cus(), true, limit);
+    stats_collect(hs);
+    return plan_build((int)L->nvars, (int)L->bits, L->ring, in, hs.stats.data(), hs.flags.data(), tune, P, device_cus(),
+                      true, limit);
 }
 
 // Upload the descriptor block of plan P (output pointers filled) and enqueue
@@ -216,7 +279,10 @@ int upload_descriptors(HostStage &hs, Plan &P, void *ws, hipStream_t st, hipStre
     // the copy runs on `ust` (default: the launch stream); the launch stream
     // then waits for it, so the staging is free once `ust` has run the copy
     if (!ust) ust = st;
-    hipError_t e = hipMemcpyAsync((char *)ws + d0, pin, P.r_desc.bytes, hipMemcpyHostToDevice, ust);
+    const bool by_kernel = !hs.fixed && ust == st && P.r_desc.bytes <= sizeof(DescArg);
+    hipError_t e = by_kernel ? launch_upload((char *)ws + d0, pin, P.r_desc.bytes, st)
+                             : hipMemcpyAsync((char *)ws + d0, pin, P.r_desc.bytes, hipMemcpyHostToDevice, ust);
+    if (e == hipSuccess && by_kernel) return PM_OK;  // the staging is free again
     if (e == hipSuccess) e = hs.fixed ? hipStreamSynchronize(ust) : hipEventRecord(hs.ev, ust);
     if (e == hipSuccess && !hs.fixed && ust != st) e = hipStreamWaitEvent(st, hs.ev, 0);
     if (e != hipSuccess) {
@@ -360,13 +426,12 @@ int pm_mul_batch_drain(const pm_layout *layout, int64_t count, const pm_cpoly *f
     if ((size_t)device_bytes < need0) return PM_ENOMEM;
     // one statistics round trip for all products: bounds and planning inputs
     std::vector<SegInput> in;
-    const uint64_t *st_p = nullptr;
-    const uint32_t *fl_p = nullptr;
-    rc = stats_roundtrip(g_stage, layout, count, f, g, device_buffer, st, in, &st_p, &fl_p);
+    rc = stats_roundtrip(g_stage, layout, count, f, g, device_buffer, st, in);
     if (rc) return rc;
+    stats_collect(g_stage);
     const size_t sw = (size_t)4 * nv;
-    std::vector<uint64_t> stats(st_p, st_p + (size_t)count * sw);
-    std::vector<uint32_t> flags(fl_p, fl_p + (size_t)count * 2);
+    const std::vector<uint64_t> stats = g_stage.stats;
+    const std::vector<uint32_t> flags = g_stage.flags;
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
     const size_t half = ((size_t)device_bytes / 2) & ~(size_t)255;
     // products [a, e) as one wave: their planned workspace, bound-sized device

@@ -21,6 +21,12 @@ struct HostStage {
     bool used = false;
     void *dtmp = nullptr;
     size_t dtmp_cap = 0;
+    // the statistics rows of the last stats_roundtrip (in pin), and the table
+    // that stats_collect makes of them
+    const uint64_t *rows = nullptr;
+    int nops = 0, parts = 1, nvars = 0, bits = 0;
+    std::vector<uint64_t> stats;
+    std::vector<uint32_t> flags;
     ~HostStage();
     int reserve(size_t bytes);
     int device_tmp(size_t bytes, void **out);
@@ -30,8 +36,10 @@ void set_error(const char *what, hipError_t e);
 int device_cus();
 int check_args(const pm_layout *L, int64_t count, const pm_cpoly *f, const pm_cpoly *g, const pm_poly *h);
 int stats_roundtrip(HostStage &hs, const pm_layout *L, int64_t count, const pm_cpoly *f, const pm_cpoly *g,
-                    void *dev, hipStream_t st, std::vector<SegInput> &in, const uint64_t **stats,
-                    const uint32_t **flags, bool sync = true);
+                    void *dev, hipStream_t st, std::vector<SegInput> &in, bool sync = true);
+// The rows of the last stats_roundtrip of `hs`, which has completed, as plan_build's
+// statistics and flags in hs.stats and hs.flags.
+void stats_collect(HostStage &hs);
 int stats_and_plan(HostStage &hs, const pm_layout *L, int64_t count, const pm_cpoly *f, const pm_cpoly *g,
                    void *dev, hipStream_t st, const Tuning &tune, Plan &P, int64_t limit);
 // ust: stream of the descriptor copy (null: st); st waits for it.

@@ -75,16 +75,27 @@ __global__ __launch_bounds__(GPP_T) void k_gp_prep(Ctx C, int nop, u64 *zp, i64 
     // coefficient words: 31 and 30 bits mod p, else 32 and 32
     const u32 csh = C.ring == RING_MODP ? 31 : 32, cmask = C.ring == RING_MODP ? 0x7FFFFFFFu : ~0u;
     u32 ng = 0;
-    for (i64 b = 0; b < n; b += GPP_T * 4) {
-        const i64 i0 = b + (i64)threadIdx.x * 4;
-        u64 k[4], c[4];
+    // the next step's terms are loaded before this one's are scanned
+    u64 nk[4], nc[4], np = 0;
+    auto load = [&](i64 i0) {
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-            const i64 i = i0 + e;
-            k[e] = i < n ? key[i] : 0;
-            c[e] = i < n ? coef[i] : 0;
+            const i64 i = min(i0 + e, n - 1);
+            nk[e] = key[i];
+            nc[e] = coef[i];
         }
-        u64 prev = i0 > 0 && i0 < n ? key[i0 - 1] : 0;
+        np = key[max(min(i0, n) - 1, (i64)0)];
+    };
+    load((i64)threadIdx.x * 4);
+    for (i64 b = 0; b < n; b += GPP_T * 4) {
+        const i64 i0 = b + (i64)threadIdx.x * 4;
+        u64 k[4], c[4], prev = np;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            k[e] = nk[e];
+            c[e] = nc[e];
+        }
+        if (b + GPP_T * 4 < n) load(i0 + GPP_T * 4);
         u32 p[4], lo[4], hd = 0;
 #pragma unroll
         for (int e = 0; e < 4; e++) {
@@ -529,20 +540,6 @@ __device__ inline void gp_cols(const u32 *lut, u32 p, u32 B0, u32 B1, u32 &j0, u
         j0 = gload(lut + (B0 > p ? B0 - p : 0u));
         nc = gload(lut + (B1 - p)) - j0;
     }
-}
-
-// Inclusive sum over the wave: shifts by 1, 2, 4 and 8 within each row of 16
-// lanes, then the sums of row 0 (and 2) to row 1 (and 3), of rows 0-1 to 2-3.
-// (A wave's additions to one LDS counter are served lane by lane, about 550
-// cycles for 64 lanes; the scan takes a few dozen and leaves one addition.)
-__device__ inline u32 wave_scan_dpp(u32 x) {
-    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);
-    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);
-    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);
-    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);
-    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);
-    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);
-    return x;
 }
 
 // List counters, by parity of the listing: wide and narrow pieces, and what is

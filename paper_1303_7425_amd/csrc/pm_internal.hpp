@@ -313,6 +313,20 @@ enum Counter : int {
     CNT_COUNT
 };
 
+// Operands of a statistics launch passed by value (more of them: through
+// descriptors in device memory).
+constexpr int ST_ARGS = 32;
+struct StatOps {
+    const u64 *k[ST_ARGS], *c[ST_ARGS];
+    i64 n[ST_ARGS];
+};
+// A descriptor block passed by value (kernel arguments end at 4 KB).
+struct DescArg {
+    u32 w[960];
+};
+constexpr int ST_TERMS = 2048;       // terms of a statistics workgroup, while there are few operands
+constexpr int ST_MAX_ROWS = 4096;    // rows of a statistics launch, unless its operands alone are more
+
 // Validation flags reported by the statistics kernel.
 enum StatFlag : u32 { ST_UNSORTED = 1, ST_BADBITS = 2, ST_RANGE = 4 };
 

@@ -22,6 +22,8 @@
 // paper (problem statement, Fig. 1, Algorithm 1).  The paper's own GPU kernel
 // builds a per-interval 16-ary tree with atomics (Section 6.3); here the merge
 // and sort step is redesigned for CDNA4 as LDS combine + global radix sort.
+#include <string.h>
+
 #include <type_traits>
 
 #include "pm_internal.hpp"
@@ -29,80 +31,114 @@
 namespace pm {
 
 // ---------------------------------------------------------------------------
-// k_stats: one workgroup per (segment, operand side).  Per-variable min/max of
-// the exponents, strict ascending order, key bits outside the fields, and
-// coefficient range.  out[(q*2+side)*2*nvars + v] = min, [... + nvars + v] = max;
-// with fields of at most 32 bits the upper half of the minimum holds the
-// number of distinct prefixes of variables 0..v (the planner's group counts).
+// k_stats: `parts` workgroups per operand (blockIdx.x; blockIdx.y: the part).
+// Per-variable min/max of the exponents, strict ascending order, key bits
+// outside the fields, and coefficient range, of one stretch of the terms.  Row
+// (operand * parts + part) of out: nvars minima, nvars maxima, flags, tag; with
+// fields of at most 32 bits the upper half of a minimum holds the number of
+// terms whose variables 0..v differ from the term before (summed over the
+// parts: the distinct prefixes, the planner's group counts).
 // One sweep over the terms per group of eight variables, four independent
-// loads in flight per thread (1024 threads: an operand of a few thousand
-// terms takes one or two steps); the checks ride along with the first group.
+// loads in flight per thread; the checks ride along with the first group.
+// It is a chain of latencies for ordinary operands (fields of at most 32 bits
+// are kept in single words, only the layout's variables are worked on, and a
+// workgroup has ST_TERMS terms at most in the usual case): 6188 terms 16 us
+// in one workgroup of 1024 threads, 46376 terms 55 us.  out is pinned host
+// memory where there is some: the rows arrive with the kernel's end instead of
+// through a copy of their own.
 // ---------------------------------------------------------------------------
-constexpr int ST_T = 1024;
+constexpr int ST_T = 256;
 
 // A 64-bit value from another lane through a DPP move of both halves (lanes
 // without a source keep their own value: harmless for min and max).
 template <int CTRL>
-__device__ inline u64 dpp_u64(u64 v) {
+__device__ inline u64 dpp_keep(u64 v) {
     const u32 lo = (u32)__builtin_amdgcn_update_dpp((int)(u32)v, (int)(u32)v, CTRL, 0xF, 0xF, false);
     const u32 hi = (u32)__builtin_amdgcn_update_dpp((int)(u32)(v >> 32), (int)(u32)(v >> 32), CTRL, 0xF, 0xF, false);
     return ((u64)hi << 32) | lo;
 }
+template <int CTRL>
+__device__ inline u32 dpp_keep(u32 v) {
+    return (u32)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xF, 0xF, false);
+}
 
 // Minimum (MAX: maximum) over the wave, valid in lane 63: shifts by 1, 2, 4
 // and 8 within each row of 16 lanes, then row 15 and lane 31 broadcasts.
-template <bool MAX>
-__device__ inline u64 wave_minmax_u64(u64 v) {
-    auto op = [](u64 a, u64 b) { return MAX ? (a > b ? a : b) : (a < b ? a : b); };
-    v = op(v, dpp_u64<0x111>(v));
-    v = op(v, dpp_u64<0x112>(v));
-    v = op(v, dpp_u64<0x114>(v));
-    v = op(v, dpp_u64<0x118>(v));
-    v = op(v, dpp_u64<0x142>(v));
-    v = op(v, dpp_u64<0x143>(v));
+template <bool MAX, typename T>
+__device__ inline T wave_minmax(T v) {
+    auto op = [](T a, T b) { return MAX ? (a > b ? a : b) : (a < b ? a : b); };
+    v = op(v, dpp_keep<0x111>(v));
+    v = op(v, dpp_keep<0x112>(v));
+    v = op(v, dpp_keep<0x114>(v));
+    v = op(v, dpp_keep<0x118>(v));
+    v = op(v, dpp_keep<0x142>(v));
+    v = op(v, dpp_keep<0x143>(v));
     return v;
 }
 
-__global__ __launch_bounds__(ST_T) void k_stats(const DevSeg *segs, int nvars, int bits, int ring, u64 *out,
-                                                     u32 *flags) {
+// Inclusive sum over the wave: shifts by 1, 2, 4 and 8 within each row of 16
+// lanes, then the sums of row 0 (and 2) to row 1 (and 3), of rows 0-1 to 2-3.
+// (A wave's additions to one LDS counter are served lane by lane, about 550
+// cycles for 64 lanes; the scan takes a few dozen and leaves one addition.)
+__device__ inline u32 wave_scan_dpp(u32 x) {
+    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xF, 0xF, false);
+    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xF, 0xF, false);
+    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xF, 0xF, false);
+    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xF, 0xF, false);
+    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xA, 0xF, false);
+    x += (u32)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xC, 0xF, false);
+    return x;
+}
+
+// E: u32 when the fields have at most 32 bits, else u64.
+template <typename E>
+__global__ __launch_bounds__(ST_T) void k_stats(StatOps ops, const DevSeg *segs, int nvars, int bits, int ring, u64 *out, u64 tag) {
     constexpr int G = 8, U = 4, NW = ST_T / 64;
-    const int q = blockIdx.x >> 1, side = blockIdx.x & 1;
-    const DevSeg &s = segs[q];
-    const i64 n = side ? s.nb : s.na;
-    const u64 *k = side ? s.gk : s.fk;
-    const u64 *c = side ? s.gc : s.fc;
-    const u64 mask = bits == 64 ? ~0ull : ((1ull << bits) - 1);
+    const int o = blockIdx.x, parts = gridDim.y, part = blockIdx.y;
+    i64 n;
+    const u64 *k, *c;
+    if (segs) {
+        const DevSeg &s = segs[o >> 1];
+        n = (o & 1) ? s.nb : s.na;
+        k = (o & 1) ? s.gk : s.fk;
+        c = (o & 1) ? s.gc : s.fc;
+    } else {
+        n = ops.n[o];
+        k = ops.k[o];
+        c = ops.c[o];
+    }
+    const i64 a = n * part / parts, b = n * (part + 1) / parts;
+    const E mask = bits == 8 * (int)sizeof(E) ? (E)~(E)0 : (E)(((u64)1 << bits) - 1);
     const int used = nvars * bits;
-    __shared__ u64 s_mn[G][NW], s_mx[G][NW];
-    __shared__ u32 s_hd[G][NW];
-    __shared__ u32 s_flag;
-    if (threadIdx.x == 0) s_flag = 0;
-    __syncthreads();
+    __shared__ E s_mn[G][NW], s_mx[G][NW];
+    __shared__ u32 s_hd[G][NW], s_flag[NW];
+    const u32 lane = lane_id(), w = threadIdx.x >> 6;
     u32 fl = 0;
-    u64 *o = out + (i64)(q * 2 + side) * 2 * nvars;
+    u64 *row = out + (i64)(o * parts + part) * (2 * nvars + 2);
+    auto put = [](u64 *at, u64 v) { __hip_atomic_store(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); };
     for (int v0 = 0; v0 < nvars; v0 += G) {
-        u64 mn[G], mx[G];
+        E mn[G], mx[G];
         u32 sh[G], hd[G];
 #pragma unroll
         for (int u = 0; u < G; u++) {
             hd[u] = 0;
-            mn[u] = ~0ull;
+            mn[u] = ~(E)0;
             mx[u] = 0;
             sh[u] = v0 + u < nvars ? (u32)((nvars - 1 - (v0 + u)) * bits) : 0u;
         }
-        for (i64 i0 = threadIdx.x; i0 < n; i0 += U * ST_T) {
+        for (i64 i0 = a + threadIdx.x; i0 < b; i0 += U * ST_T) {
             u64 kk[U], kp[U], cc[U];
 #pragma unroll
             for (int r = 0; r < U; r++) {
-                const i64 i = i0 + (i64)r * ST_T;
-                kk[r] = i < n ? k[i] : 0;
-                kp[r] = (i > 0 && i < n) ? k[i - 1] : 0;
-                cc[r] = (v0 == 0 && i < n) ? c[i] : 0;
+                const i64 i = min(i0 + (i64)r * ST_T, b - 1);
+                kk[r] = k[i];
+                kp[r] = k[i > 0 ? i - 1 : 0];
+                cc[r] = v0 == 0 ? c[i] : 0;
             }
 #pragma unroll
             for (int r = 0; r < U; r++) {
                 const i64 i = i0 + (i64)r * ST_T;
-                if (i >= n) continue;
+                if (i >= b) continue;
                 if (v0 == 0) {
                     if (used < 64 && (kk[r] >> used) != 0) fl |= ST_BADBITS;
                     if (i > 0 && !(kk[r] > kp[r])) fl |= ST_UNSORTED;
@@ -110,49 +146,75 @@ __global__ __launch_bounds__(ST_T) void k_stats(const DevSeg *segs, int nvars, i
                     if (ring == RING_MODQ && cc[r] >= Q64) fl |= ST_RANGE;
                     if (ring == RING_F64 && ((cc[r] >> 52) & 0x7ff) == 0x7ff) fl |= ST_RANGE;
                 }
+                // (the first term starts a group of every depth)
+                const u64 diff = i > 0 ? kk[r] ^ kp[r] : ~0ull;
 #pragma unroll
                 for (int u = 0; u < G; u++) {
-                    const u64 e = (kk[r] >> sh[u]) & mask;
+                    if (v0 + u >= nvars) break;
+                    const E e = (E)(kk[r] >> sh[u]) & mask;
                     mn[u] = e < mn[u] ? e : mn[u];
                     mx[u] = e > mx[u] ? e : mx[u];
-                    hd[u] += i == 0 || ((kk[r] ^ kp[r]) >> sh[u]) != 0 ? 1u : 0u;
+                    if constexpr (sizeof(E) == 4) hd[u] += (diff >> sh[u]) != 0 ? 1u : 0u;
                 }
             }
         }
 #pragma unroll
         for (int u = 0; u < G; u++) {
-            mn[u] = wave_minmax_u64<false>(mn[u]);
-            mx[u] = wave_minmax_u64<true>(mx[u]);
-            if (bits <= 32) {
-                for (int d = 32; d >= 1; d >>= 1) hd[u] += (u32)__shfl_xor((int)hd[u], d, 64);
-                if (lane_id() == 0) s_hd[u][threadIdx.x >> 6] = hd[u];
+            if (v0 + u >= nvars) break;
+            mn[u] = wave_minmax<false>(mn[u]);
+            mx[u] = wave_minmax<true>(mx[u]);
+            if constexpr (sizeof(E) == 4) hd[u] = wave_scan_dpp(hd[u]);
+            if (lane == 63) {
+                s_mn[u][w] = mn[u];
+                s_mx[u][w] = mx[u];
+                s_hd[u][w] = hd[u];
             }
-            if (lane_id() == 63) {
-                s_mn[u][threadIdx.x >> 6] = mn[u];
-                s_mx[u][threadIdx.x >> 6] = mx[u];
-            }
+        }
+        if (v0 == 0) {
+            const u32 all = (__ballot(fl & 1u) ? 1u : 0u) | (__ballot(fl & 2u) ? 2u : 0u) | (__ballot(fl & 4u) ? 4u : 0u);
+            if (lane == 0) s_flag[w] = all;
         }
         __syncthreads();
         if (threadIdx.x < G && v0 + (int)threadIdx.x < nvars) {
             const int u = threadIdx.x;
-            u64 a = s_mn[u][0], b = s_mx[u][0];
-            for (int w = 1; w < NW; w++) {
-                a = s_mn[u][w] < a ? s_mn[u][w] : a;
-                b = s_mx[u][w] > b ? s_mx[u][w] : b;
+            E lo = s_mn[u][0], hi = s_mx[u][0];
+            u64 h = s_hd[u][0];
+            for (int x = 1; x < NW; x++) {
+                lo = s_mn[u][x] < lo ? s_mn[u][x] : lo;
+                hi = s_mx[u][x] > hi ? s_mx[u][x] : hi;
+                h += s_hd[u][x];
             }
-            if (bits <= 32) {
-                u64 h = 0;
-                for (int w = 0; w < NW; w++) h += s_hd[u][w];
-                a = (a & 0xFFFFFFFFull) | (min(h, (u64)0xFFFFFFFFull) << 32);
-            }
-            o[v0 + u] = a;
-            o[nvars + v0 + u] = b;
+            put(row + v0 + u, sizeof(E) == 4 ? ((u64)lo | (h << 32)) : (u64)lo);
+            put(row + nvars + v0 + u, hi);
         }
+        if (v0 == 0 && threadIdx.x == ST_T - 1) {
+            u32 all = 0;
+            for (int x = 0; x < NW; x++) all |= s_flag[x];
+            put(row + 2 * nvars, all);
+        }
+        // (a fence at system scope would write the whole L2 back, about 40 us
+        // for 432 workgroups; the stores above go past it, so it is enough
+        // that they have arrived)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
     }
-    if (fl) atomicOr(&s_flag, fl);
-    __syncthreads();
-    if (threadIdx.x == 0) flags[q * 2 + side] = s_flag;
+    // the row is complete: a host that polls its last word may read it
+    if (threadIdx.x == 0) put(row + 2 * nvars + 1, tag);
+}
+static_assert(ST_UNSORTED == 1 && ST_BADBITS == 2 && ST_RANGE == 4, "k_stats gathers the flags by bit");
+
+// A small descriptor block passed by value: a copy command costs the stream
+// about 12 us between the kernels before and after it, and a kernel that reads
+// pinned host memory 15 us.
+__global__ __launch_bounds__(256) void k_upload(DescArg blk, u32 *dst, int words) {
+    for (int i = threadIdx.x; i < words; i += 256) dst[i] = blk.w[i];
+}
+
+hipError_t launch_upload(void *dst, const void *src, size_t bytes, hipStream_t st) {
+    DescArg blk;
+    memcpy(blk.w, src, bytes);
+    hipLaunchKernelGGL(k_upload, dim3(1), dim3(256), 0, st, blk, (u32 *)dst, (int)(bytes / 4));
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -1750,10 +1812,13 @@ hipError_t launch_dense_ceiling(int ring, int grid, int tiles, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_stats(const DevSeg *segs, int nseg, int nvars, int bits, int ring, u64 *out, u32 *flags,
-                        hipStream_t st) {
+hipError_t launch_stats(const StatOps &ops, const DevSeg *segs, int nops, int parts, int nvars, int bits, int ring,
+                        u64 *out, u64 tag, hipStream_t st) {
     ProfScope ps("stats", st);
-    hipLaunchKernelGGL(k_stats, dim3(2 * nseg), dim3(ST_T), 0, st, segs, nvars, bits, ring, out, flags);
+    if (bits <= 32)
+        hipLaunchKernelGGL(k_stats<u32>, dim3(nops, parts), dim3(ST_T), 0, st, ops, segs, nvars, bits, ring, out, tag);
+    else
+        hipLaunchKernelGGL(k_stats<u64>, dim3(nops, parts), dim3(ST_T), 0, st, ops, segs, nvars, bits, ring, out, tag);
     return hipGetLastError();
 }
 

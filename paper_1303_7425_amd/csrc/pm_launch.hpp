@@ -7,8 +7,12 @@
 
 namespace pm {
 
-hipError_t launch_stats(const DevSeg *segs, int nseg, int nvars, int bits, int ring, u64 *out, u32 *flags,
-                        hipStream_t st);
+// segs: device descriptors of the operands (null: `ops`); out: nops * parts
+// rows of 2 nvars + 2 words, the last one `tag` once the row is complete.
+hipError_t launch_stats(const StatOps &ops, const DevSeg *segs, int nops, int parts, int nvars, int bits, int ring,
+                        u64 *out, u64 tag, hipStream_t st);
+// `bytes` of host memory (at most sizeof(DescArg)) to the device as a kernel's argument.
+hipError_t launch_upload(void *dst, const void *src, size_t bytes, hipStream_t st);
 // Everything after validation: zero the per-call state, compress keys, tile /
 // expand, radix passes, reduction and dense compaction.  Enqueued on `st`.
 // `part` (optional) enqueues one part only, so that a caller can space the

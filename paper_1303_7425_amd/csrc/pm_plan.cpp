@@ -656,23 +656,30 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
     P.r_stats.bytes = stats_bytes(S, nvars);
     P.r_flags.off = take((size_t)S * 2 * 4);
     P.r_flags.bytes = (size_t)S * 2 * 4;
+    // descriptors side by side: the block of a few products fits a kernel's arguments
+    auto small = [&](size_t bytes) {
+        size_t o = off;
+        off = (off + bytes + 15) & ~(size_t)15;
+        return o;
+    };
     const size_t desc0 = off;
-    P.o_segs = take(sizeof(DevSeg) * S);
-    P.o_vars = take(sizeof(VarParam) * S * nvars);
-    P.o_tile_pre = take(8 * P.tile_pre.size());
-    P.o_tile_seg = take(4 * std::max<size_t>(1, P.tile_seg.size()));
-    P.o_dpart_pre = take(8 * P.dpart_pre.size());
-    P.o_dseg = take(4 * std::max<size_t>(1, P.dseg.size()));
-    P.o_cpre = take(8 * P.cpre.size());
-    P.o_iv_pre = take(8 * P.iv_pre.size());
-    P.o_iv_seg = take(4 * std::max<size_t>(1, P.iv_seg.size()));
-    P.o_bk_tile_pre = take(8 * std::max<size_t>(1, P.bk_tile_pre.size()));
-    P.o_bk_seg = take(4 * std::max<size_t>(1, P.bk_seg.size()));
-    P.o_bk_sb_pre = take(8 * std::max<size_t>(1, P.bk_sb_pre.size()));
+    P.o_segs = small(sizeof(DevSeg) * S);
+    P.o_vars = small(sizeof(VarParam) * S * nvars);
+    P.o_tile_pre = small(8 * P.tile_pre.size());
+    P.o_tile_seg = small(4 * std::max<size_t>(1, P.tile_seg.size()));
+    P.o_dpart_pre = small(8 * P.dpart_pre.size());
+    P.o_dseg = small(4 * std::max<size_t>(1, P.dseg.size()));
+    P.o_cpre = small(8 * P.cpre.size());
+    P.o_iv_pre = small(8 * P.iv_pre.size());
+    P.o_iv_seg = small(4 * std::max<size_t>(1, P.iv_seg.size()));
+    P.o_bk_tile_pre = small(8 * std::max<size_t>(1, P.bk_tile_pre.size()));
+    P.o_bk_seg = small(4 * std::max<size_t>(1, P.bk_seg.size()));
+    P.o_bk_sb_pre = small(8 * std::max<size_t>(1, P.bk_sb_pre.size()));
     if (P.ngp) {
-        P.o_gp_seg = take(4 * P.gp_seg.size());
-        P.o_gp_sb_pre = take(8 * P.gp_sb_pre.size());
+        P.o_gp_seg = small(4 * P.gp_seg.size());
+        P.o_gp_sb_pre = small(8 * P.gp_sb_pre.size());
     }
+    off = align256(off);
     P.r_desc.off = desc0;
     P.r_desc.bytes = off - desc0;
     const size_t zero0 = off;

@@ -119,8 +119,6 @@ struct Validation {
     int64_t off0 = -1, need0 = 0;
     hipEvent_t ev = nullptr;
     std::vector<SegInput> in;
-    const uint64_t *stats = nullptr;
-    const uint32_t *flags = nullptr;
 };
 
 }  // namespace pm
@@ -174,8 +172,9 @@ static void plan_and_launch(pm_server *s, std::vector<hipEvent_t> &free_events) 
     const size_t sw = (size_t)4 * nv;
     int k = (int)v.group.size();
     // the statistics live in the pinned staging, which the upload reuses
-    std::vector<uint64_t> stats(v.stats, v.stats + (size_t)k * sw);
-    std::vector<uint32_t> flags(v.flags, v.flags + (size_t)k * 2);
+    stats_collect(s->stage);
+    std::vector<uint64_t> stats = s->stage.stats;
+    std::vector<uint32_t> flags = s->stage.flags;
     std::vector<SegInput> in = v.in;
     std::vector<Request *> group = v.group;
     {
@@ -398,8 +397,7 @@ static void scheduler(pm_server *s) {
                         g[i] = group[i]->g;
                     }
                     int rc = stats_roundtrip(s->stage, &group[0]->L, k, f.data(), g.data(),
-                                             (char *)s->arena_ptr + off0, s->plan_stream, v.in, &v.stats, &v.flags,
-                                             false);
+                                             (char *)s->arena_ptr + off0, s->plan_stream, v.in, false);
                     if (rc == PM_OK && hipEventRecord(v.ev, s->plan_stream) != hipSuccess) rc = PM_EDEVICE;
                     if (rc != PM_OK) {
                         std::lock_guard<std::mutex> lk(s->mu);

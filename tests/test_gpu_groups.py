@@ -210,3 +210,39 @@ def test_f64_denormal_and_cancelled():
         takes_groups(W.Poly(f.layout, f.keys, f.coefs * a), W.Poly(g.layout, g.keys, g.coefs * b), f"scaled {a} {b}")
     ff, gg = (W.Poly(p.layout, p.keys, np.round(2 * p.coefs)) for p in (f, g))
     takes_groups(ff, gg, "cancelling")
+
+
+@pytest.mark.parametrize("bits,nvars", [(1, 64), (2, 32), (7, 9), (32, 2), (33, 1), (64, 1)])
+@pytest.mark.parametrize("n", [1, 255, 256, 257, 2047, 2049, 9001])
+def test_statistics_in_parts(n, bits, nvars):
+    # the validation's ranges from several workgroups per operand, in one word
+    # and in two per exponent: the bound is the product of the ranges; a fault
+    # in the first, the last or a stretch's first term is seen
+    pm = _pm()
+    rng = W.rng_for(n + bits)
+    width = min(bits * nvars, 62)
+    if n > 1 << (width - 1):
+        return
+    keys = np.zeros(0, np.uint64)
+    while len(keys) < n:
+        keys = np.unique(np.concatenate([keys, rng.integers(0, 1 << (width - 1), n, dtype=np.uint64)]))
+    keys = keys[np.sort(rng.choice(len(keys), n, replace=False))]
+    if bits < 64:  # leave room for the sum in every field
+        top = sum(((1 << (bits - 1)) - 1 if bits > 1 else 0) << (v * bits) for v in range(nvars))
+        keys = np.unique(keys & np.uint64(top & (2**64 - 1)))
+    f = W.Poly(W.Layout(nvars, bits, "i64"), keys, np.ones(len(keys), np.int64))
+    one = W.Poly(f.layout, np.zeros(1, np.uint64), np.ones(1, np.int64))
+    e = [(keys >> np.uint64((nvars - 1 - v) * bits)) & np.uint64((1 << bits) - 1 if bits < 64 else 2**64 - 1) for v in range(nvars)]
+    box = 1
+    for x in e:
+        box *= int(x.max()) - int(x.min()) + 1
+    lay = (nvars, bits, "i64")
+    assert pm.bound(lay, pm.to_device(f), pm.to_device(one))[0] == min(len(keys), box)
+    if len(keys) < 2:
+        return
+    for at in {0, len(keys) - 2, len(keys) // 2, min(2048, len(keys) - 2)}:
+        k = keys.copy()
+        k[at + 1] = k[at]
+        with pytest.raises(pm.PolymulError) as err:
+            pm.bound(lay, pm.to_device(W.Poly(f.layout, k, f.coefs)), pm.to_device(one))
+        assert err.value.code == pm.PM_EUNSORTED
