@@ -18,6 +18,8 @@
 //   k_gp_cut     bins to work items of about gp.T pairs
 //   k_gp_reduce  work items summed in LDS: sparse results to staging
 //                (SEG_GRP), degree-box cells stored directly (SEG_GRPD)
+//   k_gp_list    the same for products of small blocks, whose pairs are listed
+//                in LDS first
 //   k_gp_copy    result offsets, keys decompressed, terms to h
 #pragma once
 
@@ -302,6 +304,7 @@ __global__ __launch_bounds__(BC_T) void k_gp_cut(Ctx C) {
             I.bin_lo = b0 + (u32)((u64)K * e / np[k]);
             I.bin_hi = b0 + (u32)((u64)K * (e + 1) / np[k]);
             I.q = q;
+            I.pre = I.end = 0;
             I.off = 0;
         }
     }
@@ -312,13 +315,20 @@ __global__ __launch_bounds__(BC_T) void k_gp_cut(Ctx C) {
         const u32 b = 4 * t + k;
         if ((st >> k) & 1u) {
             const i64 at = (i64)(s_ibase + it);
-            if (it > 0 && at - 1 < C.gp_ibound) C.gp_item[at - 1].bin_hi = lsb * GP_SB + pv;
+            if (it > 0 && at - 1 < C.gp_ibound) {
+                C.gp_item[at - 1].bin_hi = lsb * GP_SB + pv;
+                C.gp_item[at - 1].end = s_pre[pv];
+            }
             if (at < C.gp_ibound) {
                 GpItem &I = C.gp_item[at];
                 I.bin_lo = lsb * GP_SB + b;
                 I.q = q;
                 I.off = off;
-                if (it + 1 == ni) I.bin_hi = lsb * GP_SB + all;
+                I.pre = s_pre[b];
+                if (it + 1 == ni) {
+                    I.bin_hi = lsb * GP_SB + all;
+                    I.end = tot;
+                }
             }
             it++;
         }
@@ -641,9 +651,9 @@ __device__ inline void gp_sweep(const GpOperand &O, const GpOperand &I, const u3
 
 // The same with a thread per outer term, each walking its own columns: for
 // operands whose groups hold a term or two.
-template <int RING, int MODE>
+template <int RING>
 __device__ inline void gp_rows(const GpOperand &O, const GpOperand &I, const u32 *lut, u32 B0, u32 B1, u32 base,
-                               unsigned char *mem, u32 wbase) {
+                               unsigned char *mem) {
     for (u32 i = threadIdx.x; i < O.n; i += GR_T) {
         const u32x3 a = gp_term(O.t, i * (u32)sizeof(GpTerm));
         u32 j0, nc;
@@ -655,7 +665,7 @@ __device__ inline void gp_rows(const GpOperand &O, const GpOperand &I, const u32
             for (u32 u = 0; u < 4; u++) b[u] = gp_term(I.t, (j0 + c + u) * (u32)sizeof(GpTerm));
 #pragma unroll
             for (u32 u = 0; u < 4; u++)
-                if (c + u < nc) gp_pair<RING, MODE>(mem, a, b[u], b[u].z + ka, wbase, true);
+                if (c + u < nc) gp_pair<RING, GP_DIRECT>(mem, a, b[u], b[u].z + ka, 0u, true);
         }
     }
     __syncthreads();
@@ -712,12 +722,12 @@ __global__ __launch_bounds__(GR_T) __attribute__((amdgpu_waves_per_eu(4))) void 
             const DevSeg &s = C.segs[q];
             const int bq = (int)uniform32(s.gp.bq), so = (int)uniform32(s.gp.swap);
             S = uniform32(s.gp.S);
-            rowmode = uniform32(s.gp.rows);
+            rowmode = BOX ? uniform32(s.gp.rows) : 0u;
             O = gp_operand(C, s, bq, so);
             I = gp_operand(C, s, bq, 1 - so);
             lut = C.gp_lut + uniform64(s.gp.lut);
             if constexpr (BOX) box = C.box + uniform64(s.stage_base);
-            mine = (uniform32(s.gp.K) != 0) == BOX;
+            mine = BOX ? uniform32(s.gp.K) != 0 : uniform32(s.gp.K) == 0 && uniform32(s.gp.rows) == 0;
             qc = q;
             F.rows = 0;
             if (threadIdx.x < O.groups) {
@@ -742,7 +752,7 @@ __global__ __launch_bounds__(GR_T) __attribute__((amdgpu_waves_per_eu(4))) void 
         if (!mine) {
             // another kernel's product
         } else if (BOX || span <= (u32)GP_CELLS) {
-            if (rowmode) gp_rows<RING, GP_DIRECT>(O, I, lut, B0, B1, base, s_mem, 0u);
+            if (BOX && rowmode) gp_rows<RING>(O, I, lut, B0, B1, base, s_mem);
             else gp_sweep<RING, GP_DIRECT>(O, I, lut, B0, B1, base, s_mem, s_list, &s_ctl, lpar, F0, 0u, ahead);
             // a wave's cells are consecutive, a lane takes two at a time
             const u32 cw = (span + GR_NW * 128 - 1) / (GR_NW * 128) * 128;
@@ -814,8 +824,7 @@ __global__ __launch_bounds__(GR_T) __attribute__((amdgpu_waves_per_eu(4))) void 
             u64 *bm = (u64 *)(s_mem + GrLds::BM);
             unsigned short *pre = (unsigned short *)(s_mem + GrLds::PRE);
             auto none = [] {};
-            if (rowmode) gp_rows<RING, GP_MARK>(O, I, lut, B0, B1, base, s_mem, 0u);
-            else gp_sweep<RING, GP_MARK>(O, I, lut, B0, B1, base, s_mem, s_list, &s_ctl, lpar, F0, 0u, ahead);
+            gp_sweep<RING, GP_MARK>(O, I, lut, B0, B1, base, s_mem, s_list, &s_ctl, lpar, F0, 0u, ahead);
             // rank of a word's first key (thread t: words 4t .. 4t + 3)
             u64 wd[4];
             u32 sum = 0, distinct;
@@ -850,8 +859,7 @@ __global__ __launch_bounds__(GR_T) __attribute__((amdgpu_waves_per_eu(4))) void 
                     }
                 }
                 __syncthreads();
-                if (rowmode) gp_rows<RING, GP_RANK>(O, I, lut, B0, B1, base, s_mem, wb);
-                else gp_sweep<RING, GP_RANK>(O, I, lut, B0, B1, base, s_mem, s_list, &s_ctl, lpar, F0, wb, none);
+                gp_sweep<RING, GP_RANK>(O, I, lut, B0, B1, base, s_mem, s_list, &s_ctl, lpar, F0, wb, none);
                 const u32 ncell = min(distinct - wb, (u32)GP_CELLS);
                 const u32 cw = (ncell + GR_T - 1) / GR_T * 64;  // cells of a wave
                 constexpr int CPT = GP_CELLS / GR_T;
@@ -905,6 +913,397 @@ __global__ __launch_bounds__(GR_T) __attribute__((amdgpu_waves_per_eu(4))) void 
         d0 = d1;
         t = t1;
         t1 = round < own ? tb + blockIdx.x + round * G : tb + own * G + (i64)uniform32(s_tn[par]);
+        d1 = item(t1);
+        round++;
+        par ^= 1u;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// k_gp_list: work items of products whose blocks hold few pairs (gp.rows).
+// Such a block leaves most lanes of a wave idle, so the pairs are listed in
+// LDS first (a thread per outer group, cheap steps) and worked off with every
+// lane.  A work item of at most GL_PAIRS pairs whose keys span more than the
+// direct cells is listed once: its pairs' keys and products stay in registers
+// between the marks in the presence bitmap and the accumulation by rank.
+// Others accumulate in direct cells, GL_CELLS keys per round.
+// One workgroup of 1024 threads per compute unit, all of its LDS: larger work
+// items look fewer outer groups up and share the bitmap's scan among more
+// pairs, which is what bounds it (a sixth of the time forms products).  With a
+// thread per outer term walking its columns, twice and more (the way it was),
+// 777 x 12345 random terms in 6 variables took 255 us here, now 151 (2^17 keys
+// per work item: 241, 2^19: 164, then the scan without bank conflicts); a batch
+// of 24 random products up to 217 million pairs 8.1 ms, now 4.8.
+// ---------------------------------------------------------------------------
+constexpr int GL_T = 1024;
+constexpr int GL_NW = GL_T / 64;
+constexpr int GL_E = 10;               // pairs of a thread, at most
+constexpr int GL_CELLS = 15360;        // direct cells
+constexpr int GL_LIST = 3072;          // pairs listed at a time beside direct cells
+constexpr int GL_G = 4;                // outer groups of a thread that stay in registers
+
+// Ranked: the list uint2[P] and later, in its place, the cells; rkey u32[P],
+// the bitmap of 2^sl bits, pre u16[2^sl / 64], with P = gl_pairs(sl).
+// Direct: the cells, the list uint2[GL_LIST].  Behind them the heads, a byte
+// per listed pair, zero between uses.
+struct GlLds {
+    static constexpr int LIST = GL_CELLS * 8;
+    static constexpr int HEAD = LIST + GL_LIST * 8;
+    static constexpr int MEM = HEAD + GL_E * GL_T;
+};
+constexpr int gl_ranked_bytes(u32 sl) { return (int)gl_pairs(sl) * 12 + (1 << (sl - 3)) + (1 << (sl - 5)); }
+static_assert(gl_ranked_bytes(17) <= GlLds::HEAD && gl_ranked_bytes(18) <= GlLds::HEAD && gl_ranked_bytes(19) <= GlLds::HEAD,
+              "one memory for both");
+static_assert(gl_pairs(17) <= GL_E * GL_T && gl_pairs(18) <= GL_E * GL_T && gl_pairs(19) <= GL_E * GL_T, "pairs of a thread");
+
+// The part of a block that a thread has not listed yet: byte offsets of the
+// next pair's terms and of the block's columns, pairs left.
+struct GlBlock {
+    u32 i, j, jlo, jhi, left;
+};
+
+// The list holds the first pair of every row (byte offsets of its two terms),
+// and again the one at every multiple of 64 that the row covers; heads marks
+// these places.  So the 64 pairs of a wave find their rows by a ballot.
+__device__ inline void gl_row(uint2 *list, unsigned char *head, u32 pos, u32 i, u32 j, u32 len) {
+    list[pos] = make_uint2(i, j);
+    head[pos] = 1;
+    for (u32 b = (pos | 63) + 1; b < pos + len; b += 64) {
+        list[b] = make_uint2(i, j + (b - pos) * (u32)sizeof(GpTerm));
+        head[b] = 1;
+    }
+}
+
+// The terms of listed pair pos (a wave's are 64 consecutive ones from a
+// multiple of 64; past the list's end: some term's, within the padding).
+__device__ inline uint2 gl_pair(const uint2 *list, unsigned char *head, u32 pos) {
+    const u64 m = __ballot(head[pos] != 0);
+    head[pos] = 0;
+    const u32 d = m ? (u32)__clzll((long long)(m << (63 - (pos & 63)))) : 0u;
+    uint2 p = list[pos - d];
+    p.y += d * (u32)sizeof(GpTerm);
+    return m ? p : make_uint2(0, 0);
+}
+
+template <int RING>
+__global__ __launch_bounds__(GL_T) void k_gp_list(Ctx C) {
+    constexpr u32 TB = (u32)sizeof(GpTerm);
+    constexpr u64 WRAP = RING == RING_MODP ? 8 : Q64_C;
+    __shared__ __align__(16) unsigned char s_mem[GlLds::MEM];
+    __shared__ u32 s_w[GL_NW], s_n[2], s_more[2], s_tn[2];
+    u64 *acc = (u64 *)s_mem;
+    const u32 tid = threadIdx.x, lane = tid & 63, w = uniform32(tid >> 6);
+    unsigned char *head = s_mem + GlLds::HEAD;
+    for (u32 e = tid; e < (u32)(GL_E * GL_T) / 16; e += GL_T) ((uint4 *)head)[e] = make_uint4(0, 0, 0, 0);
+    if (tid < 2) s_n[tid] = s_more[tid] = 0;
+    __syncthreads();
+    const i64 ntk = (i64)uniform32(C.gp_sbit[C.gp_nsb]), G = gridDim.x;
+    const i64 own = max((i64)2, ntk / G * 3 / 8);  // work items of its own, see k_gp_reduce
+    i64 t = blockIdx.x, t1 = t + G, round = 2;
+    u32 par = 0, lpar = 0;
+    auto item = [&](i64 t) -> GpItem {
+        GpItem it{};
+        if (t < ntk) it = C.gp_item[t];
+        return it;
+    };
+    GpItem d0 = item(t), d1 = item(t1);
+    int qc = -1;
+    u32 S = 1, sl = 17;
+    GpOperand O, I;
+    const u32 *lut = nullptr;
+    u32 gp[GL_G] = {};                 // prefixes of a thread's first groups (~0: no such group)
+    u32 cj[GL_G] = {}, ce[GL_G] = {};  // their columns in the work item: [cj, ce)
+    bool have = false, mine = false;
+    while (t < ntk) {
+        const int q = (int)uniform32((u32)d0.q);
+        const u32 B0 = uniform32(d0.bin_lo), B1 = uniform32(d0.bin_hi), np = uniform32(d0.end - d0.pre);
+        const u64 off = (u64)uniform64((i64)d0.off);
+        if (q != qc) {
+            const DevSeg &s = C.segs[q];
+            const int bq = (int)uniform32(s.gp.bq), so = (int)uniform32(s.gp.swap);
+            S = uniform32(s.gp.S);
+            sl = uniform32(s.gp.rows);
+            O = gp_operand(C, s, bq, so);
+            I = gp_operand(C, s, bq, 1 - so);
+            lut = C.gp_lut + uniform64(s.gp.lut);
+            mine = uniform32(s.gp.K) == 0 && sl != 0;
+            qc = q;
+#pragma unroll
+            for (int k = 0; k < GL_G; k++) {
+                const u32 og = tid + k * GL_T;
+                gp[k] = og < O.groups && mine ? gload(O.pfx + og) : ~0u;
+            }
+            have = false;
+        }
+        auto columns = [&](u32 b0, u32 b1) {
+#pragma unroll
+            for (int k = 0; k < GL_G; k++) {
+                const bool in = gp[k] < b1;  // (else lut[0] twice: none; loads without a branch: all of them under way at once)
+                cj[k] = gload(lut + (in && b0 > gp[k] ? b0 - gp[k] : 0u));
+                ce[k] = gload(lut + (in ? b1 - gp[k] : 0u));
+            }
+        };
+        if (!have) columns(B0, B1);
+        u32 tk = 0;
+        auto ahead = [&]() {  // the next work item's columns, the ticket of the one after it
+            have = t1 < ntk && (int)uniform32((u32)d1.q) == qc;
+            if (have) columns(uniform32(d1.bin_lo), uniform32(d1.bin_hi));
+            if (round >= own && tid == 0) tk = atomicAdd(&C.counters[CNT_GP_LIST], 1u);
+        };
+        // (taken before the stores: later their wait would be one for the stores, too)
+        auto taken = [&]() {
+            asm volatile("" : "+v"(cj[0]), "+v"(cj[1]), "+v"(cj[2]), "+v"(cj[3]), "+v"(ce[0]), "+v"(ce[1]),
+                         "+v"(ce[2]), "+v"(ce[3]), "+v"(tk));
+        };
+        // Lists the work item's pairs, cap at a time, and calls use(count).
+        auto pairs = [&](uint2 *list, u32 cap, auto &&use) {
+            GlBlock B{0, 0, 0, 0, 0};
+            u32 og = tid;
+            int k = 0;
+            while (true) {
+                bool room = true;
+                while (room && __ballot(B.left || og < O.groups)) {
+                    if (!B.left && og < O.groups) {
+                        u32 j0, nc;
+                        if (k < GL_G) {
+                            j0 = k == 0 ? cj[0] : k == 1 ? cj[1] : k == 2 ? cj[2] : cj[3];
+                            nc = (k == 0 ? ce[0] : k == 1 ? ce[1] : k == 2 ? ce[2] : ce[3]) - j0;
+                        } else {
+                            gp_cols(lut, gload(O.pfx + og), B0, B1, j0, nc);
+                        }
+                        if (nc) {
+                            const u32 i0 = gload(O.start + og), rows = gload(O.start + og + 1) - i0;
+                            B.i = i0 * TB;
+                            B.j = B.jlo = j0 * TB;
+                            B.jhi = (j0 + nc) * TB;
+                            B.left = rows * nc;
+                        }
+                        og += GL_T;
+                        k++;
+                    }
+                    const u32 want = min(B.left, cap);
+                    const u32 inc = wave_scan_dpp(want);
+                    const u32 tot = (u32)__builtin_amdgcn_readlane((int)inc, 63);
+                    u32 at = 0;
+                    if (tot && lane == 0) at = atomicAdd(&s_n[lpar], tot);
+                    at = uniform32(at);
+                    room = at + tot <= cap;
+                    at += inc - want;
+                    const u32 take = at < cap ? min(want, cap - at) : 0u;
+                    // long blocks by the whole wave, a lane per row, the others a lane each
+                    const bool lg = take > 128;
+                    for (u64 m = __ballot(lg); m; m &= m - 1) {
+                        const int l = __ffsll((unsigned long long)m) - 1;
+                        const u32 bi = (u32)__builtin_amdgcn_readlane((int)B.i, l);
+                        const u32 jl = (u32)__builtin_amdgcn_readlane((int)B.jlo, l);
+                        const u32 c0 = ((u32)__builtin_amdgcn_readlane((int)B.j, l) - jl) / TB;  // listed before of this row
+                        const u32 nc = ((u32)__builtin_amdgcn_readlane((int)B.jhi, l) - jl) / TB;
+                        const u32 ba = (u32)__builtin_amdgcn_readlane((int)at, l);
+                        const u32 end = c0 + (u32)__builtin_amdgcn_readlane((int)take, l);
+                        const u32 nr = (end + nc - 1) / nc;
+                        for (u32 r = lane; r < nr; r += 64) {
+                            const u32 s0 = max(r * nc, c0), s1 = min(r * nc + nc, end);
+                            gl_row(list, head, ba + s0 - c0, bi + r * TB, jl + (s0 - r * nc) * TB, s1 - s0);
+                        }
+                        if ((int)lane == l) {
+                            const u32 r = end / nc;
+                            B.i = bi + r * TB;
+                            B.j = jl + (end - r * nc) * TB;
+                        }
+                    }
+                    for (u32 e = 0; e < (lg ? 0u : take);) {
+                        const u32 len = min((B.jhi - B.j) / TB, take - e);
+                        gl_row(list, head, at + e, B.i, B.j, len);
+                        e += len;
+                        B.j += len * TB;
+                        if (B.j == B.jhi) {
+                            B.j = B.jlo;
+                            B.i += TB;
+                        }
+                    }
+                    B.left -= take;
+                }
+                if (__ballot(B.left || og < O.groups) && lane == 0) s_more[lpar] = 1;
+                __syncthreads();
+                const u32 n = min(uniform32(s_n[lpar]), cap);
+                const bool more = uniform32(s_more[lpar]) != 0;
+                lpar ^= 1u;
+                if (tid == 0) s_n[lpar] = s_more[lpar] = 0;  // read by everyone before the barrier above
+                use(n);
+                __syncthreads();
+                if (!more) break;
+            }
+        };
+        const u32 base = B0 * S, span = (B1 - B0) * S;
+        u32 done = 0;
+        // Stages the non-zero ones of n cells; last: the work item's last cells.
+        auto emit = [&](u32 n, auto &&key, bool last) {
+            const u32 cw = (n + GL_T - 1) / GL_T * 64;  // cells of a wave
+            const u32 c1 = min(w * cw + cw, n);
+            u32 mine_n = 0;
+            for (u32 c = w * cw; c < c1; c += 256) {
+                u64 y[4];
+#pragma unroll
+                for (u32 e = 0; e < 4; e++) y[e] = acc[min(c + e * 64, c1 - 1) + lane];
+#pragma unroll
+                for (u32 e = 0; e < 4; e++)
+                    mine_n += c + e * 64 + lane < c1 && !ring_is_zero<RING>(ring_cell_final<RING>(y[e])) ? 1u : 0u;
+            }
+            const u32 inc = wave_scan_dpp(mine_n);
+            if (lane == 63) s_w[w] = inc;
+            if (last) ahead();
+            __syncthreads();
+            const u32 sw = s_w[lane & (GL_NW - 1)];
+            const u32 wi = wave_scan_dpp(lane < (u32)GL_NW ? sw : 0u);
+            const u32 tot = (u32)__builtin_amdgcn_readlane((int)wi, 63);
+            u32 at = w ? (u32)__builtin_amdgcn_readlane((int)wi, (int)w - 1) : 0u;
+            taken();
+            u32 *rk = C.gp_rkey + off + done;
+            u64 *rc = C.gp_rcoef + off + done;
+            for (u32 c = w * cw; c < c1; c += 128) {
+                u64 y[2];
+                u32 k[2];
+#pragma unroll
+                for (u32 e = 0; e < 2; e++) {
+                    const u32 x = min(c + e * 64, c1 - 1) + lane;
+                    y[e] = acc[x];
+                    k[e] = key(x);
+                }
+#pragma unroll
+                for (u32 e = 0; e < 2; e++) {
+                    const u64 val = ring_cell_final<RING>(y[e]);
+                    const bool in = c + e * 64 + lane < c1 && !ring_is_zero<RING>(val);
+                    const u64 em = __ballot(in);
+                    if (in) {
+                        rk[at + mbcnt(em)] = k[e];
+                        rc[at + mbcnt(em)] = val;
+                    }
+                    at += (u32)__popcll(em);
+                }
+            }
+            done += tot;
+        };
+        if (!mine) {
+            ahead();  // another kernel's product
+        } else if (np <= gl_pairs(sl) && span > (u32)GL_CELLS) {
+            const u32 P = gl_pairs(sl);
+            u32 *rkey = (u32 *)(s_mem + P * 8);
+            u64 *bm = (u64 *)(s_mem + P * 12);
+            unsigned short *pre = (unsigned short *)(s_mem + P * 12 + (1u << (sl - 3)));
+            for (u32 e = tid; e < 1u << (sl - 7); e += GL_T) ((uint4 *)bm)[e] = make_uint4(0, 0, 0, 0);
+            u32 x[GL_E];  // key, then rank; ~0: no pair
+            u64 v[GL_E];
+            const uint2 *list = (const uint2 *)s_mem;
+            pairs((uint2 *)s_mem, P, [&](u32 n) {
+#pragma unroll
+                for (int e = 0; e < GL_E; e++) x[e] = ~0u;
+#pragma unroll
+                for (int e0 = 0; e0 < GL_E; e0 += GL_E / 2) {
+                    if ((u32)e0 * GL_T >= n) break;
+                    u32x3 a[GL_E / 2], b[GL_E / 2];
+#pragma unroll
+                    for (int e = 0; e < GL_E / 2; e++) {
+                        const uint2 p = gl_pair(list, head, tid + (e0 + e) * GL_T);
+                        a[e] = gp_term(O.t, p.x);
+                        b[e] = gp_term(I.t, p.y);
+                    }
+#pragma unroll
+                    for (int e = 0; e < GL_E / 2; e++) {
+                        if (tid + (e0 + e) * GL_T < n) {
+                            x[e0 + e] = a[e].z + b[e].z - base;
+                            atomicOr((u32 *)bm + (x[e0 + e] >> 5), 1u << (x[e0 + e] & 31));
+                        }
+                        v[e0 + e] = gp_mul<RING>(a[e].x, a[e].y, b[e].x, b[e].y);
+                    }
+                }
+            });
+            // rank of a word's first key (a wave has consecutive words, a lane every 64th of them)
+            u32 distinct;
+            {
+                const u32 nw = 1u << (sl - 16), w0 = w * nw * 64 + lane;
+                u32 cnt[8], sum = 0;
+#pragma unroll
+                for (u32 e = 0; e < 8; e++) {
+                    cnt[e] = 0;
+                    if (e < nw) cnt[e] = (u32)__popcll(bm[w0 + e * 64]);
+                    sum += cnt[e];
+                }
+                const u32 tot = (u32)__builtin_amdgcn_readlane((int)wave_scan_dpp(sum), 63);
+                if (lane == 0) s_w[w] = tot;
+                __syncthreads();
+                const u32 sw = s_w[lane & (GL_NW - 1)];
+                const u32 wi = wave_scan_dpp(lane < (u32)GL_NW ? sw : 0u);
+                distinct = (u32)__builtin_amdgcn_readlane((int)wi, 63);
+                u32 r = w ? (u32)__builtin_amdgcn_readlane((int)wi, (int)w - 1) : 0u;
+#pragma unroll
+                for (u32 e = 0; e < 8; e++) {
+                    if (e >= nw) break;
+                    const u32 inc = wave_scan_dpp(cnt[e]);
+                    pre[w0 + e * 64] = (unsigned short)(r + inc - cnt[e]);
+                    r += (u32)__builtin_amdgcn_readlane((int)inc, 63);
+                }
+            }
+            for (u32 c = tid; c < distinct; c += GL_T) acc[c] = 0;
+            __syncthreads();
+            {
+#pragma unroll
+                for (int e0 = 0; e0 < GL_E; e0 += GL_E / 2) {
+                    if ((u32)e0 * GL_T >= np) break;
+                    u64 old[GL_E / 2];
+#pragma unroll
+                    for (int e = 0; e < GL_E / 2; e++) {
+                        u32 &y = x[e0 + e];
+                        old[e] = 0;
+                        if (y == ~0u) continue;
+                        const u32 key = y;
+                        y = pre[y >> 6] + (u32)__popcll(bm[y >> 6] & ((1ull << (y & 63)) - 1));
+                        rkey[y] = key;
+                        old[e] = atomicAdd((unsigned long long *)acc + y, (unsigned long long)v[e0 + e]);
+                    }
+                    if constexpr (gp_split<RING>()) {
+#pragma unroll
+                        for (int e = 0; e < GL_E / 2; e++)
+                            if (x[e0 + e] != ~0u && old[e] + v[e0 + e] < old[e]) ring_atomic_acc<RING>(acc + x[e0 + e], WRAP);
+                    }
+                }
+            }
+            __syncthreads();
+            emit(distinct, [&](u32 c) { return rkey[c]; }, true);
+        } else {
+            uint2 *list = (uint2 *)(s_mem + GlLds::LIST);
+            const u32 nwin = (span + GL_CELLS - 1) / GL_CELLS, width = (span + nwin - 1) / nwin;
+            for (u32 w0 = 0; w0 < span; w0 += width) {
+                for (u32 c = tid; c < width; c += GL_T) acc[c] = 0;
+                const u32 sub = base + w0;
+                pairs(list, GL_LIST, [&](u32 n) {
+                    u32x3 a[GL_LIST / GL_T], b[GL_LIST / GL_T];
+                    if (!n) return;
+#pragma unroll
+                    for (int e = 0; e < GL_LIST / GL_T; e++) {
+                        const uint2 p = gl_pair(list, head, tid + e * GL_T);
+                        a[e] = gp_term(O.t, p.x);
+                        b[e] = gp_term(I.t, p.y);
+                    }
+#pragma unroll
+                    for (int e = 0; e < GL_LIST / GL_T; e++) {
+                        const u32 x = a[e].z + b[e].z - sub;
+                        const u64 v = gp_mul<RING>(a[e].x, a[e].y, b[e].x, b[e].y);
+                        if (tid + e * GL_T < n && x < width) ring_atomic_acc<RING>(acc + x, v);
+                    }
+                });
+                emit(width, [&](u32 c) { return w0 + c; }, w0 + width >= span);
+                __syncthreads();  // the next round clears the cells
+            }
+        }
+        if (mine && tid == 0) {
+            C.gp_u[t] = done;
+            atomicAdd(&C.gp_usum[t >> GP_USUM_LOG], done);
+        }
+        if (round >= own && tid == 0) s_tn[par] = tk;
+        __syncthreads();
+        d0 = d1;
+        t = t1;
+        t1 = round < own ? blockIdx.x + round * G : own * G + (i64)uniform32(s_tn[par]);
         d1 = item(t1);
         round++;
         par ^= 1u;

@@ -37,6 +37,9 @@ constexpr int GP_SPAN_LOG = 17;        // key span (log2) of the presence bitmap
 constexpr int GP_MAX_S = 61440;        // cells of a bin, at most: a work item then has at most 2^16 keys (gp.T <= 4096 pairs before its last bin)
 constexpr int GP_F64_CELLS = 3840;     // FP64: LDS cells of a wave, at most (five waves per compute unit)
 constexpr int GP_PAD = 1024;           // term slots after the last operand (loads past a block's rows)
+// Listed work items: pairs of one whose keys span up to 2^sl (17 to 19) and are
+// ranked, at most; what the bitmap leaves of the LDS.
+constexpr u32 gl_pairs(u32 sl) { return sl == 17 ? 10240 : sl == 18 ? 8192 : 5120; }
 constexpr int GP_USUM_LOG = 7;         // work items per partial sum of result counts
 
 // An operand term: coefficient, compressed key modulo 2^32, prefix.
@@ -44,10 +47,12 @@ struct GpTerm {
     u32 c0, c1, ck, pfx;
 };
 
-// Work item: bins [bin_lo, bin_hi) of product q, results staged from off.
+// Work item: bins [bin_lo, bin_hi) of product q, results staged from off; SEG_GRP:
+// its pairs are [pre, end) of the super-bin's.
 struct GpItem {
     u32 bin_lo, bin_hi;
     i32 q;
+    u32 pre, end;
     u32 pad;
     u64 off;
 };
@@ -64,7 +69,8 @@ struct GrpSeg {
     u32 K;          // SEG_GRPD: bins of a run (one value of the variables before the last prefix variable)
     u32 csh;        // SEG_GRPD: a run's pairs are counted in units of 2^csh
     u32 bq;         // index among the launch's group products
-    u32 rows;       // 1: a thread per outer term instead of a wave per block
+    u32 rows;       // not 0: small blocks.  SEG_GRP: pairs are listed first, key span (log2) of a work item;
+                    // SEG_GRPD: a thread per outer term
     u32 pad;
     i64 tf, tg;     // offsets of the operands' terms
     i64 lut;        // offset of the prefix table (nbins + 1 entries)
@@ -309,6 +315,7 @@ enum Counter : int {
     CNT_BK_REDUCE,                  // work items of the in-LDS sort and sum
     CNT_GP_CUT,
     CNT_GP_REDUCE,
+    CNT_GP_LIST,
     CNT_GP_BOX,
     CNT_COUNT
 };

@@ -1989,20 +1989,25 @@ static void launch_gp_head(const Plan &P, const Ctx &C, hipStream_t st, int cus,
 
 template <int RING>
 static void launch_gp_sparse(const Plan &P, const Ctx &C, hipStream_t st, int cus) {
-    {
+    if constexpr (RING == RING_F64) {
         ProfScope ps("gp_reduce", st);
-        if constexpr (RING == RING_F64) {
-            // the waves whose cells fit the compute units' LDS
-            auto go = [&](auto k, int fc) {
-                hipLaunchKernelGGL(k, dim3(grid_for(P.gp_ibound, cus * ((160 << 10) / (fc * 8 + 256)))), dim3(64), 0, st, C);
-            };
-            if (P.gp_fc <= 1024) go(k_gp_f64<1024>, 1024);
-            else if (P.gp_fc <= 2048) go(k_gp_f64<2048>, 2048);
-            else go(k_gp_f64<GP_F64_CELLS>, GP_F64_CELLS);
-            return;
-        } else
-        hipLaunchKernelGGL((k_gp_reduce<RING, false>), dim3(grid_for(P.gp_ibound, cus * 2)), dim3(GR_T), 0, st, C, (i64)0,
-                           (i64)1);
+        // the waves whose cells fit the compute units' LDS
+        auto go = [&](auto k, int fc) {
+            hipLaunchKernelGGL(k, dim3(grid_for(P.gp_ibound, cus * ((160 << 10) / (fc * 8 + 256)))), dim3(64), 0, st, C);
+        };
+        if (P.gp_fc <= 1024) go(k_gp_f64<1024>, 1024);
+        else if (P.gp_fc <= 2048) go(k_gp_f64<2048>, 2048);
+        else go(k_gp_f64<GP_F64_CELLS>, GP_F64_CELLS);
+    } else {
+        if (P.ngp_sparse > P.ngp_list) {
+            ProfScope ps("gp_reduce", st);
+            hipLaunchKernelGGL((k_gp_reduce<RING, false>), dim3(grid_for(P.gp_ibound, cus * 2)), dim3(GR_T), 0, st, C,
+                               (i64)0, (i64)1);
+        }
+        if (P.ngp_list) {
+            ProfScope ps("gp_reduce_list", st);
+            hipLaunchKernelGGL((k_gp_list<RING>), dim3(grid_for(P.gp_ibound, cus)), dim3(GL_T), 0, st, C);
+        }
     }
 }
 

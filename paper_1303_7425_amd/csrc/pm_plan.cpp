@@ -208,11 +208,26 @@ static GpTry gp_try(int nvars, const VarParam *vp, int64_t na, int64_t nb, unsig
     // multiple of T (or of a span), a heavy bin and the one after it
     const int64_t span_cross = ((int64_t)g.nbins + g.span_bins - 1) / g.span_bins + g.nsb;
     o.ibound = (int64_t)(pairs / g.T) + span_cross + 2 * g.nsb;
-    if (g.heavy != 0xFFFFFFFFu) o.ibound += 2 * (int64_t)(pairs / g.heavy);
+    o.ibound += 2 * (int64_t)(pairs / std::min<uint32_t>(g.heavy, gl_pairs(19) / 4));  // (also gp_list's)
     o.ibound = std::min<int64_t>(o.ibound, g.nbins) + 1;
     o.items = std::max<int64_t>((int64_t)(pairs / g.T), (g.nbins + g.span_bins - 1) / g.span_bins);
     o.bytes += g.nsb * (4 * GP_SB + 20) + o.ibound * ((int64_t)sizeof(GpItem) + 5) + 12 * o.nres;
     return o;
+}
+
+// Small blocks: their pairs are listed (k_gp_list).  The sparser the product,
+// the wider the key span of a work item.
+static void gp_list(GpTry &t, double pairs, unsigned __int128 box, int cus) {
+    GrpSeg &g = t.g;
+    const double density = pairs / (double)box;
+    uint32_t sl = 17;
+    while (sl < 19 && density * (double)(1u << sl) < gl_pairs(sl) * 2.0 / 3) sl++;
+    g.rows = sl;
+    // a work item has its share of T pairs and at most one bin that is not heavy
+    g.T = (uint32_t)std::min(gl_pairs(sl) * 0.75, std::max(512.0, pairs / (4.0 * cus)));
+    g.heavy = gl_pairs(sl) / 4;
+    g.span_bins = std::max<uint32_t>(1, (1u << sl) / g.S);
+    t.items = std::max<int64_t>((int64_t)(pairs / g.T), (g.nbins + g.span_bins - 1) / g.span_bins);
 }
 
 // Whether the operands' groups make that split pay.  Every work item looks
@@ -235,7 +250,7 @@ static bool gp_pays(const GpTry &t, const GpCounts &c, int64_t na, int64_t nb, u
     if ((double)t.items * std::min(gf, gg) > 2 * pairs) return false;
     const double block = pairs / (gf * gg);
     if (dense) return block * t.g.nbins / t.items >= 4;
-    if (pairs / (double)box * (double)(1 << GP_SPAN_LOG) < 256) return false;
+    if (pairs / (double)box * t.g.span_bins * t.g.S < (t.g.rows ? 512 : 256)) return false;
     return block >= (way == 1 ? 4 : 1.5);
 }
 
@@ -369,15 +384,21 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
             GpTry t = gp_try(nvars, &P.vars[(size_t)q * nvars], d.na, d.nb, box[q], dense, cus, way, ring == RING_F64);
             if (!t.ok) continue;
             if (gp_bytes) (*gp_bytes)[q] = std::max((*gp_bytes)[q], t.bytes);
-            if (counts && gp_pays(t, (*counts)[q], d.na, d.nb, box[q], dense, way, ring == RING_F64)) {
+            if (!counts) continue;
+            const double gf = (double)(*counts)[q].f[t.g.d - 1], gg = (double)(*counts)[q].g[t.g.d - 1];
+            const double pairs = (double)d.na * (double)d.nb;
+            // pairs that an outer group has with the bins of a work item
+            const double bins = dense ? (double)t.g.nbins / (double)t.items
+                                      : std::max(1.0, std::min<double>(t.g.span_bins, (double)t.g.nbins * t.g.T / pairs));
+            if (gf >= 1 && gg >= 1 && pairs / (gf * gg) * bins < 32) {
+                if (dense) t.g.rows = 1;
+                else if (ring != RING_F64) gp_list(t, pairs, box[q], cus);
+            }
+            if (gp_pays(t, (*counts)[q], d.na, d.nb, box[q], dense, way, ring == RING_F64)) {
                 gt[q] = t;
-                const double gf = (double)(*counts)[q].f[t.g.d - 1], gg = (double)(*counts)[q].g[t.g.d - 1];
-                // pairs that an outer group has with the bins of a work item
-                const double bins = dense ? (double)t.g.nbins / (double)t.items : std::max(1.0, std::min<double>(t.g.span_bins, (double)t.g.nbins * t.g.T / ((double)d.na * d.nb)));
-                gt[q].g.rows = (double)d.na * (double)d.nb / (gf * gg) * bins < 32 ? 1 : 0;
-                gt[q].g.swap = (*counts)[q].g[t.g.d - 1] < (*counts)[q].f[t.g.d - 1] ? 1 : 0;
+                gt[q].g.swap = gg < gf ? 1 : 0;
                 if (ring == RING_F64) {
-                    gt[q].g.swap = gt[q].g.rows = 0;  // row-major sums: f's groups are the rows
+                    gt[q].g.swap = 0;  // row-major sums: f's groups are the rows
                     P.gp_fc = std::max(P.gp_fc, t.g.S <= 1024 ? 1024 : t.g.S <= 2048 ? 2048 : GP_F64_CELLS);
                 }
                 d.mode = dense ? SEG_GRPD : SEG_GRP;
@@ -526,6 +547,7 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
                 P.gp_dpairs += (double)d.na * (double)d.nb;
             } else {
                 P.ngp_sparse++;
+                if (t.g.rows) P.ngp_list++;
             }
         }
         if (d.mode == SEG_COMBINE || d.mode == SEG_DENSE) {

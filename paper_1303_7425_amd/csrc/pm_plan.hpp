@@ -87,7 +87,7 @@ struct Plan {
     size_t o_bk_hist = 0, o_bk_wbin = 0, o_bk_sbtot = 0, o_bk_sbwi = 0, o_bk_sbtb = 0, o_bk_sbpre = 0;
     size_t o_bk_tlist = 0, o_bk_tcnt = 0, o_bk_rkey = 0, o_bk_u = 0, o_bk_opre = 0, o_bk_wi = 0, o_bk_fill = 0, o_bk_fatc = 0, o_bk_fbase = 0, o_bk_fatfill = 0, o_bk_stage = 0, o_bk_tile_pre = 0, o_bk_seg = 0, o_bk_sb_pre = 0;
     // prefix groups (SEG_GRP, SEG_GRPD)
-    int ngp = 0, ngp_sparse = 0;
+    int ngp = 0, ngp_sparse = 0, ngp_list = 0;
     std::vector<int32_t> gp_seg;
     std::vector<int64_t> gp_sb_pre;
     int64_t gp_nterm = 0, gp_nlut = 0, gp_nsb = 0, gp_ibound = 0, gp_nres = 0, gp_maxgrp = 0, gp_maxbins = 0;

@@ -95,6 +95,46 @@ def test_one_term_per_group(ring):
     takes_groups(g, f, "random, swapped", "gp_reduce")
 
 
+def scattered(rng, ring, side, groups, terms, last, big=0):
+    """`terms` distinct terms in `groups` prefixes of a side x side square, the
+    last exponent below `last`; `big` more in the middle prefix."""
+    at = rng.choice(side * side, groups, replace=False)
+    pre = np.concatenate([at, rng.choice(at, terms - groups), np.full(big, side * side // 2)])
+    e = np.stack([pre // side, pre % side, rng.integers(0, last, len(pre))], 1)
+    e[0], e[1] = (0, 0, 0), (side - 1, side - 1, last - 1)
+    lay = W.Layout(3, 16, ring)
+    keys = np.unique(W.pack(e, 3, 16))
+    return W.with_random_coefs(W.Poly(lay, keys, np.zeros(len(keys), np.uint64)), rng, ring)
+
+
+# side, groups, terms, last, big: pairs ranked in each key span, direct cells
+# in one and in four rounds, a block of a million pairs, more groups than a
+# workgroup's threads keep, rows longer than a wave
+@pytest.mark.parametrize("side,groups,terms,last,big", [(40, 1300, 2000, 5000, 0), (40, 1400, 3000, 30000, 0),
+                                                        (40, 1300, 2000, 30000, 0), (25, 600, 3000, 7000, 0),
+                                                        (25, 600, 3000, 30000, 0), (40, 1300, 2000, 30000, 1000),
+                                                        (68, 4500, 6000, 2500, 0)])
+@pytest.mark.parametrize("ring", ["modp", "i64", "modq"])
+def test_listed_pairs(ring, side, groups, terms, last, big):
+    if ring != "modp" and groups > 4000:
+        pytest.skip("one ring for the largest")
+    rng = W.rng_for(side + terms + last)
+    f = scattered(rng, ring, side, groups, terms, last, big)
+    g = scattered(rng, ring, side, groups, terms, last, big)
+    takes_groups(f, g, f"side {side} groups {groups} terms {terms} last {last} big {big}", "gp_reduce_list")
+
+
+def test_listed_pairs_that_cancel():
+    # (A - A x)(B + B x) = A B - A B x^2: half of the distinct keys cancel
+    rng = W.rng_for(8)
+    f, g = (scattered(rng, "i64", 40, 1300, 1500, 2000) for _ in "fg")
+    step = np.uint64(4099)
+    f = W.Poly(f.layout, np.concatenate([f.keys, f.keys + step]), np.concatenate([f.coefs, -f.coefs]))
+    g = W.Poly(g.layout, np.concatenate([g.keys, g.keys + step]), np.concatenate([g.coefs, g.coefs]))
+    f, g = (W.Poly(x.layout, x.keys[o], x.coefs[o]) for x, o in ((f, np.argsort(f.keys)), (g, np.argsort(g.keys))))
+    takes_groups(f, g, "cancelling", "gp_reduce_list")
+
+
 def test_many_additions_wrap():
     # p - 1 everywhere: every cell's sum wraps past 2^64 many times
     lay = W.Layout(2, 12, "modp")
