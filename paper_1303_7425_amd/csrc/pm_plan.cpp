@@ -138,7 +138,7 @@ struct GpCounts {
 // rounds of the device, 512 to GP_CELLS); way 2 (sparse): bins that only fit
 // the presence bitmap.  The fewest prefix variables that do: fewer groups,
 // larger blocks.
-static GpTry gp_try(int nvars, const VarParam *vp, int64_t na, int64_t nb, unsigned __int128 box, bool dense, int cus,
+static GpTry gp_try(int nvars, const VarParam *vp, int64_t na, int64_t nb, unsigned __int128 box, bool dense, double cus,
                     int way, bool f64) {
     GpTry o;
     const double pairs = (double)na * (double)nb;
@@ -146,11 +146,11 @@ static GpTry gp_try(int nvars, const VarParam *vp, int64_t na, int64_t nb, unsig
     if (std::min(na, nb) > 65536) return o;  // pairs of one monomial: see gp_split
     if (!dense && (unsigned __int128)na * nb > 0xFFFFFFFFull) return o;
     const int64_t target =
-        (int64_t)std::min<unsigned __int128>(GP_CELLS, std::max<unsigned __int128>(512, box / ((unsigned)cus * 16)));
+        (int64_t)std::min<unsigned __int128>(GP_CELLS, std::max<unsigned __int128>(512, (unsigned __int128)((double)box / (cus * 16))));
     if (f64 && way != 1) return o;
     const uint64_t fit = f64 ? (uint64_t)GP_F64_CELLS : dense ? (way == 1 ? (uint64_t)target / 4 : (uint64_t)GP_CELLS)
                                : (way == 1 ? (uint64_t)GP_CELLS : (uint64_t)GP_MAX_S);
-    const double most_bins = dense ? 2147483648.0 : std::max(16384.0, pairs / 4);
+    const double most_bins = dense ? 2147483648.0 : std::max(way == 1 ? 16384.0 : 65536.0, pairs / 4);
     GrpSeg &g = o.g;
     for (int d = 1; d <= nvars && !o.ok; d++) {
         const VarParam &v = vp[d - 1];
@@ -217,7 +217,7 @@ static GpTry gp_try(int nvars, const VarParam *vp, int64_t na, int64_t nb, unsig
 
 // Small blocks: their pairs are listed (k_gp_list).  The sparser the product,
 // the wider the key span of a work item.
-static void gp_list(GpTry &t, double pairs, unsigned __int128 box, int cus) {
+static void gp_list(GpTry &t, double pairs, unsigned __int128 box, double cus) {
     GrpSeg &g = t.g;
     const double density = pairs / (double)box;
     uint32_t sl = 17;
@@ -247,11 +247,11 @@ static bool gp_pays(const GpTry &t, const GpCounts &c, int64_t na, int64_t nb, u
         const double items = std::min<double>(t.items, 32 * (gf + gg) + pairs / t.g.T);
         return (double)nb / gg >= 4 && items * gf <= pairs;
     }
-    if ((double)t.items * std::min(gf, gg) > 2 * pairs) return false;
+    if ((double)t.items * std::min(gf, gg) > (t.g.rows ? 8 : 2) * pairs) return false;
     const double block = pairs / (gf * gg);
     if (dense) return block * t.g.nbins / t.items >= 4;
-    if (pairs / (double)box * t.g.span_bins * t.g.S < (t.g.rows ? 512 : 256)) return false;
-    return block >= (way == 1 ? 4 : 1.5);
+    if (pairs / (double)box * t.g.span_bins * t.g.S < (t.g.rows ? 24 : 256)) return false;
+    return way == 1 ? block >= 4 : t.g.rows || block >= 1.5;
 }
 
 // counts: null, or the group counts of every product; products that pay then
@@ -375,13 +375,19 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
 
     // prefix groups, where an explicit setting does not ask for another path
     std::vector<GpTry> gt(S);
+    double all_pairs = 0;
+    for (int q = 0; q < S; q++) all_pairs += (double)P.segs[q].na * (double)P.segs[q].nb;
     for (int q = 0; q < S; q++) {
         DevSeg &d = P.segs[q];
         const bool dense = d.mode == SEG_DENSE;
         if (d.mode == SEG_EMPTY) continue;
         if (dense ? tune_in.tile_cfg >= 0 : tune.combine != -1 && tune.combine != 3) continue;
+        // compute units that the product's share of the launch keeps busy (work
+        // items as for the whole chip each made a burst of 14 products of 0.2 to
+        // 4 million pairs spend 780 us in their reductions)
+        const double share = std::max(1.0, cus * ((double)d.na * (double)d.nb / all_pairs));
         for (int way = 1; way <= 2 && !gt[q].ok; way++) {
-            GpTry t = gp_try(nvars, &P.vars[(size_t)q * nvars], d.na, d.nb, box[q], dense, cus, way, ring == RING_F64);
+            GpTry t = gp_try(nvars, &P.vars[(size_t)q * nvars], d.na, d.nb, box[q], dense, share, way, ring == RING_F64);
             if (!t.ok) continue;
             if (gp_bytes) (*gp_bytes)[q] = std::max((*gp_bytes)[q], t.bytes);
             if (!counts) continue;
@@ -392,7 +398,7 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
                                       : std::max(1.0, std::min<double>(t.g.span_bins, (double)t.g.nbins * t.g.T / pairs));
             if (gf >= 1 && gg >= 1 && pairs / (gf * gg) * bins < 32) {
                 if (dense) t.g.rows = 1;
-                else if (ring != RING_F64) gp_list(t, pairs, box[q], cus);
+                else if (ring != RING_F64) gp_list(t, pairs, box[q], share);
             }
             if (gp_pays(t, (*counts)[q], d.na, d.nb, box[q], dense, way, ring == RING_F64)) {
                 gt[q] = t;

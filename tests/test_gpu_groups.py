@@ -108,12 +108,12 @@ def scattered(rng, ring, side, groups, terms, last, big=0):
 
 
 # side, groups, terms, last, big: pairs ranked in each key span, direct cells
-# in one and in four rounds, a block of a million pairs, more groups than a
-# workgroup's threads keep, rows longer than a wave
+# in one and in four rounds, a block of a million pairs, very few pairs per key
+# span, more groups than a workgroup's threads keep, rows longer than a wave
 @pytest.mark.parametrize("side,groups,terms,last,big", [(40, 1300, 2000, 5000, 0), (40, 1400, 3000, 30000, 0),
                                                         (40, 1300, 2000, 30000, 0), (25, 600, 3000, 7000, 0),
                                                         (25, 600, 3000, 30000, 0), (40, 1300, 2000, 30000, 1000),
-                                                        (68, 4500, 6000, 2500, 0)])
+                                                        (40, 300, 320, 30000, 0), (68, 4500, 6000, 2500, 0)])
 @pytest.mark.parametrize("ring", ["modp", "i64", "modq"])
 def test_listed_pairs(ring, side, groups, terms, last, big):
     if ring != "modp" and groups > 4000:
