@@ -172,3 +172,14 @@ def test_z192_rejected_by_batch_entry_points():
     with pytest.raises(pm.PolymulError) as ei:
         pm.mul_batch((3, 10, "z192"), [pm.to_device(f)], [pm.to_device(f)])
     assert ei.value.code == pm.PM_EINVAL
+
+
+@pytest.mark.parametrize("residue", [0, 1 << 64, W.P61, W.Q64])
+def test_z192_lists_that_differ(residue):
+    # a coefficient that is a multiple of one modulus leaves its monomials out
+    # of that list, which must then be merged; none does for residue 0
+    rng = W.rng_for(65)
+    f, g = (W.random_sparse(rng, n, 6, 10, 15, "z192") for n in (700, 400))
+    if residue:
+        f.coefs[3] = [residue & (2**64 - 1), residue >> 64, 0]
+    same_as_oracle(f, g, f"z192 residue {residue}")
