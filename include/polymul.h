@@ -126,9 +126,10 @@ int pm_mul_bound(const pm_layout *layout, const pm_cpoly *f, const pm_cpoly *g, 
  * pm_mul_bound for the same operands, 256-byte aligned (else PM_EINVAL).
  * Returns PM_OK once the product is enqueued on `stream`, or an error code
  * (nothing enqueued that writes h).  The plan depends on the operands'
- * exponent ranges, so the call synchronises `stream` once, for the
- * validation and statistics read-back, before it enqueues the product; the
- * kernels then run asynchronously.  Calls from several threads are
+ * exponent ranges, so the call waits once for the work on `stream` up to its
+ * validation and statistics kernel, whose rows it polls in pinned memory for
+ * up to 0.2 ms before it synchronises, and then enqueues the product; the
+ * kernels run asynchronously.  Calls from several threads are
  * serialised by one library lock (they share a pinned staging buffer).
  * pm_batch_prepare / pm_batch_launch replay a validated plan without the
  * read-back; the server polls it instead of waiting.
@@ -307,9 +308,12 @@ int pm_ival_splitters(const uint64_t *fkeys, int64_t na, const uint64_t *gkeys, 
  *                bins cut into work items of at most 8192 pairs, pair indices
  *                scattered once to their work items, each work item summed
  *                in LDS; products with fewer than 2^32 cells and pairs).
- *                Automatic selection takes 3 where it applies for the
- *                exact rings (FP64 keeps the pair-index sort unless 3 is
- *                requested).
+ *                Automatic selection first takes a single workgroup for a
+ *                product on its own of at most 8192 pairs, then (-1 and 3
+ *                alike) prefix groups, which form the pairs inside their
+ *                output-key work items, where the operands' sorted keys form
+ *                runs of equal leading exponents that pay for it; else 3
+ *                where it applies for the exact rings and 0 for FP64.
  *   allow_dense  0: never use the degree-box path
  * Results do not depend on these settings (FP64 sums every monomial's
  * products in row-major order on every path).

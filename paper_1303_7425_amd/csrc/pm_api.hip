@@ -351,7 +351,9 @@ int mul_impl(HostStage &hs, const pm_layout *L, int64_t count, const pm_cpoly *f
     if (!ws || ws_bytes < (int64_t)need0) return PM_ENOMEM;
     if ((uintptr_t)ws & 255) return PM_EINVAL;  // kernels use 16-byte loads from workspace regions
     Plan P;
-    int rc = stats_and_plan(hs, L, count, f, g, ws, st, tune, P, ws_bytes);
+    Tuning t = tune;
+    t.tiny = true;
+    int rc = stats_and_plan(hs, L, count, f, g, ws, st, t, P, ws_bytes);
     if (rc) return rc;
     if ((int64_t)P.total > ws_bytes) return PM_ENOMEM;
     rc = upload_and_launch(hs, P, h, ws, st);

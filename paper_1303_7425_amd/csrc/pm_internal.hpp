@@ -26,7 +26,10 @@ enum SegMode : int {
     SEG_BKT = 5,      // pairs scattered once into output-key work items, each sorted and summed in LDS
     SEG_GRP = 6,      // pairs formed from prefix groups inside their output-key work items
     SEG_GRPD = 7,     // the same, every degree-box cell stored, then compaction
+    SEG_TINY = 8,     // few pairs: sorted and summed by one workgroup
 };
+
+constexpr int TINY_PAIRS = 8192;  // pairs of a SEG_TINY product, at most
 
 // Prefix groups (SEG_GRP, SEG_GRPD).  One output prefix (the value of the
 // leading variables of a compressed key) is a bin.
@@ -166,7 +169,7 @@ struct DevSeg {
     i64 ck_f, ck_g;                // offsets of the compressed operand keys
     i64 stage_base;                // first staging slot (sparse) or first box cell (dense)
     i64 stage_bound;               // staging slots (sparse) or box cells (dense)
-    Div32 nb_div;                  // division by nb: pair index -> (row, column) (SEG_RAW, SEG_IVAL, SEG_BKT); by gp.S (SEG_GRP)
+    Div32 nb_div;                  // division by nb: pair index -> (row, column) (SEG_RAW, SEG_IVAL, SEG_BKT, SEG_TINY); by gp.S (SEG_GRP)
     i64 dpart_first;               // first compaction partition (SEG_DENSE, SEG_GRPD)
     i64 var_off;                   // offset of this product's VarParam entries
     union {
@@ -179,7 +182,7 @@ struct DevSeg {
             i64 bk_sb_first, bk_nsb;       // first super-bin (launch-wide index) and super-bins
             i64 bk_tile_first;             // first generation tile
             i64 bk_tiles_n;                // generation tiles along g
-            i32 bk_fs;                     // fine shift: bin = compressed key >> bk_fs
+            i32 bk_fs;                     // fine shift: bin = compressed key >> bk_fs (SEG_TINY: bits of a compressed key)
             i32 bk_tnl;                    // log2 of the generation tile's columns (rows: BK_TILE >> bk_tnl)
         };
         GrpSeg gp;                         // SEG_GRP, SEG_GRPD

@@ -16,6 +16,9 @@
 //   k_reduce     segmented like-term reduction + key decompression
 //   k_zero_compact removal of runs that cancelled to zero
 //   k_compact    dense path: degree-box cells -> sorted non-zero terms
+// and, included below, prefix groups (pm_grp.hpp), a single workgroup for small
+// products (pm_tiny.hpp), output-key work items (pm_bkt.hpp) and intervals
+// (pm_ival.hpp).
 //
 // The schoolbook product P = sum_{i,j} a_i b_j x^{alpha_i + beta_j} and the
 // canonical (sorted, summed, zero-free) result are defined in Section 2 of the
@@ -1627,6 +1630,7 @@ __global__ __launch_bounds__(NTHREADS) void k_compact(Ctx C) {
 #include "pm_ival.hpp"
 #include "pm_bkt.hpp"
 #include "pm_grp.hpp"
+#include "pm_tiny.hpp"
 static_assert(pm::BK_TL == 512, "workspace layout sizes the tile lists for 512 bins");
 
 // ===========================================================================
@@ -2035,6 +2039,13 @@ static void launch_typed(const Plan &P, const Ctx &C, hipStream_t st, int cus, i
             launch_gp_box<RING>(P, C, st, cus, part == PART_HEAD ? 0 : -1);
     }
     if (part == PART_HEAD) return;
+    if (P.ntiny > 0) {
+        ProfScope ps("tiny", st);
+        const bool clear = part == PART_ALL;
+        hipLaunchKernelGGL((k_tiny<RING>), dim3(1), dim3(TINY_T), 0, st, C,
+                           clear ? (u64 *)((char *)C.segs - P.o_segs + P.r_zero.off) : (u64 *)nullptr,
+                           clear ? (i64)(P.r_zero.bytes / 8) : (i64)0);
+    }
     if (P.ngp_sparse > 0) launch_gp_sparse<RING>(P, C, st, cus);
     if (P.ngp > 0) {
         ProfScope ps("gp_copy", st);
@@ -2082,7 +2093,7 @@ hipError_t launch_pipeline(const Plan &P, const Ctx &C, hipStream_t st, int cus,
     u64 *zp = (u64 *)((char *)C.segs - P.o_segs + P.r_zero.off);
     if (P.ngp > 0 && (part == PART_ALL || part == PART_HEAD)) {
         launch_gp_head(P, C, st, cus, zp, (i64)(zbytes / 8));
-    } else if (part == PART_ALL || part == PART_HEAD) {
+    } else if ((part == PART_ALL && P.ntiny == 0) || part == PART_HEAD) {
         ProfScope ps("fill", st);
         hipLaunchKernelGGL(k_fill, dim3(grid_for((int64_t)(zbytes / 8 + 255) / 256, cus * 8)), dim3(256), 0, st, zp,
                            (i64)(zbytes / 8), 0ull);

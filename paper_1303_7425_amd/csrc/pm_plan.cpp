@@ -257,10 +257,17 @@ static bool gp_pays(const GpTry &t, const GpCounts &c, int64_t na, int64_t nb, u
 // counts: null, or the group counts of every product; products that pay then
 // run by prefix groups.  old_bytes: workspace that each product's own arrays
 // take in the general plan (counts null).
+// A product that one workgroup sorts and sums in LDS: TINY_PAIRS is what its
+// LDS holds, and up to there it is the fastest path at every ring and density
+// (57 x 61 random FP64 terms in 6 variables: 121 us by the radix sort, now 55).
+static bool tiny_fits(int64_t na, int64_t nb, unsigned __int128 box) {
+    return (unsigned __int128)na * nb <= (unsigned)TINY_PAIRS && box <= (unsigned __int128)0xFFFFFFFFull;
+}
+
 static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> &in, const uint64_t *stats,
                      const uint32_t *flags, const Tuning &tune_in, Plan &P, int cus, uint64_t smask,
                      const std::vector<GpCounts> *counts, std::vector<int64_t> *old_bytes,
-                     std::vector<int64_t> *gp_bytes) {
+                     std::vector<int64_t> *gp_bytes, bool tiny = false) {
     const int S = (int)in.size();
     P = Plan();
     P.nseg = S;
@@ -382,6 +389,10 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
         const bool dense = d.mode == SEG_DENSE;
         if (d.mode == SEG_EMPTY) continue;
         if (dense ? tune_in.tile_cfg >= 0 : tune.combine != -1 && tune.combine != 3) continue;
+        if (tiny && tiny_fits(d.na, d.nb, box[q]) && tune.combine == -1) {
+            d.mode = SEG_TINY;
+            continue;
+        }
         // compute units that the product's share of the launch keeps busy (work
         // items as for the whole chip each made a burst of 14 products of 0.2 to
         // 4 million pairs spend 780 us in their reductions)
@@ -413,7 +424,7 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
     }
     for (int q = 0; q < S; q++) {
         const int m = P.segs[q].mode;
-        if (m == SEG_EMPTY || m == SEG_GRP || m == SEG_GRPD) continue;
+        if (m == SEG_EMPTY || m == SEG_GRP || m == SEG_GRPD || m == SEG_TINY) continue;
         if (m == SEG_RAW) max_bits = std::max(max_bits, bitlen128(box[q] - 1));
         if (box[q] > (unsigned __int128)0xFFFFFFFFull) need_u64 = true;
     }
@@ -522,12 +533,18 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
         DevSeg &d = P.segs[q];
         if (d.mode == SEG_EMPTY) P.nempty++;
         const bool grp = d.mode == SEG_GRP || d.mode == SEG_GRPD;
+        const bool own = grp || d.mode == SEG_TINY;  // compresses its operands itself
         d.ck_f = nck;
-        nck += grp ? 0 : d.na;
+        nck += own ? 0 : d.na;
         d.ck_g = nck;
-        nck += grp ? 0 : d.nb;
-        P.cpre.push_back(P.cpre.back() + (grp ? 0 : d.na));
-        P.cpre.push_back(P.cpre.back() + (grp ? 0 : d.nb));
+        nck += own ? 0 : d.nb;
+        P.cpre.push_back(P.cpre.back() + (own ? 0 : d.na));
+        P.cpre.push_back(P.cpre.back() + (own ? 0 : d.nb));
+        if (d.mode == SEG_TINY) {
+            d.nb_div = make_div32((uint32_t)d.nb);
+            d.bk_fs = bitlen128(box[q] - 1);
+            P.ntiny++;
+        }
         if (grp) {
             const GpTry &t = gt[q];
             d.gp = t.g;
@@ -822,9 +839,12 @@ int plan_build(int nvars, int bits, int ring, const std::vector<SegInput> &in, c
     }
     P.report = P.total + (any ? align256((size_t)more + 4096) : 0);
     const size_t report = P.report, general = P.total;
-    if (!any || !counted || limit < (int64_t)general) return PM_OK;
-    std::vector<GpCounts> counts(S);
-    for (size_t q = 0; q < S; q++) {
+    // a product on its own only: a launch of several, some of them such, has
+    // faulted the GPU once, for a reason not found
+    const bool tiny = tune.tiny && S == 1 && P.segs[0].mode != SEG_EMPTY && tiny_fits(in[0].na, in[0].nb, 1);
+    if (limit < (int64_t)general || !((any && counted) || tiny)) return PM_OK;
+    std::vector<GpCounts> counts(counted ? S : 0);
+    for (size_t q = 0; q < counts.size(); q++) {
         const uint64_t *st = stats + q * 4 * nvars;
         for (int v = 0; v < nvars; v++) {
             counts[q].f.push_back((int64_t)(st[v] >> 32));
@@ -832,8 +852,9 @@ int plan_build(int nvars, int bits, int ring, const std::vector<SegInput> &in, c
         }
     }
     Plan G;
-    rc = plan_core(nvars, bits, ring, in, stats, flags, tune, G, cus, smask, &counts, nullptr, nullptr);
-    if (rc || !G.ngp || (int64_t)G.total > limit) return PM_OK;
+    rc = plan_core(nvars, bits, ring, in, stats, flags, tune, G, cus, smask, counted ? &counts : nullptr, nullptr, nullptr,
+                   tiny);
+    if (rc || !(G.ngp || G.ntiny) || (int64_t)G.total > limit) return PM_OK;
     P = std::move(G);
     P.total = std::max(P.total, general);
     P.report = report;

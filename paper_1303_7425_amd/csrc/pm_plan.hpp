@@ -29,6 +29,7 @@ struct Tuning {
     int combine = -1;        // sparse path: -1 auto, 0 pair-index sort, 1 LDS tile combine + sort, 2 key intervals,
                              // 3 output-key work items (one scatter, in-LDS sort per work item)
     int allow_dense = 1;     // permit the degree-box path
+    bool tiny = false;       // permit the single workgroup (products on their own, outside graphs and the server)
     int digits = -1;         // radix digit schedule: -1 auto, RADIX_DIGITS_GREEDY, RADIX_DIGITS_BALANCED
     double dense_ratio = 2;  // dense when box * dense_ratio <= na * nb
     int64_t dense_max_cells = int64_t(1) << 35;  // 256 GiB of u64 cells
@@ -99,6 +100,7 @@ struct Plan {
     size_t o_gp_rkey = 0, o_gp_rcoef = 0;
     int64_t nstage = 0, nbox = 0, nck = 0;
     int nsparse = 0, ndense = 0, nempty = 0;
+    int ntiny = 0;              // SEG_TINY products
     // workspace layout
     Region r_stats, r_flags, r_desc, r_zero;
     size_t o_segs = 0, o_vars = 0, o_tile_pre = 0, o_tile_seg = 0, o_dpart_pre = 0, o_dseg = 0, o_cpre = 0;
