@@ -22,7 +22,7 @@ HBM_PEAK_GBS = 8000.0
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "sparse5_n12_modp_hbm_traffic.json")
 
 
-KERNEL_SOURCES = ["pm_kernels.hip", "pm_bkt.hpp", "pm_ival.hpp", "pm_internal.hpp", "pm_plan.cpp", "pm_plan.hpp"]
+KERNEL_SOURCES = ["pm_kernels.hip", "pm_grp.hpp", "pm_tiny.hpp", "pm_bkt.hpp", "pm_ival.hpp", "pm_internal.hpp", "pm_plan.cpp", "pm_plan.hpp"]
 
 
 def kernel_source_hash():
@@ -63,6 +63,16 @@ def measured_step_traffic():
 
 # rocprofv3 kernel names -> the labels used in the summaries
 KERNEL_LABELS = [
+    ("k_gp_prep", "gp_prep (compressed terms, groups)"),
+    ("k_gp_lut", "gp_lut (prefix table, pairs per bin)"),
+    ("k_gp_cut", "gp_cut (bins to work items)"),
+    ("k_gp_coarse", "gp_coarse (pairs per run of bins)"),
+    ("k_gp_reduce<", "gp_reduce (pairs formed and summed in LDS)"),
+    ("k_gp_list<", "gp_list (pairs listed and summed in LDS)"),
+    ("k_gp_f64<", "gp_f64 (rows summed in LDS)"),
+    ("k_gp_copy", "gp_copy (result placement)"),
+    ("k_tiny<", "tiny (one workgroup per product)"),
+    ("k_upload", "upload (descriptors)"),
     ("k_bk_count", "bk_count (fine-bin counts)"),
     ("k_bk_cut", "bk_cut (greedy cut into work items)"),
     ("k_bk_scan", "bk_scan"),
@@ -130,7 +140,7 @@ def traffic_summary(fetch_csv, write_csv, out_path=None, workload="sparse 5-var 
                       "write_bytes": sum(wr[name]) / len(wr[name]) * write_scale, "launches": len(vs)}
     # products in the profiled run: launches of a kernel that runs once per
     # product (the statistics kernel also runs for the bound query)
-    once = ("bk_reduce (per-work-item LDS sum)", "zero_compact", "compact")
+    once = ("gp_copy (result placement)", "bk_reduce (per-work-item LDS sum)", "zero_compact", "compact")
     nsteps = steps or next((per[k]["launches"] for k in once if k in per), None)
     out = {"kernel_source_sha256_16": kernel_source_hash(),
            "workload": workload, "fetch_scale": fetch_scale, "write_scale": write_scale,
@@ -664,7 +674,13 @@ def main():
     dom_ms, dom_n = prof[dom]
     dom_avg_ms = dom_ms / max(dom_n, 1)
     pair_item = 8  # staged (compressed key, pair index), two u32
-    if dom == "bk_reduce":
+    if dom in ("gp_reduce", "gp_reduce_list", "gp_box"):
+        # writes each result term's key inside its work item (u32) and
+        # coefficient (u64); the operands' terms (16 bytes) come from cache
+        dom_bytes = n_out * 12 + (len(f) + len(g)) * 16
+        dom_kernel = "k_gp_reduce (pairs formed and summed in LDS)" if args.ring == "modp" else "k_gp_f64 (rows summed in LDS)"
+        dom_label = dom_kernel.replace("k_gp", "gp", 1)
+    elif dom == "bk_reduce":
         # reads every staged pair once, writes each result term's key (u32)
         # and coefficient (u64); operand coefficients come from cache
         dom_bytes = products * pair_item + n_out * 12 + (len(f) + len(g)) * 8
