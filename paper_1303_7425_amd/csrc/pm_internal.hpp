@@ -193,6 +193,9 @@ struct DevSeg {
     i64 cap;
     i32 mode;
     i32 bk_span_bins;              // SEG_BKT: most fine bins per work item (0: no limit)
+    // 264 bytes: indexed with 256, the address arithmetic of k_tile spills scalar registers
+    // (dense n = 40 mod p 124 ms, with 256 bytes 130)
+    i64 pad;
 };
 
 // Values produced on the device during a call.
