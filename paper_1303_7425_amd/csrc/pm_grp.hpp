@@ -209,7 +209,8 @@ __global__ __launch_bounds__(256) void k_gp_coarse(Ctx C) {
 // key order: their places and their staging offsets (at most min(pairs, S)
 // results per bin) are prefix sums over the super-bins, by a look-back.
 // SEG_GRPD: the counted bins are runs of K bins; a run is cut into work items
-// of equal width, as many as its pairs ask for and its cells need.
+// of equal width to a bin, as many as its pairs ask for and its cells need
+// (gp_run_items).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(BC_T) void k_gp_cut(Ctx C) {
     __shared__ u32 s_pre[GP_SB + 1];
@@ -268,7 +269,7 @@ __global__ __launch_bounds__(BC_T) void k_gp_cut(Ctx C) {
         np[k] = 0;
         const u32 b = 4 * t + k;
         if (K && (u64)(lsb * GP_SB + b) * K < s.gp.nbins)
-            np[k] = max((u32)(((u64)K * S + GP_CELLS - 1) / GP_CELLS), min(K, h[k] / T + 1));
+            np[k] = gp_run_items(K, S, h[k] / T + 1);
         if (K) nsum += np[k];
         if (K || !h[k]) continue;
         bool start = pv == 0;
@@ -301,8 +302,8 @@ __global__ __launch_bounds__(BC_T) void k_gp_cut(Ctx C) {
             const i64 at = (i64)(s_ibase + it++);
             if (at >= C.gp_ibound) break;
             GpItem &I = C.gp_item[at];
-            I.bin_lo = b0 + (u32)((u64)K * e / np[k]);
-            I.bin_hi = b0 + (u32)((u64)K * (e + 1) / np[k]);
+            I.bin_lo = b0 + gp_run_bin(K, np[k], e);
+            I.bin_hi = b0 + gp_run_bin(K, np[k], e + 1);
             I.q = q;
             I.pre = I.end = 0;
             I.off = 0;

@@ -60,6 +60,16 @@ struct GpItem {
     u64 off;
 };
 
+// SEG_GRPD: how a run of K bins of S cells (S <= GP_CELLS) is cut into work
+// items: at least so many that the widest one, of ceil(K / items) whole bins,
+// fits the LDS cells, and otherwise as many as its pairs ask for (`asked`).
+// Work item e has the run's bins [K e / items, K (e + 1) / items).
+__host__ __device__ inline u32 gp_run_items(u32 K, u32 S, u32 asked) {
+    const u32 bins = (u32)GP_CELLS / S, least = (K + bins - 1) / bins;
+    return asked < least ? least : asked < K ? asked : K;
+}
+__host__ __device__ inline u32 gp_run_bin(u32 K, u32 items, u32 e) { return (u32)((u64)K * e / items); }
+
 // Plan of one such product.
 struct GrpSeg {
     u32 S;          // cells of a bin (product of the ranges of variables d and up)

@@ -172,7 +172,7 @@ static GpTry gp_try(int nvars, const VarParam *vp, int64_t na, int64_t nb, unsig
         // runs of K bins, cut into work items of about 1/12 of a workgroup's
         // share (512 workgroups), at least 2048 pairs
         g.K = (uint32_t)vp[g.d - 1].range;
-        const int64_t runs = g.nbins / g.K, least = ((int64_t)g.K * g.S + GP_CELLS - 1) / GP_CELLS;
+        const int64_t runs = g.nbins / g.K, least = gp_run_items(g.K, g.S, 0);
         const double t = std::max(2048.0, pairs / (24.0 * cus));
         while (pairs / (double)(1ull << g.csh) + 1e6 > 4e9) g.csh++;
         g.T = (uint32_t)std::max(1.0, t / (double)(1ull << g.csh));

@@ -286,3 +286,63 @@ def test_statistics_in_parts(n, bits, nvars):
         with pytest.raises(pm.PolymulError) as err:
             pm.bound(lay, pm.to_device(W.Poly(f.layout, k, f.coefs)), pm.to_device(one))
         assert err.value.code == pm.PM_EUNSORTED
+
+
+def dirty(layout, f, g):
+    """A workspace of the recommended size, filled with non-zero words."""
+    pm = _pm()
+    ws = pm.Workspace()
+    ws.get(pm.bound(layout, f, g)[1]).fill_(0x5B)
+    return ws
+
+
+@pytest.mark.parametrize("ring", ["modp", "i64", "modq"])
+def test_box_runs_that_do_not_divide_evenly(ring):
+    # a run of 9 bins of 899 cells: four bins fit a work item, five do not; the
+    # runs at the box's ends have few pairs.  Every box cell is stored.
+    from test_gpu_parity import gpu_mul, assert_same
+    import oracle
+    pm = _pm()
+    rng = W.rng_for(3)
+    e = [(x, y, z) for x in range(911) for y in range(5) for z in rng.integers(0, 450, 2)] + [(0, 0, 0), (910, 4, 449)]
+    keys = np.unique(W.pack(np.array(e), 3, 16))
+    f, g = (W.with_random_coefs(W.Poly(W.Layout(3, 16, ring), keys, np.zeros(len(keys), np.uint64)), rng, ring) for _ in "fg")
+    ws = dirty((3, 16, ring), pm.to_device(f), pm.to_device(g))
+    pm.profile_enable(True)
+    got = gpu_mul(f, g, ws)
+    assert "gp_box" in pm.profile_read()
+    pm.profile_enable(False)
+    assert_same(got, oracle.mul(f, g), ring, "runs of 9 x 899 cells")
+
+
+@pytest.mark.parametrize("ring", ["modp", "i64", "modq"])
+@pytest.mark.parametrize("nvars,n", [(3, 71), (5, 13), (5, 14)])
+def test_powers_whose_runs_do_not_divide_evenly(ring, nvars, n):
+    # (1 + x + y + ...)^n squared is its power 2n: multinomial coefficients,
+    # modulo 2^61 - 1, 2^64 - 59 and 2^64 (none of them vanishes)
+    from math import factorial
+    pm = _pm()
+    mod = {"modp": W.P61, "modq": W.Q64, "i64": 1 << 64}[ring]
+
+    def power(m):
+        rows = [()]
+        for _ in range(nvars):
+            rows = [r + (x,) for r in rows for x in range(m - sum(r) + 1)]
+        fact = [factorial(i) for i in range(m + 1)]
+        c = []
+        for r in rows:
+            d = fact[m - sum(r)]
+            for x in r:
+                d *= fact[x]
+            c.append(fact[m] // d % mod)
+        keys = W.pack(np.array(rows), nvars, 8)
+        assert np.all(keys[1:] > keys[:-1])
+        c = np.array(c, np.uint64)
+        return W.Poly(W.Layout(nvars, 8, ring), keys, c.view(np.int64) if ring == "i64" else c)
+
+    f, want = power(n), power(2 * n)
+    df = pm.to_device(f)
+    h = pm.mul((nvars, 8, ring), df, df, workspace=dirty((nvars, 8, ring), df, df))
+    assert pm.last_call_status() == 0
+    k, c = h.numpy()
+    assert np.array_equal(k, want.keys) and np.array_equal(c.view(np.uint64), want.coefs.view(np.uint64))

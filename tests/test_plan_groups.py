@@ -1,0 +1,77 @@
+"""The planner's choices for products with prefix groups, on the CPU: the
+planner is compiled for the host and asked for its plans."""
+import json
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_1303_7425_amd import build as B
+from paper_1303_7425_amd import workloads as W
+
+RINGS = {"modp": 0, "f64": 1, "i64": 2, "modq": 3}
+EMPTY, COMBINE, RAW, DENSE, IVAL, BKT, GRP, GRPD, TINY = range(9)
+
+
+@pytest.fixture(scope="module")
+def report(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("plan") / "plan_report")
+    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "plan_report.cpp")
+    subprocess.check_call([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-x", "hip", "--offload-host-only", "-O2", "-std=c++17",
+                           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-I", B.CSRC, src,
+                           os.path.join(B.CSRC, "pm_plan.cpp"), "-o", exe])
+
+    def run(*products):
+        got = subprocess.run([exe, "plan"], input="\n".join(products), capture_output=True, text=True, check=True).stdout
+        return [json.loads(ln) for ln in got.splitlines()]
+    run.exe = exe
+    return run
+
+
+def line(f, g, ring, tile_cfg=-1, combine=-1, tiny=0):
+    """A product's sizes, ranges and group counts as plan_report reads them."""
+    nv, bits = f.layout.nvars, f.layout.bits
+    cols = []
+    for p in (f, g):
+        e = W.unpack(p.keys, nv, bits)
+        diff = p.keys[1:] ^ p.keys[:-1]
+        cnt = [1 + int(np.count_nonzero(diff >> np.uint64((nv - 1 - v) * bits))) for v in range(nv)]
+        cols.append((e.min(0), e.max(0), cnt))
+    (fl, fh, fc), (gl, gh, gc) = cols
+    per = " ".join(f"{fl[v]} {fh[v]} {gl[v]} {gh[v]} {fc[v]} {gc[v]}" for v in range(nv))
+    return f"{nv} {bits} {RINGS[ring]} {len(f)} {len(g)} {tile_cfg} {combine} {tiny} {per}"
+
+
+def simplex(nvars, n, bits):
+    """All monomials of degree at most n, coefficients one."""
+    rows = [()]
+    for _ in range(nvars):
+        rows = [r + (x,) for r in rows for x in range(n - sum(r) + 1)]
+    e = np.array(rows)
+    return W.Poly(W.Layout(nvars, bits, "modp"), np.sort(W.pack(e, nvars, bits)), np.ones(len(e), np.uint64))
+
+
+def ragged_box(bits=16):
+    """Exponents 0..1000 x 0..4 x 0..14 x 0..14, eight terms per prefix."""
+    rng = W.rng_for(3)
+    e = [(x, y, z, t) for x in range(1001) for y in range(5) for z, t in rng.integers(0, 15, (8, 2))]
+    e += [(0, 0, 0, 0), (1000, 4, 14, 14)]
+    keys = np.unique(W.pack(np.array(e), 4, bits))
+    return W.Poly(W.Layout(4, bits, "modp"), keys, np.ones(len(keys), np.uint64))
+
+
+def test_cut_of_a_run_tiles_it_and_fits_the_cells(report):
+    got = subprocess.run([report.exe, "runs"], capture_output=True, text=True)
+    assert got.returncode == 0, got.stdout
+
+
+# degree boxes whose runs do not divide into whole bins of cells: with as many
+# work items as cells ask for, the widest one had 4147, 4205, 4374 and 4205
+@pytest.mark.parametrize("ring", ["modp", "i64", "modq"])
+def test_boxes_whose_runs_do_not_divide_evenly(report, ring):
+    for p in (simplex(3, 71, 8), ragged_box(), simplex(5, 13, 8), simplex(5, 14, 8), simplex(3, 70, 8), simplex(4, 30, 8)):
+        (r,) = report(line(p, p, ring))
+        assert r["mode"] == GRPD
+        assert -(-r["K"] // r["least"]) * r["S"] <= r["cells"]
+        assert r["ibound"] >= r["nbins"] // r["K"] * r["least"]
