@@ -308,12 +308,12 @@ int pm_ival_splitters(const uint64_t *fkeys, int64_t na, const uint64_t *gkeys, 
  *                bins cut into work items of at most 8192 pairs, pair indices
  *                scattered once to their work items, each work item summed
  *                in LDS; products with fewer than 2^32 cells and pairs).
- *                Automatic selection first takes a single workgroup for a
- *                product on its own of at most 8192 pairs, then (-1 and 3
- *                alike) prefix groups, which form the pairs inside their
- *                output-key work items, where the operands' sorted keys form
- *                runs of equal leading exponents that pay for it; else 3
- *                where it applies for the exact rings and 0 for FP64.
+ *                0 to 3 run what they name wherever it applies.  Automatic
+ *                selection first takes a single workgroup for a product on its
+ *                own of at most 8192 pairs, then prefix groups, which form the
+ *                pairs inside their output-key work items, where the operands'
+ *                sorted keys form runs of equal leading exponents that pay for
+ *                it; else 3 where it applies for the exact rings and 0 for FP64.
  *   allow_dense  0: never use the degree-box path
  * Results do not depend on these settings (FP64 sums every monomial's
  * products in row-major order on every path).

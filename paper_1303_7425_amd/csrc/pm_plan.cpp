@@ -388,7 +388,8 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
         DevSeg &d = P.segs[q];
         const bool dense = d.mode == SEG_DENSE;
         if (d.mode == SEG_EMPTY) continue;
-        if (dense ? tune_in.tile_cfg >= 0 : tune.combine != -1 && tune.combine != 3) continue;
+        // (an explicit tile shape or sparse mode is what runs; a remembered mode 3 is not explicit)
+        if (dense ? tune_in.tile_cfg >= 0 : tune_in.combine != -1 || (tune.combine != -1 && tune.combine != 3)) continue;
         if (tiny && tiny_fits(d.na, d.nb, box[q]) && tune.combine == -1) {
             d.mode = SEG_TINY;
             continue;

@@ -83,3 +83,15 @@ def test_workitems_cancellation_and_empty():
     check(f, g, "work items, cancellation")
     e = W.Poly(lay, np.zeros(0, np.uint64), np.zeros(0, np.uint64))
     check(f, e, "work items, empty operand")
+
+
+@pytest.mark.parametrize("ring", ["modp", "f64", "i64"])
+def test_requested_work_items_are_what_runs(ring):
+    # products whose automatic path is another one
+    pm = _pm()
+    for f, g in (fat_bins(ring), W.config3("modp" if ring == "i64" else ring, n=8)):
+        pm.profile_enable(True)
+        check(f, g, "work items requested")
+        names = list(pm.profile_read())
+        pm.profile_enable(False)
+        assert "bk_reduce" in names and not any(x.startswith("gp_") for x in names), names

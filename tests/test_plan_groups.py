@@ -75,3 +75,20 @@ def test_boxes_whose_runs_do_not_divide_evenly(report, ring):
         assert r["mode"] == GRPD
         assert -(-r["K"] // r["least"]) * r["S"] <= r["cells"]
         assert r["ibound"] >= r["nbins"] // r["K"] * r["least"]
+
+
+def test_explicit_sparse_modes_run_what_they_name(report):
+    # the sparse family and a dense one without its box form groups that pay;
+    # a requested mode is taken all the same
+    f, g = W.config3("modp", n=8)
+    for ring, auto in (("modp", GRP), ("i64", GRP), ("f64", GRP)):
+        got = report(*(line(W.config3("modp", n=12)[0], W.config3("modp", n=12)[1], ring, combine=c) for c in (-1, 3, 2, 0)))
+        assert [r["mode"] for r in got] == [auto, BKT, IVAL, RAW]
+    got = report(*(line(f, g, "modp", combine=c) for c in (-1, 3, 2, 1, 0)))
+    assert [r["mode"] for r in got] == [GRP, BKT, IVAL, COMBINE, RAW]
+    small = W.random_sparse(W.rng_for(1), 57, 6, 10, 15, "modp"), W.random_sparse(W.rng_for(2), 61, 6, 10, 15, "modp")
+    got = report(*(line(*small, "modp", combine=c, tiny=1) for c in (-1, 3, 0)))
+    assert [r["mode"] for r in got] == [TINY, BKT, RAW]
+    box = simplex(4, 12, 8)
+    got = report(*(line(box, box, "modp", tile_cfg=t) for t in (-1, 0, 2)))
+    assert [r["mode"] for r in got] == [GRPD, DENSE, DENSE]
