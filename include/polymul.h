@@ -373,7 +373,9 @@ int pm_profile_read(int32_t i, char *name, int32_t name_cap, double *total_ms, i
  * for the product's size class (ring, path, floor(log2(term pairs))).  Later
  * calls with automatic settings (pm_set_tuning(-1, -1, ...) and
  * pm_set_radix(-1), the defaults) use the remembered choice for their
- * largest product's class.  A setting whose workspace exceeds
+ * largest product's class.  Products that automatic selection gives to the
+ * single workgroup or to prefix groups stay there, unless that path was what
+ * this product took and the choice was timed faster than it.  A setting whose workspace exceeds
  * `workspace_bytes` is skipped.  *tile_cfg, *combine and *digits (each may be
  * NULL; *digits is -1 where no radix sort runs) receive the choice.  Results
  * never depend on it.  Synchronises `stream`.
@@ -384,7 +386,8 @@ int pm_autotune(const pm_layout *layout, const pm_cpoly *f, const pm_cpoly *g, c
  * Keep the autotuner's choices across processes (Section 5 tunes l once, at
  * installation): pm_autotune_save writes every remembered choice to the text
  * file `path` (one line per size class: ring, path, floor(log2(term pairs)),
- * tile shape, sparse mode, digit schedule); pm_autotune_load adds the choices
+ * tile shape, sparse mode, digit schedule, and a 1 behind them where the choice
+ * also replaces the single workgroup or prefix groups); pm_autotune_load adds the choices
  * of such a file to the remembered ones (a class already remembered takes the
  * file's choice).  Host only.  PM_EINVAL if the file cannot be written or
  * read or a line is malformed (then nothing is loaded).

@@ -736,14 +736,12 @@ int pm_autotune(const pm_layout *layout, const pm_cpoly *f, const pm_cpoly *g, c
     base.tile_cfg = -1;
     base.combine = -1;
     base.digits = -1;
+    base.remembered = false;  // what was remembered before is not timed as the automatic choice
     rc = mul_impl(g_stage, layout, 1, f, g, h, workspace, workspace_bytes, st, base, &P0);
     if (rc) return rc;
     if (P0.nseg < 1 || P0.segs[0].mode == SEG_EMPTY) return PM_OK;
-    const bool dense = P0.segs[0].mode == SEG_DENSE || P0.segs[0].mode == SEG_GRPD;
-    struct Cand {
-        int tile_cfg, combine, digits;
-    };
-    std::vector<Cand> cands;  // radix-sorted settings are tried with both digit schedules
+    const bool dense = P0.cls.dense != 0;
+    std::vector<TuneChoice> cands;  // radix-sorted settings are tried with both digit schedules
     const int G = RADIX_DIGITS_GREEDY, B = RADIX_DIGITS_BALANCED;
     if (dense) {
         for (int t = 0; t < N_TILE_CFGS; t++) cands.push_back({t, 0, -1});
@@ -762,28 +760,33 @@ int pm_autotune(const pm_layout *layout, const pm_cpoly *f, const pm_cpoly *g, c
     }
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return PM_EDEVICE;
-    float best = 1e30f;
-    Cand choice = cands[0];
-    for (auto &cd : cands) {
+    // two runs after one to warm up; PM_ENOMEM: more workspace than given
+    auto time_of = [&](const TuneChoice &cd, float &total) -> int {
         Tuning t = base;
         t.tile_cfg = cd.tile_cfg;
         t.combine = cd.combine;
         t.digits = cd.digits;
-        rc = mul_impl(g_stage, layout, 1, f, g, h, workspace, workspace_bytes, st, t, nullptr);  // warm-up
-        if (rc == PM_ENOMEM) {  // this setting needs more workspace than given: not a candidate
-            rc = PM_OK;
-            continue;
-        }
-        if (rc) break;
-        float total = 0;
-        for (int rep = 0; rep < 2 && !rc; rep++) {
+        int r = mul_impl(g_stage, layout, 1, f, g, h, workspace, workspace_bytes, st, t, nullptr);
+        total = 0;
+        for (int rep = 0; rep < 2 && !r; rep++) {
             (void)hipEventRecord(e0, st);
-            rc = mul_impl(g_stage, layout, 1, f, g, h, workspace, workspace_bytes, st, t, nullptr);
+            r = mul_impl(g_stage, layout, 1, f, g, h, workspace, workspace_bytes, st, t, nullptr);
             (void)hipEventRecord(e1, st);
             (void)hipEventSynchronize(e1);
             float ms = 0;
             (void)hipEventElapsedTime(&ms, e0, e1);
             total += ms;
+        }
+        return r;
+    };
+    float best = 1e30f;
+    TuneChoice choice = cands[0];
+    for (auto &cd : cands) {
+        float total;
+        rc = time_of(cd, total);
+        if (rc == PM_ENOMEM) {  // not a candidate
+            rc = PM_OK;
+            continue;
         }
         if (rc) break;
         if (total < best) {
@@ -791,12 +794,16 @@ int pm_autotune(const pm_layout *layout, const pm_cpoly *f, const pm_cpoly *g, c
             choice = cd;
         }
     }
+    const int m0 = P0.segs[0].mode;
+    if (!rc && (m0 == SEG_TINY || m0 == SEG_GRP || m0 == SEG_GRPD)) {
+        float total;
+        rc = time_of(TuneChoice{}, total);
+        choice.over_auto = best < total;
+    }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc) return rc;
-    const uint64_t pairs = (uint64_t)f->n * (uint64_t)g->n;
-    tune_store(TuneClass{layout->ring, dense ? 1 : 0, log2_floor(pairs)}, choice.tile_cfg, choice.combine,
-               choice.digits);
+    tune_store(P0.cls, choice);
     if (tile_cfg) *tile_cfg = choice.tile_cfg;
     if (combine) *combine = choice.combine;
     if (digits) *digits = choice.digits;

@@ -14,24 +14,19 @@
 namespace pm {
 
 static std::mutex g_tune_mu;
-struct TuneChoice {
-    int tile_cfg, combine, digits;
-};
 static std::map<TuneClass, TuneChoice> g_tune_cache;
 
-bool tune_lookup(const TuneClass &c, int &tile_cfg, int &combine, int &digits) {
+bool tune_lookup(const TuneClass &c, TuneChoice &choice) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tune_cache.find(c);
     if (it == g_tune_cache.end()) return false;
-    tile_cfg = it->second.tile_cfg;
-    combine = it->second.combine;
-    digits = it->second.digits;
+    choice = it->second;
     return true;
 }
 
-void tune_store(const TuneClass &c, int tile_cfg, int combine, int digits) {
+void tune_store(const TuneClass &c, const TuneChoice &choice) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
-    g_tune_cache[c] = {tile_cfg, combine, digits};
+    g_tune_cache[c] = choice;
 }
 
 void tune_reset() {
@@ -39,15 +34,16 @@ void tune_reset() {
     g_tune_cache.clear();
 }
 
-// Text file, one choice per line: ring dense log2pairs tile_cfg combine digits.
+// Text file, one choice per line: ring dense log2pairs tile_cfg combine digits,
+// and a 1 behind them where the choice was faster than the automatic path too.
 int tune_save(const char *path) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     FILE *f = fopen(path, "w");
     if (!f) return PM_EINVAL;
     fprintf(f, "# polymul tuning: ring dense log2pairs tile_cfg combine digits\n");
     for (auto &kv : g_tune_cache)
-        fprintf(f, "%d %d %d %d %d %d\n", kv.first.ring, kv.first.dense, kv.first.log2pairs, kv.second.tile_cfg,
-                kv.second.combine, kv.second.digits);
+        fprintf(f, "%d %d %d %d %d %d%s\n", kv.first.ring, kv.first.dense, kv.first.log2pairs, kv.second.tile_cfg,
+                kv.second.combine, kv.second.digits, kv.second.over_auto ? " 1" : "");
     return fclose(f) == 0 ? PM_OK : PM_EINVAL;
 }
 
@@ -59,13 +55,13 @@ int tune_load(const char *path) {
     int rc = PM_OK;
     while (fgets(line, sizeof line, f)) {
         if (line[0] == '#' || line[0] == '\n') continue;
-        int r, d, l, t, c, g;
-        if (sscanf(line, "%d %d %d %d %d %d", &r, &d, &l, &t, &c, &g) != 6 || r < 0 || r > 4 || d < 0 || d > 1 ||
+        int r, d, l, t, c, g, over = 0;
+        if (sscanf(line, "%d %d %d %d %d %d %d", &r, &d, &l, &t, &c, &g, &over) < 6 || r < 0 || r > 4 || d < 0 || d > 1 ||
             l < 0 || l > 127 || t < -1 || t >= N_TILE_CFGS || c < -1 || c > 3 || g < -1 || g > 1) {
             rc = PM_EINVAL;
             break;
         }
-        got.push_back({TuneClass{r, d, l}, TuneChoice{t, c, g}});
+        got.push_back({TuneClass{r, d, l}, TuneChoice{t, c, g, over == 1}});
     }
     fclose(f);
     if (rc != PM_OK) return rc;  // nothing is taken from a malformed file
@@ -359,6 +355,7 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
 
     // automatic settings: the autotuner's choice for the largest product's class
     Tuning tune = tune_in;
+    bool over_auto = false;
     {
         int big = -1;
         unsigned __int128 bigp = 0;
@@ -370,12 +367,13 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
             }
         }
         if (big >= 0) {
-            TuneClass tc{ring, P.segs[big].mode == SEG_DENSE ? 1 : 0, log2_floor((uint64_t)bigp)};
-            int tcfg, comb, dig;
-            if (tune_lookup(tc, tcfg, comb, dig)) {
-                if (tune.tile_cfg < 0) tune.tile_cfg = tcfg;
-                if (tune.combine < 0) tune.combine = comb;
-                if (tune.digits < 0) tune.digits = dig;
+            P.cls = TuneClass{ring, P.segs[big].mode == SEG_DENSE ? 1 : 0, log2_floor((uint64_t)bigp)};
+            TuneChoice c;
+            if (tune_in.remembered && tune_lookup(P.cls, c)) {
+                if (tune.tile_cfg < 0) tune.tile_cfg = c.tile_cfg;
+                if (tune.combine < 0 && !P.cls.dense) tune.combine = c.combine;  // (a box's choice times no sparse mode)
+                if (tune.digits < 0) tune.digits = c.digits;
+                over_auto = c.over_auto;
             }
         }
     }
@@ -388,9 +386,11 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
         DevSeg &d = P.segs[q];
         const bool dense = d.mode == SEG_DENSE;
         if (d.mode == SEG_EMPTY) continue;
-        // (an explicit tile shape or sparse mode is what runs; a remembered mode 3 is not explicit)
-        if (dense ? tune_in.tile_cfg >= 0 : tune_in.combine != -1 || (tune.combine != -1 && tune.combine != 3)) continue;
-        if (tiny && tiny_fits(d.na, d.nb, box[q]) && tune.combine == -1) {
+        // an explicit tile shape or sparse mode is what runs; a remembered one
+        // leaves these paths alone unless it was timed against them
+        if (dense ? tune_in.tile_cfg >= 0 : tune_in.combine != -1) continue;
+        if (over_auto && (dense ? 1 : 0) == P.cls.dense && log2_floor((uint64_t)d.na * (uint64_t)d.nb) == P.cls.log2pairs) continue;
+        if (tiny && tiny_fits(d.na, d.nb, box[q])) {
             d.mode = SEG_TINY;
             continue;
         }

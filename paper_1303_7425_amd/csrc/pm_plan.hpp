@@ -30,22 +30,30 @@ struct Tuning {
                              // 3 output-key work items (one scatter, in-LDS sort per work item)
     int allow_dense = 1;     // permit the degree-box path
     bool tiny = false;       // permit the single workgroup (products on their own, outside graphs and the server)
+    bool remembered = true;  // automatic settings take the autotuner's choices
     int digits = -1;         // radix digit schedule: -1 auto, RADIX_DIGITS_GREEDY, RADIX_DIGITS_BALANCED
     double dense_ratio = 2;  // dense when box * dense_ratio <= na * nb
     int64_t dense_max_cells = int64_t(1) << 35;  // 256 GiB of u64 cells
 };
 
-// Autotuner cache: size class -> (tile_cfg, combine, digits).  Thread-safe.
+// Autotuner cache: size class -> choice among the explicit settings.
+// Thread-safe.  over_auto: the choice was also timed faster than a path that
+// automatic selection alone takes (single workgroup, prefix groups), and so
+// replaces it for products of the class; otherwise those keep their path.
+struct TuneChoice {
+    int tile_cfg = -1, combine = -1, digits = -1;
+    bool over_auto = false;
+};
 struct TuneClass {
-    int ring, dense, log2pairs;
+    int ring = 0, dense = 0, log2pairs = 0;
     bool operator<(const TuneClass &o) const {
         if (ring != o.ring) return ring < o.ring;
         if (dense != o.dense) return dense < o.dense;
         return log2pairs < o.log2pairs;
     }
 };
-bool tune_lookup(const TuneClass &c, int &tile_cfg, int &combine, int &digits);
-void tune_store(const TuneClass &c, int tile_cfg, int combine, int digits);
+bool tune_lookup(const TuneClass &c, TuneChoice &choice);
+void tune_store(const TuneClass &c, const TuneChoice &choice);
 void tune_reset();
 int tune_save(const char *path);
 int tune_load(const char *path);
@@ -98,6 +106,7 @@ struct Plan {
     size_t o_gp_seg = 0, o_gp_sb_pre = 0, o_gp_term = 0, o_gp_pfx = 0, o_gp_start = 0, o_gp_ng = 0;
     size_t o_gp_lut = 0, o_gp_hist = 0, o_gp_look = 0, o_gp_sbit = 0, o_gp_item = 0, o_gp_u = 0, o_gp_usum = 0;
     size_t o_gp_rkey = 0, o_gp_rcoef = 0;
+    TuneClass cls;              // the largest product's
     int64_t nstage = 0, nbox = 0, nck = 0;
     int nsparse = 0, ndense = 0, nempty = 0;
     int ntiny = 0;              // SEG_TINY products

@@ -1,6 +1,7 @@
 // Host program around the planner for test_plan_groups.py.
-//   runs   checks every cut of a run of bins into work items
-//   plan   reads products from stdin, prints each one's plan as a line of JSON
+//   runs         checks every cut of a run of bins into work items
+//   plan [file]  reads products from stdin, prints each one's plan as a line of
+//                JSON; file: remembered tuning choices
 #include <stdio.h>
 #include <string.h>
 
@@ -70,6 +71,7 @@ static int plan() {
 
 int main(int argc, char **argv) {
     if (argc == 2 && !strcmp(argv[1], "runs")) return runs();
-    if (argc == 2 && !strcmp(argv[1], "plan")) return plan();
+    if (argc == 3 && tune_load(argv[2]) != 0) return 2;
+    if (argc >= 2 && !strcmp(argv[1], "plan")) return plan();
     return 2;
 }

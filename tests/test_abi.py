@@ -159,3 +159,15 @@ def test_plan_paper_examples_beyond_sparse_limits_take_degree_box(example):
     assert 8 * cells <= wb < 8 * cells + (1 << 30)
     rc, _, _ = pm.plan_from_stats((5, 12, "f64"), [len(f)], [len(g)], st[None, :])
     assert rc == pm.PM_ENOMEM
+
+
+def test_autotune_choices_that_replace_automatic_paths_save_and_load(tmp_path):
+    # the mark behind a choice that was timed against the automatic path
+    src, out = tmp_path / "tune.txt", tmp_path / "out.txt"
+    src.write_text("0 0 25 -1 3 -1 1\n1 0 11 -1 0 1\n0 1 20 2 0 -1 0\n")
+    pm.autotune_reset()
+    pm.autotune_load(src)
+    pm.autotune_save(out)
+    pm.autotune_reset()
+    assert sorted(ln for ln in out.read_text().splitlines() if not ln.startswith("#")) == \
+        sorted(["0 0 25 -1 3 -1 1", "1 0 11 -1 0 1", "0 1 20 2 0 -1"])

@@ -159,3 +159,27 @@ def test_config4_subsample_full_parity():
         print(f"[cfg4 subsample] ring={ring} pairs={[(len(f), len(g)) for f, g in pairs]}", flush=True)
         res = pm.mul_batch((6, 10, ring), [pm.to_device(f) for f, _ in pairs], [pm.to_device(g) for _, g in pairs])
         check_results(pairs, res, ring)
+
+
+def test_autotune_keeps_the_paths_that_are_faster():
+    # a small product stays with its single workgroup and a box with its prefix
+    # groups after they were tuned; the remembered settings are explicit ones
+    pm = _pm()
+    pm.autotune_reset()
+    rng = W.rng_for(7)
+    small = tuple(W.random_sparse(rng, m, 6, 10, 15, "f64") for m in (57, 61))
+    from test_gpu_groups import grid
+    box = tuple(grid(rng, "modp", (9, 9, 9, 9), 10) for _ in "fg")
+    for (f, g), kernel in ((small, "tiny"), (box, "gp_box"), (W.config3("modp", n=10), "gp_reduce")):
+        lay = (f.layout.nvars, f.layout.bits, f.layout.ring)
+        df, dg = pm.to_device(f), pm.to_device(g)
+        for _ in range(2):  # the second time with the first one's choice remembered
+            assert pm.autotune(lay, df, dg)[1] in (0, 1, 2, 3)
+            pm.profile_enable(True)
+            got = pm.mul(lay, df, dg).numpy()
+            names = list(pm.profile_read())
+            pm.profile_enable(False)
+            assert kernel in names, names
+        want = oracle.mul(f, g)
+        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1].view(np.uint64), want[1].view(np.uint64))
+    pm.autotune_reset()

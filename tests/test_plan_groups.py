@@ -22,8 +22,8 @@ def report(tmp_path_factory):
                            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-I", B.CSRC, src,
                            os.path.join(B.CSRC, "pm_plan.cpp"), "-o", exe])
 
-    def run(*products):
-        got = subprocess.run([exe, "plan"], input="\n".join(products), capture_output=True, text=True, check=True).stdout
+    def run(*products, tuned=None):
+        got = subprocess.run([exe, "plan"] + ([tuned] if tuned else []), input="\n".join(products), capture_output=True, text=True, check=True).stdout
         return [json.loads(ln) for ln in got.splitlines()]
     run.exe = exe
     return run
@@ -92,3 +92,32 @@ def test_explicit_sparse_modes_run_what_they_name(report):
     box = simplex(4, 12, 8)
     got = report(*(line(box, box, "modp", tile_cfg=t) for t in (-1, 0, 2)))
     assert [r["mode"] for r in got] == [GRPD, DENSE, DENSE]
+
+
+def test_remembered_choices_leave_automatic_paths_alone(report, tmp_path):
+    # choices among the explicit settings, as files of before hold them, do not
+    # switch the single workgroup or prefix groups off; one that was timed
+    # against them does, for its own class; a box's choice is no sparse mode
+    sparse = W.config3("modp", n=8)
+    small = W.random_sparse(W.rng_for(1), 57, 6, 10, 15, "f64"), W.random_sparse(W.rng_for(2), 61, 6, 10, 15, "f64")
+    box, other = simplex(4, 12, 8), (W.random_sparse(W.rng_for(1), 1820, 12, 5, 3, "modp"), W.random_sparse(W.rng_for(2), 1820, 12, 5, 3, "modp"))
+    cases = [line(*sparse, "modp"), line(*small, "f64", tiny=1), line(box, box, "modp")]
+    log2 = [(len(f) * len(g)).bit_length() - 1 for f, g in (sparse, small, (box, box))]
+
+    def modes(lines, *products):
+        path = tmp_path / "tune.txt"
+        path.write_text("\n".join(lines) + "\n")
+        return [r["mode"] for r in report(*products, tuned=str(path))]
+
+    auto = [GRP, TINY, GRPD]
+    old = [f"0 0 {log2[0]} -1 0 1", f"1 0 {log2[1]} -1 0 1", f"0 1 {log2[2]} 1 0 -1"]
+    assert modes(["# none"], *cases) == auto
+    assert modes(old, *cases) == auto
+    assert modes([o + " 1" for o in old], *cases) == [RAW, RAW, DENSE]
+    assert modes([f"0 0 {log2[0] + 1} -1 0 1 1", f"0 1 {log2[0]} 1 0 -1 1"], *cases) == auto
+    # without groups, the remembered mode is taken; a dense class's is not
+    k = (len(other[0]) * len(other[1])).bit_length() - 1
+    free = report(line(*other, "modp"))[0]["mode"]
+    assert free not in (GRP, GRPD)
+    assert modes([f"0 0 {k} -1 1 1"], line(*other, "modp")) == [COMBINE]
+    assert modes([f"0 1 {k} -1 1 1"], line(*other, "modp")) == [free]
