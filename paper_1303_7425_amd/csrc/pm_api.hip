@@ -274,6 +274,7 @@ int upload_descriptors(HostStage &hs, Plan &P, void *ws, hipStream_t st, hipStre
     if (P.ngp) {
         memcpy(pin + (P.o_gp_seg - d0), P.gp_seg.data(), 4 * P.gp_seg.size());
         memcpy(pin + (P.o_gp_sb_pre - d0), P.gp_sb_pre.data(), 8 * P.gp_sb_pre.size());
+        if (!P.gp_pt_pre.empty()) memcpy(pin + (P.o_gp_pt_pre - d0), P.gp_pt_pre.data(), 8 * P.gp_pt_pre.size());
     }
     if (!P.bk_sb_pre.empty()) memcpy(pin + (P.o_bk_sb_pre - d0), P.bk_sb_pre.data(), 8 * P.bk_sb_pre.size());
     // the copy runs on `ust` (default: the launch stream); the launch stream

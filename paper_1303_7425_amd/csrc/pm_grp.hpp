@@ -11,6 +11,7 @@
 // itself, from contiguous pieces of both operands, in LDS cells: no pair is
 // staged in memory, counted or scattered one by one.  This is Algorithm 1's
 // output interval with FindEdge done once per group instead of once per row.
+//   k_gp_heads   groups per part of the operands, where some operand is large
 //   k_gp_prep    compressed terms, group lists, zeroing of the per-call state
 //   k_gp_lut     first inner term of every prefix; SEG_GRP: pairs per bin, one
 //                addition per pair of groups
@@ -46,8 +47,51 @@ __device__ inline GpOperand gp_operand(const Ctx &C, const DevSeg &s, int bq, in
     return o;
 }
 
-// Workgroups [0, nop): one operand each.  The others clear [zp, zp + zn).
-__global__ __launch_bounds__(GPP_T) void k_gp_prep(Ctx C, int nop, u64 *zp, i64 zn) {
+// Part x of the operands' parts (gp_pt_pre, or one part per operand): the
+// operand's index and its terms [b0, b1).
+struct GpPart {
+    int op;
+    i64 b0, b1;
+};
+__device__ inline GpPart gp_part(const Ctx &C, bool split, int x) {
+    GpPart p;
+    p.op = split ? seg_search(C.gp_pt_pre, 2 * C.ngp, (i64)x) : x;
+    const DevSeg &s = C.segs[C.gp_seg[p.op >> 1]];
+    const i64 n = (p.op & 1) ? s.nb : s.na;
+    p.b0 = split ? (x - C.gp_pt_pre[p.op]) * GP_PART : 0;
+    p.b1 = split ? min(n, p.b0 + GP_PART) : n;
+    return p;
+}
+
+// Groups that start in every part, where an operand has several.  (One
+// workgroup alone takes 1.2 ms for a million terms, most of it latency.)
+__global__ __launch_bounds__(GPP_T) void k_gp_heads(Ctx C) {
+    __shared__ u32 s_sum[GPP_T / 64];
+    const GpPart pt = gp_part(C, true, blockIdx.x);
+    const DevSeg &s = C.segs[C.gp_seg[pt.op >> 1]];
+    const u64 *key = (pt.op & 1) ? s.gk : s.fk;
+    const u32 psh = C.vars[s.var_off + s.gp.d - 1].shift;
+    u64 k[GP_PART / GPP_T], prev[GP_PART / GPP_T];
+#pragma unroll
+    for (int e = 0; e < GP_PART / GPP_T; e++) {
+        const i64 i = min(pt.b0 + e * GPP_T + threadIdx.x, pt.b1 - 1);
+        k[e] = key[i];
+        prev[e] = key[max(i - 1, (i64)0)];
+    }
+    u32 hd = 0;
+#pragma unroll
+    for (int e = 0; e < GP_PART / GPP_T; e++) {
+        const i64 i = pt.b0 + e * GPP_T + threadIdx.x;
+        if (i < pt.b1 && (i == 0 || ((k[e] ^ prev[e]) >> psh) != 0)) hd++;
+    }
+    u32 tot;
+    (void)block_excl_scan<u32, GPP_T>(hd, s_sum, tot);
+    if (threadIdx.x == 0) C.gp_pt_cnt[blockIdx.x] = tot;
+}
+
+// Workgroups [0, nop): one part of an operand each (split: of several, whose
+// group counts k_gp_heads has left).  The others clear [zp, zp + zn).
+__global__ __launch_bounds__(GPP_T) void k_gp_prep(Ctx C, int nop, bool split, u64 *zp, i64 zn) {
     if ((int)blockIdx.x >= nop) {
         for (i64 i = (i64)(blockIdx.x - nop) * GPP_T + threadIdx.x; i < zn; i += (i64)(gridDim.x - nop) * GPP_T)
             zp[i] = 0;
@@ -56,7 +100,8 @@ __global__ __launch_bounds__(GPP_T) void k_gp_prep(Ctx C, int nop, u64 *zp, i64 
     __shared__ u32 s_hi[MAX_VARS], s_lo[MAX_VARS], s_sh[MAX_VARS];
     __shared__ u64 s_mn[MAX_VARS];
     __shared__ u32 s_scan[GPP_T / 64];
-    const int bq = blockIdx.x >> 1, side = blockIdx.x & 1;
+    const GpPart pt = gp_part(C, split, blockIdx.x);
+    const int bq = pt.op >> 1, side = pt.op & 1;
     const DevSeg &s = C.segs[C.gp_seg[bq]];
     const int nv = C.nvars, d = (int)s.gp.d;
     const VarParam *vp = C.vars + s.var_off;
@@ -77,6 +122,11 @@ __global__ __launch_bounds__(GPP_T) void k_gp_prep(Ctx C, int nop, u64 *zp, i64 
     // coefficient words: 31 and 30 bits mod p, else 32 and 32
     const u32 csh = C.ring == RING_MODP ? 31 : 32, cmask = C.ring == RING_MODP ? 0x7FFFFFFFu : ~0u;
     u32 ng = 0;
+    if (split) {  // groups of the operand's earlier parts
+        u32 x = 0;
+        for (i64 i = C.gp_pt_pre[pt.op] + threadIdx.x; i < (i64)blockIdx.x; i += GPP_T) x += C.gp_pt_cnt[i];
+        (void)block_excl_scan<u32, GPP_T>(x, s_scan, ng);
+    }
     // the next step's terms are loaded before this one's are scanned
     u64 nk[4], nc[4], np = 0;
     auto load = [&](i64 i0) {
@@ -88,8 +138,8 @@ __global__ __launch_bounds__(GPP_T) void k_gp_prep(Ctx C, int nop, u64 *zp, i64 
         }
         np = key[max(min(i0, n) - 1, (i64)0)];
     };
-    load((i64)threadIdx.x * 4);
-    for (i64 b = 0; b < n; b += GPP_T * 4) {
+    load(pt.b0 + (i64)threadIdx.x * 4);
+    for (i64 b = pt.b0; b < pt.b1; b += GPP_T * 4) {
         const i64 i0 = b + (i64)threadIdx.x * 4;
         u64 k[4], c[4], prev = np;
 #pragma unroll
@@ -97,7 +147,7 @@ __global__ __launch_bounds__(GPP_T) void k_gp_prep(Ctx C, int nop, u64 *zp, i64 
             k[e] = nk[e];
             c[e] = nc[e];
         }
-        if (b + GPP_T * 4 < n) load(i0 + GPP_T * 4);
+        if (b + GPP_T * 4 < pt.b1) load(i0 + GPP_T * 4);
         u32 p[4], lo[4], hd = 0;
 #pragma unroll
         for (int e = 0; e < 4; e++) {
@@ -125,11 +175,12 @@ __global__ __launch_bounds__(GPP_T) void k_gp_prep(Ctx C, int nop, u64 *zp, i64 
         }
         ng += tot;
     }
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 0 && pt.b1 == n) {
         start[ng] = (u32)n;
         C.gp_ng[2 * bq + side] = ng;
     }
 }
+static_assert(GP_PART % (GPP_T * 4) == 0, "steps of a part");
 
 // lut[b]: first inner term of prefix b or more (b up to and including nbins).
 // SEG_GRP: pairs of every bin, each pair of groups adding its block's size.

@@ -40,6 +40,9 @@ constexpr int GP_SPAN_LOG = 17;        // key span (log2) of the presence bitmap
 constexpr int GP_MAX_S = 61440;        // cells of a bin, at most: a work item then has at most 2^16 keys (gp.T <= 4096 pairs before its last bin)
 constexpr int GP_F64_CELLS = 3840;     // FP64: LDS cells of a wave, at most (five waves per compute unit)
 constexpr int GP_PAD = 1024;           // term slots after the last operand (loads past a block's rows)
+constexpr int GP_PART = 16384;         // terms of a workgroup of k_gp_prep
+constexpr i64 GP_SPLIT = 2 * GP_PART;  // operands of more terms are prepared in parts; up to there one workgroup takes
+                                       // 1.2 ns per term (40 us), a second launch and its counts some 10 us
 // Listed work items: pairs of one whose keys span up to 2^sl (17 to 19) and are
 // ranked, at most; what the bitmap leaves of the LDS.
 constexpr u32 gl_pairs(u32 sl) { return sl == 17 ? 10240 : sl == 18 ? 8192 : 5120; }
@@ -304,6 +307,8 @@ struct Ctx {
     const i64 *gp_sb_pre;       // [ngp+1] super-bin prefix
     i32 ngp;
     i64 gp_nsb, gp_ibound;      // super-bins; work-item slots of SEG_GRP
+    const i64 *gp_pt_pre;       // [2 ngp + 1] parts of the operands (f, g of every product), where prepared in parts
+    u32 *gp_pt_cnt;             // groups that start in every part
     GpTerm *gp_term;            // operand terms
     u32 *gp_pfx, *gp_start;     // groups of every operand: prefix, first term (closed by the term count)
     u32 *gp_ng;                 // [2 ngp] groups of f and g

@@ -1978,8 +1978,10 @@ static void launch_gp_box(const Plan &P, const Ctx &C, hipStream_t st, int cus, 
 static void launch_gp_head(const Plan &P, const Ctx &C, hipStream_t st, int cus, u64 *zp, i64 zn) {
     {
         ProfScope ps("gp_prep", st);
-        const int nz = grid_for((zn + GPP_T - 1) / GPP_T, cus * 2);
-        hipLaunchKernelGGL(k_gp_prep, dim3(2 * P.ngp + nz), dim3(GPP_T), 0, st, C, 2 * P.ngp, zp, zn);
+        const bool split = !P.gp_pt_pre.empty();
+        const int nz = grid_for((zn + GPP_T - 1) / GPP_T, cus * 2), nop = split ? (int)P.gp_pt_pre.back() : 2 * P.ngp;
+        if (split) hipLaunchKernelGGL(k_gp_heads, dim3(nop), dim3(GPP_T), 0, st, C);
+        hipLaunchKernelGGL(k_gp_prep, dim3(nop + nz), dim3(GPP_T), 0, st, C, nop, split, zp, zn);
     }
     ProfScope ps("gp_lut", st);
     const int gy = std::min(P.ngp, 1024);
@@ -2205,6 +2207,8 @@ Ctx make_ctx(const Plan &P, void *ws) {
     C.gp_ibound = P.gp_ibound;
     C.gp_seg = (const i32 *)(b + P.o_gp_seg);
     C.gp_sb_pre = (const i64 *)(b + P.o_gp_sb_pre);
+    C.gp_pt_pre = (const i64 *)(b + P.o_gp_pt_pre);
+    C.gp_pt_cnt = (u32 *)(b + P.o_gp_pt_cnt);
     C.gp_term = (GpTerm *)(b + P.o_gp_term);
     C.gp_pfx = (u32 *)(b + P.o_gp_pfx);
     C.gp_start = (u32 *)(b + P.o_gp_start);

@@ -162,8 +162,8 @@ static GpTry gp_try(int nvars, const VarParam *vp, int64_t na, int64_t nb, unsig
     }
     if (!o.ok) return o;
     const int64_t nt = na + nb;
-    o.bytes = (int64_t)(sizeof(GpTerm) + 8) * nt + 4 * ((int64_t)g.nbins + 1) + 16 * 256 +
-              GP_PAD * (int64_t)sizeof(GpTerm);
+    o.bytes = (int64_t)(sizeof(GpTerm) + 8) * nt + 4 * ((int64_t)g.nbins + 1) + 18 * 256 +
+              GP_PAD * (int64_t)sizeof(GpTerm) + 4 * (nt / GP_PART + 2);
     if (dense) {
         // runs of K bins, cut into work items of about 1/12 of a workgroup's
         // share (512 workgroups), at least 2048 pairs
@@ -530,6 +530,7 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
     P.dpart_pre.push_back(0);
     P.cpre.push_back(0);
     int64_t nstage = 0, nbox = 0, nck = 0;
+    bool split = false;
     for (int q = 0; q < S; q++) {
         DevSeg &d = P.segs[q];
         if (d.mode == SEG_EMPTY) P.nempty++;
@@ -566,6 +567,7 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
             d.nb_div = make_div32(t.g.S);
             P.gp_seg.push_back(q);
             P.gp_sb_pre.push_back(P.gp_nsb);
+            split |= std::max(d.na, d.nb) > GP_SPLIT;
             if (d.mode == SEG_GRPD) {
                 P.ngp_box++;
                 P.gp_dpairs += (double)d.na * (double)d.nb;
@@ -663,6 +665,11 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
             P.ndense++;
         }
     }
+    if (split) {
+        P.gp_pt_pre.push_back(0);
+        for (int32_t q : P.gp_seg)
+            for (int64_t n : {P.segs[q].na, P.segs[q].nb}) P.gp_pt_pre.push_back(P.gp_pt_pre.back() + (n + GP_PART - 1) / GP_PART);
+    }
     P.ntiles = P.tile_pre.back();
     P.ndparts = P.dpart_pre.back();
     P.nstage = nstage;
@@ -724,6 +731,7 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
     if (P.ngp) {
         P.o_gp_seg = small(4 * P.gp_seg.size());
         P.o_gp_sb_pre = small(8 * P.gp_sb_pre.size());
+        P.o_gp_pt_pre = small(8 * P.gp_pt_pre.size());
     }
     off = align256(off);
     P.r_desc.off = desc0;
@@ -778,6 +786,7 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
     P.r_zero.bytes = off - zero0;
     if (!zero_box) P.o_box = take((size_t)8 * std::max<int64_t>(1, nbox));
     if (P.ngp) {
+        P.o_gp_pt_cnt = take((size_t)4 * (P.gp_pt_pre.empty() ? 0 : P.gp_pt_pre.back()));
         P.o_gp_term = take(sizeof(GpTerm) * (size_t)(P.gp_nterm + GP_PAD));
         P.o_gp_pfx = take((size_t)4 * P.gp_nterm);
         P.o_gp_start = take((size_t)4 * (P.gp_nterm + 2 * P.ngp));

@@ -99,10 +99,12 @@ struct Plan {
     int ngp = 0, ngp_sparse = 0, ngp_list = 0;
     std::vector<int32_t> gp_seg;
     std::vector<int64_t> gp_sb_pre;
+    std::vector<int64_t> gp_pt_pre;  // parts of the operands (empty: one each)
     int64_t gp_nterm = 0, gp_nlut = 0, gp_nsb = 0, gp_ibound = 0, gp_nres = 0, gp_maxgrp = 0, gp_maxbins = 0;
     int ngp_box = 0;            // SEG_GRPD products
     double gp_dpairs = 0;       // their term pairs
     int gp_fc = 0;              // FP64: LDS cells of a wave (1024, 2048 or GP_F64_CELLS)
+    size_t o_gp_pt_pre = 0, o_gp_pt_cnt = 0;
     size_t o_gp_seg = 0, o_gp_sb_pre = 0, o_gp_term = 0, o_gp_pfx = 0, o_gp_start = 0, o_gp_ng = 0;
     size_t o_gp_lut = 0, o_gp_hist = 0, o_gp_look = 0, o_gp_sbit = 0, o_gp_item = 0, o_gp_u = 0, o_gp_usum = 0;
     size_t o_gp_rkey = 0, o_gp_rcoef = 0;

@@ -346,3 +346,40 @@ def test_powers_whose_runs_do_not_divide_evenly(ring, nvars, n):
     assert pm.last_call_status() == 0
     k, c = h.numpy()
     assert np.array_equal(k, want.keys) and np.array_equal(c.view(np.uint64), want.coefs.view(np.uint64))
+
+
+@pytest.mark.parametrize("ring", ["modp", "f64"])
+@pytest.mark.parametrize("n", [32768, 32769, 49151, 49153, 90000])
+def test_operands_prepared_in_parts(ring, n):
+    # parts of 16384 terms from 32769 terms on: groups that end at, straddle and
+    # start at a part's edge, beside an operand of one part
+    rng = W.rng_for(n)
+    rows = 300 if n == 32768 else 128 if n == 32769 else 257
+    e = np.indices((rows, -(-n // rows))).reshape(2, -1).T[:n] * np.array([1, 2])
+    p = W.Poly(W.Layout(2, 16, ring), np.sort(W.pack(e, 2, 16)), np.zeros(n, np.uint64))
+    f, g = W.with_random_coefs(p, rng, ring), grid(rng, ring, (5, 9), 16, step=(40, 3))
+    takes_groups(f, g, f"{n} terms in {rows} groups")
+    takes_groups(g, f, f"{n} terms in {rows} groups, swapped")
+
+
+def test_batch_with_an_operand_in_parts():
+    # parts of one product's operands beside operands of one part, replayed
+    pm = _pm()
+    import oracle
+    import torch
+    rng = W.rng_for(41)
+    pairs = [(grid(rng, "modp", (20, 30), 16), grid(rng, "modp", (9, 60), 16, step=(2, 1))),
+             (grid(rng, "modp", (150, 300), 16), grid(rng, "modp", (4, 40), 16, step=(50, 2))),
+             (grid(rng, "modp", (30, 40), 16), grid(rng, "modp", (20, 30), 16))]
+    call = pm.BatchCall((2, 16, "modp"), [pm.to_device(f) for f, _ in pairs], [pm.to_device(g) for _, g in pairs])
+    call.run()
+    call.prepare_graph()
+    for again in range(3):
+        if again:
+            call.launch_graph()
+        torch.cuda.synchronize()
+        assert pm.last_call_status() == 0
+        for (k, c), (f, g) in zip(call.results(), pairs):
+            wk, wc, _ = oracle.mul(f, g)
+            assert np.array_equal(k, wk) and np.array_equal(c, wc)
+        call.out_k.fill_(0)
