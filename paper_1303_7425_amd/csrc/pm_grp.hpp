@@ -202,10 +202,14 @@ __global__ __launch_bounds__(256) void k_gp_lut(Ctx C) {
         }
         if (s.mode != SEG_GRP) continue;
         u32 *hist = C.gp_hist + uniform64(s.gp.hist);
-        const u32 nw = gridDim.x * 4;
-        for (u32 o = uniform32(blockIdx.x * 4 + (threadIdx.x >> 6)); o < O.groups; o += nw) {
+        // a wave takes one outer group and GP_LUT_I inner ones (with all of them,
+        // one outer group by 160000 inner ones took 0.8 ms, one wave's latencies)
+        const u32 nw = gridDim.x * 4, ni = (I.groups + GP_LUT_I - 1) / GP_LUT_I;
+        const u64 nu = (u64)O.groups * ni;
+        for (u64 x = (u64)uniform32(blockIdx.x * 4 + (threadIdx.x >> 6)); x < nu; x += nw) {
+            const u32 o = (u32)(x / ni), i0 = (u32)(x - (u64)o * ni) * GP_LUT_I, i1 = min(i0 + GP_LUT_I, I.groups);
             const u32 p = O.pfx[o], r = O.start[o + 1] - O.start[o];
-            for (u32 i = threadIdx.x & 63; i < I.groups; i += 64)
+            for (u32 i = i0 + (threadIdx.x & 63); i < i1; i += 64)
                 atomicAdd(&hist[p + I.pfx[i]], r * (I.start[i + 1] - I.start[i]));
         }
     }

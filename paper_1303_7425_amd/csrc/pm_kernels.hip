@@ -1985,7 +1985,7 @@ static void launch_gp_head(const Plan &P, const Ctx &C, hipStream_t st, int cus,
     }
     ProfScope ps("gp_lut", st);
     const int gy = std::min(P.ngp, 1024);
-    const int gx = std::max(1, std::min((int)std::max<i64>((P.gp_maxbins + 255) / 256, (P.gp_maxgrp + 3) / 4), cus * 8 / gy));
+    const int gx = std::max(1, (int)std::min<i64>(std::max<i64>((P.gp_maxbins + 255) / 256, (P.gp_maxunits + 3) / 4), cus * 8 / gy));
     hipLaunchKernelGGL(k_gp_lut, dim3(gx, gy), dim3(256), 0, st, C);
     if (P.ngp_box)
         hipLaunchKernelGGL(k_gp_coarse, dim3(std::max(1, cus * 8 / gy), gy),

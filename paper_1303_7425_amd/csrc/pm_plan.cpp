@@ -563,7 +563,7 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
             P.gp_ibound += t.ibound;
             P.gp_nres += t.nres;
             P.gp_maxbins = std::max<int64_t>(P.gp_maxbins, t.g.nbins);
-            P.gp_maxgrp = std::max<int64_t>(P.gp_maxgrp, std::min(d.na, d.nb));
+            P.gp_maxunits = std::max<int64_t>(P.gp_maxunits, std::min(d.na, d.nb) * ((std::max(d.na, d.nb) + GP_LUT_I - 1) / GP_LUT_I));
             d.nb_div = make_div32(t.g.S);
             P.gp_seg.push_back(q);
             P.gp_sb_pre.push_back(P.gp_nsb);

@@ -100,7 +100,7 @@ struct Plan {
     std::vector<int32_t> gp_seg;
     std::vector<int64_t> gp_sb_pre;
     std::vector<int64_t> gp_pt_pre;  // parts of the operands (empty: one each)
-    int64_t gp_nterm = 0, gp_nlut = 0, gp_nsb = 0, gp_ibound = 0, gp_nres = 0, gp_maxgrp = 0, gp_maxbins = 0;
+    int64_t gp_nterm = 0, gp_nlut = 0, gp_nsb = 0, gp_ibound = 0, gp_nres = 0, gp_maxunits = 0, gp_maxbins = 0;
     int ngp_box = 0;            // SEG_GRPD products
     double gp_dpairs = 0;       // their term pairs
     int gp_fc = 0;              // FP64: LDS cells of a wave (1024, 2048 or GP_F64_CELLS)

@@ -383,3 +383,15 @@ def test_batch_with_an_operand_in_parts():
             wk, wc, _ = oracle.mul(f, g)
             assert np.array_equal(k, wk) and np.array_equal(c, wc)
         call.out_k.fill_(0)
+
+
+@pytest.mark.parametrize("ring", ["modp", "i64"])
+def test_few_outer_groups_by_many_inner_ones(ring):
+    # 1 to 17 outer groups by 1023 to 5000 inner ones: pairs per bin counted in
+    # stretches of 1024 inner groups
+    rng = W.rng_for(43)
+    for a, shape in ((1, (1023, 9)), (1, (1024, 9)), (3, (1025, 7)), (17, (5000, 5))):
+        f = grid(rng, ring, (a, 30), 16, step=(1, 61))
+        g = grid(rng, ring, shape, 16, step=(3, 5))
+        takes_groups(f, g, f"{a} groups by {shape[0]}", "gp_reduce")
+        takes_groups(g, f, f"{shape[0]} groups by {a}", "gp_reduce")
