@@ -351,20 +351,34 @@ __global__ __launch_bounds__(BC_T) void k_gp_cut(Ctx C) {
         C.gp_sbit[sb] = (u32)min(s_ibase, (u64)C.gp_ibound);
         if (sb == C.gp_nsb - 1) C.gp_sbit[C.gp_nsb] = (u32)end;
     }
-    for (int k = 0; k < 4 && K; k++) {
-        const u32 b0 = (lsb * GP_SB + 4 * t + k) * K;
-        for (u32 e = 0; e < np[k]; e++) {
-            const i64 at = (i64)(s_ibase + it++);
+    if (K) {
+        // a thread per work item (a single variable's run has thousands of them,
+        // which one thread took 1.3 ms to write): its run is found by a search
+        for (int k = 0; k < 4; k++) {
+            s_pre[4 * t + k] = it;
+            it += np[k];
+        }
+        __syncthreads();
+        for (u32 x = t; x < ni; x += BC_T) {
+            u32 lo = 0, hi = GP_SB - 1;  // last run that starts at x or before
+            while (lo < hi) {
+                const u32 mid = (lo + hi + 1) >> 1;
+                if (s_pre[mid] <= x) lo = mid;
+                else hi = mid - 1;
+            }
+            const i64 at = (i64)(s_ibase + x);
             if (at >= C.gp_ibound) break;
+            const u32 b0 = (lsb * GP_SB + lo) * K, e = x - s_pre[lo];
+            const u32 n = (lo + 1 < (u32)GP_SB ? s_pre[lo + 1] : ni) - s_pre[lo];
             GpItem &I = C.gp_item[at];
-            I.bin_lo = b0 + gp_run_bin(K, np[k], e);
-            I.bin_hi = b0 + gp_run_bin(K, np[k], e + 1);
+            I.bin_lo = b0 + gp_run_bin(K, n, e);
+            I.bin_hi = b0 + gp_run_bin(K, n, e + 1);
             I.q = q;
             I.pre = I.end = 0;
             I.off = 0;
         }
+        return;
     }
-    if (K) return;
     u64 off = s_mbase + mpre;
     pv = pv0;
     for (int k = 0; k < 4; k++) {

@@ -395,3 +395,11 @@ def test_few_outer_groups_by_many_inner_ones(ring):
         g = grid(rng, ring, shape, 16, step=(3, 5))
         takes_groups(f, g, f"{a} groups by {shape[0]}", "gp_reduce")
         takes_groups(g, f, f"{shape[0]} groups by {a}", "gp_reduce")
+
+
+@pytest.mark.parametrize("ring", ["modp", "i64"])
+def test_runs_of_thousands_of_work_items(ring):
+    # one variable: the whole box is one run; two: many runs of a few work items
+    rng = W.rng_for(44)
+    takes_groups(grid(rng, ring, (300,), 32), grid(rng, ring, (40001,), 32), "one run", "gp_box")
+    takes_groups(grid(rng, ring, (5000, 2), 16), grid(rng, ring, (40, 30), 16), "5039 runs", "gp_box")
