@@ -405,13 +405,38 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
             if (!counts) continue;
             const double gf = (double)(*counts)[q].f[t.g.d - 1], gg = (double)(*counts)[q].g[t.g.d - 1];
             const double pairs = (double)d.na * (double)d.nb;
-            // pairs that an outer group has with the bins of a work item
+            // prefixes within the operands' ranges, which their groups are some of
+            double cf = 1, cg = 1;
+            for (uint32_t v = 0; v < t.g.d; v++) {
+                const uint64_t *st = stats + (size_t)q * 4 * nvars;
+                cf *= (double)(st[nvars + v] - (st[v] & smask)) + 1;
+                cg *= (double)(st[3 * nvars + v] - (st[2 * nvars + v] & smask)) + 1;
+            }
+            const double fill = gg < gf ? gf / cf : gg / cg;  // share of them that the inner operand has
+            // pairs that an outer group has with the bins of a work item, if the inner operand has all of them
             const double bins = dense ? (double)t.g.nbins / (double)t.items
                                       : std::max(1.0, std::min<double>(t.g.span_bins, (double)t.g.nbins * t.g.T / pairs));
-            if (gf >= 1 && gg >= 1 && pairs / (gf * gg) * bins < 32) {
+            const double met = pairs / (gf * gg) * bins;
+            // (blocks of a pair or two take 8 times as long as a term each: 10002 by
+            // 10002 of 100000 exponents 4422 us, 376)
+            const bool single = dense && t.g.S == 1 && met * fill < 40;  // one term to a prefix, few prefixes to a work item
+            if (gf >= 1 && gg >= 1 && (met < 32 || (dense && met * fill < 16) || single)) {
                 if (dense) t.g.rows = 1;
                 else if (ring != RING_F64) gp_list(t, pairs, box[q], share);
             }
+            if (single) {
+                // The wider bins of way 2 take half of the time where there are
+                // enough of them (100 x 100 exponents squared 857 us, 329; a
+                // tenth of 300 x 300 426, 170).  Else, terms side by side in full
+                // lattices make a wave's lanes meet in the same cells, and the
+                // tile kernel takes 0.7 of the time (20000 by 20000 terms in one
+                // variable 2803 us, 2362; half of 20 x 2000 exponents squared
+                // 1118, 2472).
+                const GpTry w = gp_try(nvars, &P.vars[(size_t)q * nvars], d.na, d.nb, box[q], dense, share, 2, false);
+                if ((w.ok && w.g.S > 1 && w.g.nbins >= share / 2) || (gf > 0.6 * cf && gg > 0.6 * cg)) continue;
+            }
+            // so few bins leave compute units idle (39 bins: 1368 us, by tiles 411; 199 bins: 329, 570)
+            if (dense && way == 2 && t.g.nbins < share / 2) continue;
             if (gp_pays(t, (*counts)[q], d.na, d.nb, box[q], dense, way, ring == RING_F64)) {
                 gt[q] = t;
                 gt[q].g.swap = gg < gf ? 1 : 0;

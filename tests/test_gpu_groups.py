@@ -401,5 +401,22 @@ def test_few_outer_groups_by_many_inner_ones(ring):
 def test_runs_of_thousands_of_work_items(ring):
     # one variable: the whole box is one run; two: many runs of a few work items
     rng = W.rng_for(44)
-    takes_groups(grid(rng, ring, (300,), 32), grid(rng, ring, (40001,), 32), "one run", "gp_box")
+    takes_groups(grid(rng, ring, (300,), 32), grid(rng, ring, (80001,), 32, keep=0.5), "one run", "gp_box")
     takes_groups(grid(rng, ring, (5000, 2), 16), grid(rng, ring, (40, 30), 16), "5039 runs", "gp_box")
+
+
+@pytest.mark.parametrize("ring", ["modp", "i64"])
+@pytest.mark.parametrize("shape,keep", [((100, 100), 1.0), ((300, 300), 0.05), ((130, 700), 0.02), ((100000,), 0.03)])
+def test_boxes_of_single_terms(ring, shape, keep):
+    # bins of a whole variable (199 to 1399 cells), and a thread per term of one variable
+    from test_gpu_parity import gpu_mul, assert_same
+    import oracle
+    pm = _pm()
+    rng = W.rng_for(46)
+    f, g = (grid(rng, ring, shape, 32 // len(shape), keep=keep) for _ in "fg")
+    lay = (len(shape), 32 // len(shape), ring)
+    pm.profile_enable(True)
+    got = gpu_mul(f, g, dirty(lay, pm.to_device(f), pm.to_device(g)))
+    assert "gp_box" in pm.profile_read()
+    pm.profile_enable(False)
+    assert_same(got, oracle.mul(f, g), ring, f"{shape} {keep}")

@@ -121,3 +121,26 @@ def test_remembered_choices_leave_automatic_paths_alone(report, tmp_path):
     assert free not in (GRP, GRPD)
     assert modes([f"0 0 {k} -1 1 1"], line(*other, "modp")) == [COMBINE]
     assert modes([f"0 1 {k} -1 1 1"], line(*other, "modp")) == [free]
+
+
+def lattice(shape, share=1.0, bits=16):
+    """All exponent vectors below `shape` (a share of them), coefficients one."""
+    e = np.indices(shape).reshape(len(shape), -1).T
+    if share < 1:
+        keep = W.rng_for(5).uniform(size=len(e)) < share
+        keep[0] = keep[-1] = True
+        e = e[keep]
+    return W.Poly(W.Layout(len(shape), bits, "modp"), np.sort(W.pack(e, len(shape), bits)), np.ones(len(e), np.uint64))
+
+
+def test_boxes_of_single_terms(report):
+    # one term to a prefix: bins of a whole variable where there are enough of
+    # them, a thread per term else, and the tile kernel for full lattices
+    pairs = {"square": (lattice((100, 100)),) * 2, "tenth": (lattice((300, 300), 0.1),) * 2, "slab": (lattice((10, 1000)),) * 2,
+             "line": (lattice((20000,), bits=32),) * 2, "sparse line": (lattice((100000,), 0.1, bits=32),) * 2,
+             "few by many": (lattice((1000,), bits=32), lattice((1000000,), bits=32)), "simplex": (simplex(2, 300, 16),) * 2,
+             "four variables": (simplex(4, 20, 16),) * 2}
+    got = dict(zip(pairs, report(*(line(f, g, "modp") for f, g in pairs.values()))))
+    want = {"square": (GRPD, 199, 0), "tenth": (GRPD, 599, 0), "slab": (DENSE, 0, 0), "line": (DENSE, 0, 0),
+            "sparse line": (GRPD, 1, 1), "few by many": (GRPD, 1, 0), "simplex": (GRPD, 601, 0), "four variables": (GRPD, 41, 0)}
+    assert {k: (r["mode"], r["S"], r["rows"]) for k, r in got.items()} == want
