@@ -241,7 +241,16 @@ static bool gp_pays(const GpTry &t, const GpCounts &c, int64_t na, int64_t nb, u
         // from about two columns on; lookups: f's groups for every work item
         // (non-empty bins: a few dozen per group where the groups form a regular set)
         const double items = std::min<double>(t.items, 32 * (gf + gg) + pairs / t.g.T);
-        return (double)nb / gg >= 4 && items * gf <= pairs;
+        if ((double)nb / gg < 4 || items * gf > pairs) return false;
+        // Measured costs, in ps: a non-empty bin's work item about 7 ns, a row's
+        // step by how many waves the cells leave on a compute unit, a block;
+        // against the sort's 32 per pair and more for a long operand (16 x
+        // 300000 terms of 31^5 exponents 1272 us, by the sort 439; 3000 x 3000
+        // of 8^6 421, 314; 1000 x 20000 of 61^3 678, 521).
+        const double cols = (double)nb / gg, steps = (double)na * gg * std::ceil(cols / 64);
+        const double step = t.g.S <= 1024 ? 100 : t.g.S <= 2048 ? 140 : 210;
+        const double bins = std::min(std::min<double>(t.items, 16 * (gf + gg) + pairs / t.g.T), gf * gg);
+        return bins * 7000 + steps * step + gf * gg * 100 <= 20e6 + 32 * pairs + 400 * (double)(na + nb);
     }
     if ((double)t.items * std::min(gf, gg) > (t.g.rows ? 8 : 2) * pairs) return false;
     const double block = pairs / (gf * gg);

@@ -144,3 +144,18 @@ def test_boxes_of_single_terms(report):
     want = {"square": (GRPD, 199, 0), "tenth": (GRPD, 599, 0), "slab": (DENSE, 0, 0), "line": (DENSE, 0, 0),
             "sparse line": (GRPD, 1, 1), "few by many": (GRPD, 1, 0), "simplex": (GRPD, 601, 0), "four variables": (GRPD, 41, 0)}
     assert {k: (r["mode"], r["S"], r["rows"]) for k, r in got.items()} == want
+
+
+def random_pair(nvars, bits, top, na, nb, ring):
+    return tuple(W.random_sparse(W.rng_for(m), m, nvars, bits, top, ring) for m in (na, nb))
+
+
+def test_f64_products_whose_work_items_cost_more_than_the_sort(report):
+    # thousands of non-empty bins of few pairs, a term or two to a block, few
+    # waves for wide bins: pair-index sort; blocks of many pairs: prefix groups
+    cases = {(5, 12, 30, 16, 300000): RAW, (6, 10, 7, 3000, 3000): RAW, (3, 20, 60, 1000, 20000): RAW, (3, 21, 400, 16, 1000000): RAW,
+             (4, 15, 15, 3000, 3000): GRP, (5, 12, 10, 8000, 8000): GRP, (7, 9, 6, 300, 100000): GRP}
+    got = report(*(line(*random_pair(*c, "f64"), "f64") for c in cases))
+    assert [r["mode"] for r in got] == list(cases.values())
+    got = report(*(line(*W.config3("modp", n=n), "f64") for n in (9, 10, 12)))
+    assert [r["mode"] for r in got] == [GRP] * 3
