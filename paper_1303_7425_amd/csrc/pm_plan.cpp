@@ -253,6 +253,12 @@ static bool gp_pays(const GpTry &t, const GpCounts &c, int64_t na, int64_t nb, u
         return bins * 7000 + steps * step + gf * gg * 100 <= 20e6 + 32 * pairs + 400 * (double)(na + nb);
     }
     if ((double)t.items * std::min(gf, gg) > (t.g.rows ? 8 : 2) * pairs) return false;
+    // beyond 32-bit keys the alternative is the pair-index sort, some 62 ps per
+    // pair; a listed work item takes 27 ns and its pairs 34 ps with their
+    // placement, a pair of groups 18 ps (300 x 20000 terms of 4^12 exponents
+    // 961 us, by the sort 495)
+    if (t.g.rows && !dense && box > (unsigned __int128)0xFFFFFFFFull && (double)t.items * 27000 + 18 * gf * gg > 75e6 + 28 * pairs)
+        return false;
     const double block = pairs / (gf * gg);
     if (dense) return block * t.g.nbins / t.items >= 4;
     if (pairs / (double)box * t.g.span_bins * t.g.S < (t.g.rows ? 24 : 256)) return false;

@@ -159,3 +159,11 @@ def test_f64_products_whose_work_items_cost_more_than_the_sort(report):
     assert [r["mode"] for r in got] == list(cases.values())
     got = report(*(line(*W.config3("modp", n=n), "f64") for n in (9, 10, 12)))
     assert [r["mode"] for r in got] == [GRP] * 3
+
+
+def test_sparser_products_beyond_32_bit_keys(report):
+    # box of 7^12 cells: a listed work item per key span, most of them nearly
+    # empty; the same sizes within 31^6 and 15^8 cells
+    cases = {(12, 5, 3, 300, 20000): RAW, (12, 5, 3, 5000, 5000): RAW, (6, 10, 15, 300, 20000): GRP, (8, 7, 7, 5000, 5000): GRP}
+    got = report(*(line(*random_pair(*c, "modp"), "modp") for c in cases))
+    assert [r["mode"] for r in got] == list(cases.values())
