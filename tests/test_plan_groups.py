@@ -167,3 +167,10 @@ def test_sparser_products_beyond_32_bit_keys(report):
     cases = {(12, 5, 3, 300, 20000): RAW, (12, 5, 3, 5000, 5000): RAW, (6, 10, 15, 300, 20000): GRP, (8, 7, 7, 5000, 5000): GRP}
     got = report(*(line(*random_pair(*c, "modp"), "modp") for c in cases))
     assert [r["mode"] for r in got] == list(cases.values())
+
+
+def test_bins_of_more_pairs_than_cells(report):
+    # 5^8 exponents: a prefix of four variables (bins of 1372 pairs) instead of
+    # three (12346, three rounds of ranks)
+    (r,) = report(line(*random_pair(8, 7, 4, 3000, 3000, "modp"), "modp"))
+    assert (r["mode"], r["S"]) == (GRP, 6561)
