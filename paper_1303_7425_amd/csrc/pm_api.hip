@@ -187,14 +187,16 @@ int stats_roundtrip(HostStage &hs, const pm_layout *L, int64_t count, const pm_c
     // pageable staging: one row per operand fits the statistics region of `dev`
     u64 *out = hs.fixed ? (u64 *)dev : rows;
     const int w = 2 * nv + 2, nrows = nops * parts;
-    for (int r = 0; r < nrows; r++) rows[(size_t)r * w + w - 1] = 0;
+    const bool poll = sync && !hs.fixed && nrows <= ST_POLL_ROWS;
+    for (int r = 0; r < nrows && poll; r++) rows[(size_t)r * w + w - 1] = 0;
     if (e == hipSuccess) e = launch_stats(ops, dsegs, nops, parts, nv, (int)L->bits, L->ring, out, 1, st);
     if (e == hipSuccess && hs.fixed) e = hipMemcpyAsync(rows, dev, rowb, hipMemcpyDeviceToHost, st);
     if (e == hipSuccess && sync) {
         // the rows' last words are polled for a while (a stream
-        // synchronisation takes some 10 us longer to return), then waited for
+        // synchronisation takes some 10 us longer to return, clearing and
+        // reading the words of thousands of rows as much), then waited for
         bool all = false;
-        if (!hs.fixed) {
+        if (poll) {
             const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(200);
             int r = 0;
             do {

@@ -354,6 +354,7 @@ struct DescArg {
     u32 w[960];
 };
 constexpr int ST_TERMS = 2048;       // terms of a statistics workgroup, while there are few operands
+constexpr int ST_POLL_ROWS = 1024;    // rows that the host polls for, at most
 constexpr int ST_MAX_ROWS = 4096;    // rows of a statistics launch, unless its operands alone are more
 
 // Validation flags reported by the statistics kernel.

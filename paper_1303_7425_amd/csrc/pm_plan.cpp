@@ -123,10 +123,13 @@ struct GpTry {
     int64_t bytes = 0;  // of workspace
 };
 
-// Groups of both operands at every depth (prefixes of 1, 2, ... variables).
-struct GpCounts {
-    std::vector<int64_t> f, g;
+// What the general plan's pass finds out about prefix groups.
+struct GpProbe {
+    std::vector<int64_t> old_bytes, bytes;  // workspace of every product's arrays: in the general plan, by prefix groups
+    bool pays = false;                      // some product's groups pay
 };
+
+constexpr double GP_MIN_PAIRS = 4096;  // a product of fewer is not tried: latencies bound every path there, planning too
 
 // The split of a product's keys into prefix and bin, from sizes and ranges
 // alone.  way 1: bins that fit direct cells, with a few to a work item for
@@ -233,11 +236,10 @@ static void gp_list(GpTry &t, double pairs, unsigned __int128 box, double cus) {
 // every outer group up (at most two lookups per pair, where the staged path
 // spends hundreds of instructions); a block below four pairs leaves most of
 // its lanes idle.  The bitmap needs some pairs per span to pay for its scan.
-static bool gp_pays(const GpTry &t, const GpCounts &c, int64_t na, int64_t nb, unsigned __int128 box, bool dense,
+static bool gp_pays(const GpTry &t, double gf, double gg, int64_t na, int64_t nb, unsigned __int128 box, bool dense,
                     int way, bool f64) {
     const double pairs = (double)na * (double)nb;
-    const double gf = (double)c.f[t.g.d - 1], gg = (double)c.g[t.g.d - 1];
-    if (pairs < 4096 || gf < 1 || gg < 1) return false;
+    if (gf < 1 || gg < 1) return false;
     if (f64) {
         // a wave adds one row of one inner group at a time: a step per outer
         // term and inner group, which the radix sort's cost per pair buys
@@ -268,9 +270,6 @@ static bool gp_pays(const GpTry &t, const GpCounts &c, int64_t na, int64_t nb, u
     return way == 1 ? block >= 4 : t.g.rows || block >= 1.5;
 }
 
-// counts: null, or the group counts of every product; products that pay then
-// run by prefix groups.  old_bytes: workspace that each product's own arrays
-// take in the general plan (counts null).
 // A product that one workgroup sorts and sums in LDS: TINY_PAIRS is what its
 // LDS holds, and up to there it is the fastest path at every ring and density
 // (57 x 61 random FP64 terms in 6 variables: 121 us by the radix sort, now 55).
@@ -278,10 +277,13 @@ static bool tiny_fits(int64_t na, int64_t nb, unsigned __int128 box) {
     return (unsigned __int128)na * nb <= (unsigned)TINY_PAIRS && box <= (unsigned __int128)0xFFFFFFFFull;
 }
 
+// counted: the minima's upper halves hold group counts (smask takes them off).
+// probe: the general plan, and what prefix groups would need and whether some
+// product's pay; without it such products run by them, and with `tiny` one
+// that fits runs by a single workgroup.
 static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> &in, const uint64_t *stats,
-                     const uint32_t *flags, const Tuning &tune_in, Plan &P, int cus, uint64_t smask,
-                     const std::vector<GpCounts> *counts, std::vector<int64_t> *old_bytes,
-                     std::vector<int64_t> *gp_bytes, bool tiny = false) {
+                     const uint32_t *flags, const Tuning &tune_in, Plan &P, int cus, uint64_t smask, bool counted,
+                     GpProbe *probe, bool tiny = false) {
     const int S = (int)in.size();
     P = Plan();
     P.nseg = S;
@@ -412,6 +414,7 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
             d.mode = SEG_TINY;
             continue;
         }
+        if ((double)d.na * (double)d.nb < GP_MIN_PAIRS) continue;
         // compute units that the product's share of the launch keeps busy (work
         // items as for the whole chip each made a burst of 14 products of 0.2 to
         // 4 million pairs spend 780 us in their reductions)
@@ -419,14 +422,14 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
         for (int way = 1; way <= 2 && !gt[q].ok; way++) {
             GpTry t = gp_try(nvars, &P.vars[(size_t)q * nvars], d.na, d.nb, box[q], dense, share, way, ring == RING_F64);
             if (!t.ok) continue;
-            if (gp_bytes) (*gp_bytes)[q] = std::max((*gp_bytes)[q], t.bytes);
-            if (!counts) continue;
-            const double gf = (double)(*counts)[q].f[t.g.d - 1], gg = (double)(*counts)[q].g[t.g.d - 1];
+            if (probe) probe->bytes[q] = std::max(probe->bytes[q], t.bytes);
+            if (!counted || (probe && probe->pays)) continue;
+            const uint64_t *st = stats + (size_t)q * 4 * nvars;
+            const double gf = (double)(st[t.g.d - 1] >> 32), gg = (double)(st[2 * nvars + t.g.d - 1] >> 32);
             const double pairs = (double)d.na * (double)d.nb;
             // prefixes within the operands' ranges, which their groups are some of
             double cf = 1, cg = 1;
             for (uint32_t v = 0; v < t.g.d; v++) {
-                const uint64_t *st = stats + (size_t)q * 4 * nvars;
                 cf *= (double)(st[nvars + v] - (st[v] & smask)) + 1;
                 cg *= (double)(st[3 * nvars + v] - (st[2 * nvars + v] & smask)) + 1;
             }
@@ -455,7 +458,10 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
             }
             // so few bins leave compute units idle (39 bins: 1368 us, by tiles 411; 199 bins: 329, 570)
             if (dense && way == 2 && t.g.nbins < share / 2) continue;
-            if (gp_pays(t, (*counts)[q], d.na, d.nb, box[q], dense, way, ring == RING_F64)) {
+            if (!gp_pays(t, gf, gg, d.na, d.nb, box[q], dense, way, ring == RING_F64)) continue;
+            if (probe) {
+                probe->pays = true;
+            } else {
                 gt[q] = t;
                 gt[q].g.swap = gg < gf ? 1 : 0;
                 if (ring == RING_F64) {
@@ -691,9 +697,9 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
             d.nb_div = make_div32((uint32_t)d.nb);
             P.nbk++;
         }
-        if (old_bytes) {
+        if (probe) {
             const int64_t pairs = d.na * d.nb;
-            int64_t &b = (*old_bytes)[q];
+            int64_t &b = probe->old_bytes[q];
             if (d.mode == SEG_BKT) b = 4 * (d.na + d.nb) + 12 * pairs + 6 * d.bk_nsb * BK_SB;
             if (d.mode == SEG_RAW || d.mode == SEG_COMBINE) b = 2 * (int64_t)(P.ksize + P.vsize) * pairs;
         }
@@ -882,31 +888,24 @@ int plan_build(int nvars, int bits, int ring, const std::vector<SegInput> &in, c
     // with wider fields (one variable) a minimum takes the whole word
     counted = counted && bits <= 32;
     const uint64_t smask = counted ? 0xFFFFFFFFull : ~0ull;
-    std::vector<int64_t> old_bytes(S, 0), gp_bytes(S, 0);
-    int rc = plan_core(nvars, bits, ring, in, stats, flags, tune, P, cus, smask, nullptr, &old_bytes, &gp_bytes);
+    GpProbe probe;
+    probe.old_bytes.assign(S, 0);
+    probe.bytes.assign(S, 0);
+    int rc = plan_core(nvars, bits, ring, in, stats, flags, tune, P, cus, smask, counted, &probe);
     if (rc) return rc;
     int64_t more = 0, any = 0;
     for (size_t q = 0; q < S; q++) {
-        any += gp_bytes[q];
-        more += std::max<int64_t>(0, gp_bytes[q] - old_bytes[q]);
+        any += probe.bytes[q];
+        more += std::max<int64_t>(0, probe.bytes[q] - probe.old_bytes[q]);
     }
     P.report = P.total + (any ? align256((size_t)more + 4096) : 0);
     const size_t report = P.report, general = P.total;
     // a product on its own only: a launch of several, some of them such, has
     // faulted the GPU once, for a reason not found
     const bool tiny = tune.tiny && S == 1 && P.segs[0].mode != SEG_EMPTY && tiny_fits(in[0].na, in[0].nb, 1);
-    if (limit < (int64_t)general || !((any && counted) || tiny)) return PM_OK;
-    std::vector<GpCounts> counts(counted ? S : 0);
-    for (size_t q = 0; q < counts.size(); q++) {
-        const uint64_t *st = stats + q * 4 * nvars;
-        for (int v = 0; v < nvars; v++) {
-            counts[q].f.push_back((int64_t)(st[v] >> 32));
-            counts[q].g.push_back((int64_t)(st[2 * nvars + v] >> 32));
-        }
-    }
+    if (limit < (int64_t)general || !(probe.pays || tiny)) return PM_OK;
     Plan G;
-    rc = plan_core(nvars, bits, ring, in, stats, flags, tune, G, cus, smask, counted ? &counts : nullptr, nullptr, nullptr,
-                   tiny);
+    rc = plan_core(nvars, bits, ring, in, stats, flags, tune, G, cus, smask, counted, nullptr, tiny);
     if (rc || !(G.ngp || G.ntiny) || (int64_t)G.total > limit) return PM_OK;
     P = std::move(G);
     P.total = std::max(P.total, general);

@@ -420,3 +420,24 @@ def test_boxes_of_single_terms(ring, shape, keep):
     assert "gp_box" in pm.profile_read()
     pm.profile_enable(False)
     assert_same(got, oracle.mul(f, g), ring, f"{shape} {keep}")
+
+
+@pytest.mark.parametrize("count", [511, 512, 513, 1500])
+def test_batches_of_more_rows_than_are_polled(count):
+    # two statistics rows per product: up to 1024 are polled, more waited for;
+    # the second call with other operands, so that rows left behind are stale
+    pm = _pm()
+    import oracle
+    import torch
+    rng = W.rng_for(count)
+
+    def pairs(top):
+        return [tuple(W.random_sparse(rng, m, 3, 12, top, "i64") for m in (1 + q % 7, 1 + q % 11)) for q in range(count)]
+
+    for p in (pairs(9), pairs(1500)):
+        got = pm.mul_batch((3, 12, "i64"), [pm.to_device(f) for f, _ in p], [pm.to_device(g) for _, g in p])
+        torch.cuda.synchronize()
+        assert pm.last_call_status() == 0
+        for q in list(range(0, count, 37)) + [count - 1]:
+            wk, wc, _ = oracle.mul(*p[q])
+            assert np.array_equal(got[q][0], wk) and np.array_equal(np.asarray(got[q][1]).view(np.uint64), np.asarray(wc).view(np.uint64))
