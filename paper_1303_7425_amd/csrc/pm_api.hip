@@ -481,9 +481,14 @@ int pm_mul_batch_drain(const pm_layout *layout, int64_t count, const pm_cpoly *f
     starts.push_back(count);
     const int64_t nw = (int64_t)starts.size() - 1;
     hipStream_t cst = nullptr;
+    hipEvent_t ran[2] = {nullptr, nullptr};  // the kernels of a wave have run, by parity
     hipError_t e = hipStreamCreateWithFlags(&cst, hipStreamNonBlocking);
+    for (int i = 0; i < 2 && e == hipSuccess; i++) e = hipEventCreateWithFlags(&ran[i], hipEventDisableTiming);
     if (e != hipSuccess) {
         set_error("hipStreamCreate", e);
+        for (hipEvent_t ev : ran)
+            if (ev) (void)hipEventDestroy(ev);
+        if (cst) (void)hipStreamDestroy(cst);
         return PM_EDEVICE;
     }
     // device layout of a wave in its half: counts, then per product keys and
@@ -493,12 +498,14 @@ int pm_mul_batch_drain(const pm_layout *layout, int64_t count, const pm_cpoly *f
         char *base = nullptr;
         std::vector<size_t> ok, oc;
         size_t ws_off = 0;
+        hipEvent_t ran = nullptr;
     };
     auto place = [&](int64_t w) {
         Wave W;
         W.a = starts[w];
         W.e = starts[w + 1];
         W.base = (char *)device_buffer + (size_t)(w & 1) * half;
+        W.ran = ran[w & 1];
         size_t o = al(8 * (size_t)(W.e - W.a));
         for (int64_t q = W.a; q < W.e; q++) {
             W.ok.push_back(o);
@@ -510,13 +517,13 @@ int pm_mul_batch_drain(const pm_layout *layout, int64_t count, const pm_cpoly *f
         return W;
     };
     std::vector<int64_t> counts;
-    // copy wave W's results to the host buffer on the copy stream (after its
-    // kernels, which the next wave's validation round trip has waited for),
-    // then hand them to the caller
+    // copy wave W's results to the host buffer on the copy stream, after its
+    // kernels, then hand them to the caller
     auto drain = [&](const Wave &W) -> int {
         const int64_t n = W.e - W.a;
         counts.resize(n);
-        hipError_t x = hipMemcpyAsync(counts.data(), W.base, 8 * (size_t)n, hipMemcpyDeviceToHost, cst);
+        hipError_t x = hipStreamWaitEvent(cst, W.ran, 0);
+        if (x == hipSuccess) x = hipMemcpyAsync(counts.data(), W.base, 8 * (size_t)n, hipMemcpyDeviceToHost, cst);
         if (x == hipSuccess) x = hipStreamSynchronize(cst);
         char *hp = (char *)host_buffer;
         std::vector<std::pair<char *, char *>> at(n);
@@ -550,6 +557,10 @@ int pm_mul_batch_drain(const pm_layout *layout, int64_t count, const pm_cpoly *f
                            W.base + W.oc[i]};
         rc = mul_impl(g_stage, layout, n, f + W.a, g + W.a, h.data(), W.base + W.ws_off,
                       (int64_t)(half - W.ws_off), st, g_tune, nullptr);
+        if (rc == PM_OK && (e = hipEventRecord(W.ran, st)) != hipSuccess) {
+            set_error("hipEventRecord", e);
+            rc = PM_EDEVICE;
+        }
         if (rc == PM_OK && have_prev) rc = drain(prev);  // overlaps wave w on the device
         prev = W;
         have_prev = true;
@@ -560,6 +571,7 @@ int pm_mul_batch_drain(const pm_layout *layout, int64_t count, const pm_cpoly *f
         if (e != hipSuccess) set_error("drain", e);
     }
     (void)hipStreamSynchronize(cst);
+    for (hipEvent_t ev : ran) (void)hipEventDestroy(ev);
     (void)hipStreamDestroy(cst);
     if (waves_out) *waves_out = nw;
     return rc;
