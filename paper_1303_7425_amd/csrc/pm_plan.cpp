@@ -240,6 +240,7 @@ static bool gp_pays(const GpTry &t, double gf, double gg, int64_t na, int64_t nb
                     int way, bool f64) {
     const double pairs = (double)na * (double)nb;
     if (gf < 1 || gg < 1) return false;
+    const double cells = std::min<double>(t.g.nbins, gf * gg) * t.g.S;  // of the non-empty bins, at most
     if (f64) {
         // a wave adds one row of one inner group at a time: a step per outer
         // term and inner group, which the radix sort's cost per pair buys
@@ -255,9 +256,25 @@ static bool gp_pays(const GpTry &t, double gf, double gg, int64_t na, int64_t nb
         const double cols = (double)nb / gg, steps = (double)na * gg * std::ceil(cols / 64);
         const double step = t.g.S <= 1024 ? 100 : t.g.S <= 2048 ? 140 : 210;
         const double bins = std::min(std::min<double>(t.items, 16 * (gf + gg) + pairs / t.g.T), gf * gg);
+        // the fullest bin's rows come one after another, 32 ns each; the sort
+        // sums long runs of like terms one by one
+        if (steps / std::max(gf, gg) * 32000 > 90e6 + (pairs > 32 * cells ? 64 : 32) * pairs) return false;
         return bins * 7000 + steps * step + gf * gg * 100 <= 20e6 + 32 * pairs + 400 * (double)(na + nb);
     }
     if ((double)t.items * std::min(gf, gg) > (t.g.rows ? 8 : 2) * pairs) return false;
+    if (!t.g.rows || dense) {
+        // A bin is one work item, however many pairs it has: where the operands
+        // have few groups the fullest one, a block of each, outlasts the rest
+        // (1378 x 8605 terms in 3 groups each 8.5 ms, by the staged work items
+        // 0.24).  One workgroup takes 0.35 ns and more per pair and sweep: direct
+        // cells take one, ranks two and one more per 4096 keys.  The staged work
+        // items take 15 ps per pair beyond what both have, and three times that
+        // where fine bins hold few pairs or more than a work item's.
+        const double most = pairs / std::max(gf, gg);
+        const double sweeps = t.g.S <= (uint32_t)GP_CELLS ? 1 : 1 + std::ceil(std::min<double>(most, t.g.S) / GP_CELLS);
+        const bool slow = !dense && (8 * cells > pairs || 8 * (double)box > 4096 * cells);
+        if (most * sweeps * 350 > (slow ? 200e6 + 45 * pairs : 60e6 + 15 * pairs)) return false;
+    }
     // beyond 32-bit keys the alternative is the pair-index sort, some 62 ps per
     // pair; a listed work item takes 27 ns and its pairs 34 ps with their
     // placement, a pair of groups 18 ps (300 x 20000 terms of 4^12 exponents

@@ -174,3 +174,17 @@ def test_bins_of_more_pairs_than_cells(report):
     # three (12346, three rounds of ranks)
     (r,) = report(line(*random_pair(8, 7, 4, 3000, 3000, "modp"), "modp"))
     assert (r["mode"], r["S"]) == (GRP, 6561)
+
+
+def test_products_of_few_bins(report):
+    # three leading exponents each: five non-empty bins, however many pairs;
+    # a whole range of them keeps the prefix groups
+    def slabs(shape, step):
+        e = np.indices(shape).reshape(len(shape), -1).T * np.array(step)
+        return W.Poly(W.Layout(2, 16, "modp"), np.sort(W.pack(e, 2, 16)), np.ones(len(e), np.uint64))
+
+    few = slabs((3, 460), (500, 7)), slabs((3, 2870), (500, 1))
+    box = slabs((3, 400), (200, 1)), slabs((3, 400), (200, 1))
+    many = slabs((60, 23), (25, 7)), slabs((60, 140), (25, 1))
+    got = report(line(*few, "modp"), line(*box, "modp"), line(*many, "modp"), line(*few, "f64"), line(*many, "f64"))
+    assert [r["mode"] for r in got] == [BKT, DENSE, GRPD, RAW, GRP]
