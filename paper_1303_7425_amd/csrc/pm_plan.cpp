@@ -456,9 +456,10 @@ static int plan_core(int nvars, int bits, int ring, const std::vector<SegInput> 
                                       : std::max(1.0, std::min<double>(t.g.span_bins, (double)t.g.nbins * t.g.T / pairs));
             const double met = pairs / (gf * gg) * bins;
             // (blocks of a pair or two take 8 times as long as a term each: 10002 by
-            // 10002 of 100000 exponents 4422 us, 376)
+            // 10002 of 100000 exponents 4422 us, 376; small blocks far apart twice as
+            // long as listed: 3917 x 7693 terms in 1600 clusters 1244 us, 631)
             const bool single = dense && t.g.S == 1 && met * fill < 40;  // one term to a prefix, few prefixes to a work item
-            if (gf >= 1 && gg >= 1 && (met < 32 || (dense && met * fill < 16) || single)) {
+            if (gf >= 1 && gg >= 1 && (met < 32 || ((dense || pairs < 16 * gf * gg) && met * fill < 16) || single)) {
                 if (dense) t.g.rows = 1;
                 else if (ring != RING_F64) gp_list(t, pairs, box[q], share);
             }

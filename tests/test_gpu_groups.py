@@ -441,3 +441,17 @@ def test_batches_of_more_rows_than_are_polled(count):
         for q in list(range(0, count, 37)) + [count - 1]:
             wk, wc, _ = oracle.mul(*p[q])
             assert np.array_equal(got[q][0], wk) and np.array_equal(np.asarray(got[q][1]).view(np.uint64), np.asarray(wc).view(np.uint64))
+
+
+@pytest.mark.parametrize("ring", ["modp", "modq"])
+def test_listed_clusters(ring):
+    # blocks of some 14 pairs, their prefixes far apart
+    rng = W.rng_for(3)
+
+    def clusters(count, n, shape, width):
+        c = rng.integers(0, shape, (count, 2))
+        e = np.concatenate([c[rng.integers(0, count, n)], rng.integers(0, width, n)[:, None]], 1)
+        keys = np.unique(W.pack(e, 3, 16))
+        return W.with_random_coefs(W.Poly(W.Layout(3, 16, ring), keys, np.zeros(len(keys), np.uint64)), rng, ring)
+
+    takes_groups(clusters(1600, 4000, (480, 700), 60), clusters(1600, 8000, (480, 700), 60), "clusters", "gp_reduce_list")

@@ -188,3 +188,20 @@ def test_products_of_few_bins(report):
     many = slabs((60, 23), (25, 7)), slabs((60, 140), (25, 1))
     got = report(line(*few, "modp"), line(*box, "modp"), line(*many, "modp"), line(*few, "f64"), line(*many, "f64"))
     assert [r["mode"] for r in got] == [BKT, DENSE, GRPD, RAW, GRP]
+
+
+def test_small_blocks_far_apart(report):
+    # clusters: blocks of 14 pairs whose prefixes fill a few thousandths of
+    # their ranges are listed; blocks of 22 are not
+    rng = W.rng_for(3)
+
+    def clusters(count, n, shape, width):
+        c = rng.integers(0, shape, (count, 2))
+        e = np.concatenate([c[rng.integers(0, count, n)], rng.integers(0, width, n)[:, None]], 1)
+        keys = np.unique(W.pack(e, 3, 16))
+        return W.Poly(W.Layout(3, 16, "modp"), keys, np.ones(len(keys), np.uint64))
+
+    near = clusters(1000, 2800, (300, 300), 93), clusters(1000, 5600, (300, 300), 93)
+    far = clusters(1600, 4000, (480, 700), 60), clusters(1600, 8000, (480, 700), 60)
+    got = report(line(*far, "modp"), line(*near, "modp"))
+    assert [(r["mode"], r["rows"] != 0) for r in got] == [(GRP, True), (GRP, False)]
