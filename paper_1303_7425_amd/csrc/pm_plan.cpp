@@ -266,14 +266,15 @@ static bool gp_pays(const GpTry &t, double gf, double gg, int64_t na, int64_t nb
         // A bin is one work item, however many pairs it has: where the operands
         // have few groups the fullest one, a block of each, outlasts the rest
         // (1378 x 8605 terms in 3 groups each 8.5 ms, by the staged work items
-        // 0.24).  One workgroup takes 0.35 ns and more per pair and sweep: direct
-        // cells take one, ranks two and one more per 4096 keys.  The staged work
-        // items take 15 ps per pair beyond what both have, and three times that
-        // where fine bins hold few pairs or more than a work item's.
+        // 0.24).  One workgroup takes at least 0.35 ns per pair in direct cells,
+        // 0.2 per pair and sweep in ranks: two sweeps and one more per 4096 keys.
+        // The staged work items take 15 ps per pair beyond what both have, and
+        // three times that where fine bins hold few pairs or more than a work
+        // item's.
         const double most = pairs / std::max(gf, gg);
-        const double sweeps = t.g.S <= (uint32_t)GP_CELLS ? 1 : 1 + std::ceil(std::min<double>(most, t.g.S) / GP_CELLS);
+        const double each = t.g.S <= (uint32_t)GP_CELLS ? 350 : 200 * (1 + std::ceil(std::min<double>(most, t.g.S) / GP_CELLS));
         const bool slow = !dense && (8 * cells > pairs || 8 * (double)box > 4096 * cells);
-        if (most * sweeps * 350 > (slow ? 200e6 + 45 * pairs : 60e6 + 15 * pairs)) return false;
+        if (most * each > (slow ? 200e6 + 45 * pairs : 60e6 + 15 * pairs)) return false;
     }
     // beyond 32-bit keys the alternative is the pair-index sort, some 62 ps per
     // pair; a listed work item takes 27 ns and its pairs 34 ps with their
