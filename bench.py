@@ -5,9 +5,8 @@ Workload (default): the large sparse 5-variable product
     f = (1+x+y+2z^2+3t^3+5u^5)^12,  g = (1+u+t+2z^2+3y^3+5x^5)^12
 (6188 terms each, 38,291,344 term products -> 5,821,335 terms), exponents
 packed 12 bits per variable, coefficients mod 2^61-1.  A step is one whole
-pm_mul (validation, key compression, LDS tile combine, radix passes,
-segmented reduction) with the operands resident in HBM, ending with the
-result count read back.  Prints one JSON line.
+pm_mul (validation, planning, every kernel of the path) with the operands
+resident in HBM, ending with the result count read back.  Prints one JSON line.
 """
 import argparse
 import json
@@ -63,6 +62,7 @@ def measured_step_traffic():
 
 # rocprofv3 kernel names -> the labels used in the summaries
 KERNEL_LABELS = [
+    ("k_gp_heads", "gp_heads (groups per part of the operands)"),
     ("k_gp_prep", "gp_prep (compressed terms, groups)"),
     ("k_gp_lut", "gp_lut (prefix table, pairs per bin)"),
     ("k_gp_cut", "gp_cut (bins to work items)"),
@@ -674,12 +674,18 @@ def main():
     dom_ms, dom_n = prof[dom]
     dom_avg_ms = dom_ms / max(dom_n, 1)
     pair_item = 8  # staged (compressed key, pair index), two u32
+    groups = any(k.startswith("gp_") for k in prof)
+    bound = "hbm"
     if dom in ("gp_reduce", "gp_reduce_list", "gp_box"):
         # writes each result term's key inside its work item (u32) and
-        # coefficient (u64); the operands' terms (16 bytes) come from cache
+        # coefficient (u64); the operands' terms (16 bytes) come from cache.
+        # What bounds it is the LDS additions and the instructions around them
         dom_bytes = n_out * 12 + (len(f) + len(g)) * 16
-        dom_kernel = "k_gp_reduce (pairs formed and summed in LDS)" if args.ring == "modp" else "k_gp_f64 (rows summed in LDS)"
-        dom_label = dom_kernel.replace("k_gp", "gp", 1)
+        bound = "lds+valu" if args.ring == "modp" else "latency"
+        dom_label = {"gp_reduce": "gp_reduce (pairs formed and summed in LDS)" if args.ring == "modp" else "gp_f64 (rows summed in LDS)",
+                     "gp_reduce_list": "gp_list (pairs listed and summed in LDS)",
+                     "gp_box": "gp_reduce (pairs formed and summed in LDS)"}[dom]
+        dom_kernel = "k_" + dom_label
     elif dom == "bk_reduce":
         # reads every staged pair once, writes each result term's key (u32)
         # and coefficient (u64); operand coefficients come from cache
@@ -695,9 +701,10 @@ def main():
         dom_bytes = staged * item_bytes * 2
         dom_kernel, dom_label = f"{dom} (radix pass)", "onesweep pass (pair indices)"
     achieved = dom_bytes / (dom_avg_ms * 1e-3) / 1e9 if dom_avg_ms > 0 else 0.0
-    # effective bandwidth: the product's algorithmic floor (22 B per term
-    # product: inputs, output, one spill of combined tiles) over the whole step
-    floor_bytes = 22.0 * products
+    # effective bandwidth: what the path cannot do without, over the whole step:
+    # by prefix groups every operand and result term once (16 B); where pairs are
+    # staged, 22 B per term product (inputs, output, one spill of combined tiles)
+    floor_bytes = 16.0 * (len(f) + len(g) + n_out) if groups else 22.0 * products
     effective = floor_bytes / (ms_step * 1e-3) / 1e9
 
     if args.copy_calibration:
@@ -731,7 +738,7 @@ def main():
             "bits_per_var": 12, "sparse_mode": {-1: "automatic", 0: "pair-index radix sort", 1: "LDS tile combine",
                                                 2: "output-key intervals", 3: "output-key work items"}[args.combine],
         },
-        "roofline": {"bound": "hbm", "kernel": dom_kernel, "achieved": achieved,
+        "roofline": {"bound": bound, "kernel": dom_kernel, "achieved": achieved,
                      "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
                      "traffic": measured_traffic(dom_label) if args.ring == "modp" else None,
                      "algorithmic_bytes_per_launch": dom_bytes, "avg_launch_ms": dom_avg_ms,
