@@ -38,7 +38,8 @@ constexpr int GP_SB = 1 << GP_SB_LOG;  // bins per super-bin (one workgroup of t
 constexpr int GP_CELLS = 4096;         // LDS cells of a work item
 constexpr int GP_SPAN_LOG = 17;        // key span (log2) of the presence bitmap
 constexpr int GP_MAX_S = 61440;        // cells of a bin, at most: a work item then has at most 2^16 keys (gp.T <= 4096 pairs before its last bin)
-constexpr int GP_F64_CELLS = 3840;     // FP64: LDS cells of a wave, at most (five waves per compute unit)
+constexpr int GP_F64_CELLS = 3840;     // FP64: LDS cells of a wave, at most (five waves per compute unit); wider bins, as the
+                                       // sparse family's from n = 13 on (4187), keep the sort: 2.4 ms at n = 13
 constexpr int GP_PAD = 1024;           // term slots after the last operand (loads past a block's rows)
 constexpr u32 GP_LUT_I = 1024;         // inner groups that a wave of k_gp_lut meets one outer group with
 constexpr int GP_PART = 16384;         // terms of a workgroup of k_gp_prep

@@ -134,9 +134,9 @@ constexpr double GP_MIN_PAIRS = 4096;  // a product of fewer is not tried: laten
 // The split of a product's keys into prefix and bin, from sizes and ranges
 // alone.  way 1: bins that fit direct cells, with a few to a work item for
 // the degree box (so that items can be cut to an even size: box cells over 16
-// rounds of the device, 512 to GP_CELLS); way 2 (sparse): bins that only fit
-// the presence bitmap.  The fewest prefix variables that do: fewer groups,
-// larger blocks.
+// rounds of the device, 512 to GP_CELLS); way 2: bins that only fit the
+// presence bitmap (sparse), or up to all direct cells (degree box).  The fewest
+// prefix variables that do: fewer groups, larger blocks.
 static GpTry gp_try(int nvars, const VarParam *vp, int64_t na, int64_t nb, unsigned __int128 box, bool dense, double cus,
                     int way, bool f64) {
     GpTry o;

@@ -296,7 +296,7 @@ def dirty(layout, f, g):
     return ws
 
 
-@pytest.mark.parametrize("ring", ["modp", "i64", "modq"])
+@pytest.mark.parametrize("ring", ["modp", "i64"])
 def test_box_runs_that_do_not_divide_evenly(ring):
     # a run of 9 bins of 899 cells: four bins fit a work item, five do not; the
     # runs at the box's ends have few pairs.  Every box cell is stored.
@@ -445,7 +445,7 @@ def test_batches_of_more_rows_than_are_polled(count):
 
 @pytest.mark.parametrize("ring", ["modp", "modq"])
 def test_listed_clusters(ring):
-    # blocks of some 14 pairs, their prefixes far apart
+    # blocks of some 5 pairs, their prefixes far apart
     rng = W.rng_for(3)
 
     def clusters(count, n, shape, width):
@@ -454,4 +454,4 @@ def test_listed_clusters(ring):
         keys = np.unique(W.pack(e, 3, 16))
         return W.with_random_coefs(W.Poly(W.Layout(3, 16, ring), keys, np.zeros(len(keys), np.uint64)), rng, ring)
 
-    takes_groups(clusters(1600, 4000, (480, 700), 60), clusters(1600, 8000, (480, 700), 60), "clusters", "gp_reduce_list")
+    takes_groups(clusters(1200, 2000, (240, 700), 60), clusters(1200, 4000, (240, 700), 60), "clusters", "gp_reduce_list")
