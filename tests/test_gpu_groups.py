@@ -454,4 +454,4 @@ def test_listed_clusters(ring):
         keys = np.unique(W.pack(e, 3, 16))
         return W.with_random_coefs(W.Poly(W.Layout(3, 16, ring), keys, np.zeros(len(keys), np.uint64)), rng, ring)
 
-    takes_groups(clusters(1200, 2000, (240, 700), 60), clusters(1200, 4000, (240, 700), 60), "clusters", "gp_reduce_list")
+    takes_groups(clusters(1600, 2600, (240, 700), 60), clusters(1600, 4000, (240, 700), 60), "clusters", "gp_reduce_list")
