@@ -775,13 +775,18 @@ int pm_autotune(const pm_layout *layout, const pm_cpoly *f, const pm_cpoly *g, c
     }
     hipEvent_t e0, e1;
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) return PM_EDEVICE;
-    // two runs after one to warm up; PM_ENOMEM: more workspace than given
+    // two runs after one to warm up.  PM_ENOMEM: more workspace than given, or a
+    // sparse mode that this product does not run by (another one's time would
+    // be remembered for it)
     auto time_of = [&](const TuneChoice &cd, float &total) -> int {
         Tuning t = base;
         t.tile_cfg = cd.tile_cfg;
         t.combine = cd.combine;
         t.digits = cd.digits;
-        int r = mul_impl(g_stage, layout, 1, f, g, h, workspace, workspace_bytes, st, t, nullptr);
+        Plan Pc;
+        int r = mul_impl(g_stage, layout, 1, f, g, h, workspace, workspace_bytes, st, t, &Pc);
+        const int named[] = {SEG_RAW, SEG_COMBINE, SEG_IVAL, SEG_BKT};
+        if (!r && !dense && cd.combine >= 0 && Pc.segs[0].mode != named[cd.combine]) return PM_ENOMEM;
         total = 0;
         for (int rep = 0; rep < 2 && !r; rep++) {
             (void)hipEventRecord(e0, st);
@@ -796,6 +801,7 @@ int pm_autotune(const pm_layout *layout, const pm_cpoly *f, const pm_cpoly *g, c
     };
     float best = 1e30f;
     TuneChoice choice = cands[0];
+    bool any = false;
     for (auto &cd : cands) {
         float total;
         rc = time_of(cd, total);
@@ -807,6 +813,7 @@ int pm_autotune(const pm_layout *layout, const pm_cpoly *f, const pm_cpoly *g, c
         if (total < best) {
             best = total;
             choice = cd;
+            any = true;
         }
     }
     const int m0 = P0.segs[0].mode;
@@ -818,7 +825,7 @@ int pm_autotune(const pm_layout *layout, const pm_cpoly *f, const pm_cpoly *g, c
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc) return rc;
-    tune_store(P0.cls, choice);
+    if (any) tune_store(P0.cls, choice);
     if (tile_cfg) *tile_cfg = choice.tile_cfg;
     if (combine) *combine = choice.combine;
     if (digits) *digits = choice.digits;

@@ -183,3 +183,16 @@ def test_autotune_keeps_the_paths_that_are_faster():
         want = oracle.mul(f, g)
         assert np.array_equal(got[0], want[0]) and np.array_equal(got[1].view(np.uint64), want[1].view(np.uint64))
     pm.autotune_reset()
+
+
+def test_autotune_remembers_modes_that_ran():
+    # over 8192 terms on both sides the output-key work items do not apply (the
+    # pair-index sort runs in their place): mode 3 is not what is remembered
+    pm = _pm()
+    pm.autotune_reset()
+    rng = W.rng_for(19)
+    f, g = (W.random_sparse(rng, m, 6, 10, 15, "f64") for m in (8300, 8400))
+    df, dg = pm.to_device(f), pm.to_device(g)
+    for _ in range(4):
+        assert pm.autotune((6, 10, "f64"), df, dg)[1] in (0, 2)
+    pm.autotune_reset()
