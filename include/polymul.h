@@ -127,8 +127,8 @@ int pm_mul_bound(const pm_layout *layout, const pm_cpoly *f, const pm_cpoly *g, 
  * Returns PM_OK once the product is enqueued on `stream`, or an error code
  * (nothing enqueued that writes h).  The plan depends on the operands'
  * exponent ranges, so the call waits once for the work on `stream` up to its
- * validation and statistics kernel, whose rows it polls in pinned memory for
- * up to 0.2 ms before it synchronises, and then enqueues the product; the
+ * validation and statistics kernel, whose rows (up to 1024) it polls in pinned
+ * memory for up to 0.2 ms before it synchronises, and then enqueues the product; the
  * kernels run asynchronously.  Calls from several threads are
  * serialised by one library lock (they share a pinned staging buffer).
  * pm_batch_prepare / pm_batch_launch replay a validated plan without the
